@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "fr_device.hpp"
 
@@ -246,105 +247,203 @@ __global__ __launch_bounds__(512) void mlp_forward_mfma_kernel(const float *__re
 
 // Gradient of L = sum_s |y_s - t_s|^2 / n over the samples idx[0..n) (or
 // 0..n), FP32 master weights; with stats, rows are standardised on load
-// (x - mu_x) / s_x and (t - mu_y) / s_y.  Each block (one wavefront) takes chunks of 64
-// samples: every lane runs one sample forward and backward, stages the
-// per-sample vectors in shared memory, then every lane sums the outer
-// products of the parameters it owns over the chunk into the block's
-// partial-gradient row (entry MLP_NPARAM holds the partial loss).
-__global__ __launch_bounds__(64) void mlp_grad_kernel(const float *__restrict__ P,
-                                                      const float *__restrict__ X,
-                                                      const float *__restrict__ Tg,
-                                                      const int32_t *__restrict__ idx,
-                                                      int64_t n, const float *__restrict__ stats,
-                                                      float *__restrict__ partial) {
-    __shared__ float Xs[64][MLP_IN];
-    __shared__ float H1[64][MLP_H], H2[64][MLP_H], D1[64][MLP_H], D2[64][MLP_H], DY[64][MLP_OUT];
-    const int tid = threadIdx.x;
-    float *part = partial + int64_t(blockIdx.x) * (MLP_NPARAM + 1);
-    for (int p = tid; p <= MLP_NPARAM; p += 64) part[p] = 0.0f;
-    __syncthreads();
-    const float inv_n = 1.0f / float(n);
-    for (int64_t c0 = int64_t(blockIdx.x) * 64; c0 < n; c0 += int64_t(gridDim.x) * 64) {
-        const int64_t s = c0 + tid;
-        const bool live = s < n;
-        const int64_t row = live ? (idx ? int64_t(idx[s]) : s) : 0;
-        for (int k = 0; k < MLP_IN; ++k) {
-            float x = live ? X[row * MLP_IN + k] : 0.0f;
-            if (stats && live) x = (x - stats[k]) / stats[MLP_IN + k];
-            Xs[tid][k] = x;
-        }
-        for (int j = 0; j < MLP_H; ++j) {
-            float z = P[OB1 + j];
-            for (int k = 0; k < MLP_IN; ++k) z += P[OW1 + j * MLP_IN + k] * Xs[tid][k];
-            H1[tid][j] = tanhf(z);
-        }
-        for (int j = 0; j < MLP_H; ++j) {
-            float z = P[OB2 + j];
-            for (int k = 0; k < MLP_H; ++k) z += P[OW2 + j * MLP_H + k] * H1[tid][k];
-            H2[tid][j] = tanhf(z);
-        }
-        float loss = 0.0f;
-        for (int o = 0; o < MLP_OUT; ++o) {
-            float z = P[OB3 + o];
-            for (int k = 0; k < MLP_H; ++k) z += P[OW3 + o * MLP_H + k] * H2[tid][k];
-            float t = live ? Tg[row * MLP_OUT + o] : 0.0f;
-            if (stats) t = (t - stats[2 * MLP_IN + o]) / stats[2 * MLP_IN + MLP_OUT + o];
-            const float d = live ? z - t : 0.0f;
-            loss += d * d;
-            DY[tid][o] = 2.0f * d * inv_n;
-        }
-        for (int j = 0; j < MLP_H; ++j) {          // dz2 = (W3^T dy) (1 - h2^2)
-            float a = 0.0f;
-            for (int o = 0; o < MLP_OUT; ++o) a += P[OW3 + o * MLP_H + j] * DY[tid][o];
-            D2[tid][j] = a * (1.0f - H2[tid][j] * H2[tid][j]);
-        }
-        for (int j = 0; j < MLP_H; ++j) {          // dz1 = (W2^T dz2) (1 - h1^2)
-            float a = 0.0f;
-            for (int k = 0; k < MLP_H; ++k) a += P[OW2 + k * MLP_H + j] * D2[tid][k];
-            D1[tid][j] = a * (1.0f - H1[tid][j] * H1[tid][j]);
-        }
-        __syncthreads();
-        // outer products summed over the chunk; lane tid owns every 64th parameter
-        for (int p = tid; p < MLP_NPARAM; p += 64) {
-            float a = 0.0f;
-            if (p < OB1) {
-                const int j = p / MLP_IN, k = p % MLP_IN;
-                for (int q = 0; q < 64; ++q) a += D1[q][j] * Xs[q][k];
-            } else if (p < OW2) {
-                for (int q = 0; q < 64; ++q) a += D1[q][p - OB1];
-            } else if (p < OB2) {
-                const int j = (p - OW2) / MLP_H, k = (p - OW2) % MLP_H;
-                for (int q = 0; q < 64; ++q) a += D2[q][j] * H1[q][k];
-            } else if (p < OW3) {
-                for (int q = 0; q < 64; ++q) a += D2[q][p - OB2];
-            } else if (p < OB3) {
-                const int o = (p - OW3) / MLP_H, k = (p - OW3) % MLP_H;
-                for (int q = 0; q < 64; ++q) a += DY[q][o] * H2[q][k];
-            } else {
-                for (int q = 0; q < 64; ++q) a += DY[q][p - OB3];
-            }
-            part[p] += a;
-        }
-        // partial loss: lane 0 sums the chunk's per-lane losses through shared memory
-        __syncthreads();
-        H1[tid][0] = loss;
-        __syncthreads();
-        if (tid == 0) {
-            float l = 0.0f;
-            for (int q = 0; q < 64; ++q) l += H1[q][0];
-            part[MLP_NPARAM] += l * inv_n;
-        }
-        __syncthreads();
+// (x - mu_x) / s_x and (t - mu_y) / s_y.
+//
+// A workgroup of eight wavefronts takes tiles of 32 samples, every product on
+// the FP32 matrix cores: wavefront w owns the 16 x 16 output block (sample
+// block w % 2, unit block w / 2) of each layer's forward and backward
+// product, so the weight fragments it needs (83 registers) are loaded once
+// and stay in registers over all its tiles, as do its seven blocks of the
+// weight gradients (products of a tile's 32 samples as the K dimension).
+// Activations and deltas pass through LDS with odd row strides.  A workgroup
+// writes its row of partial gradients once, at the end (entry MLP_NPARAM is
+// its loss); mlp_reduce_kernel adds the rows in order.  Bound by latency at
+// the training loop's batch of 8,192 (256 tiles, one per CU: 0.5 GFLOP).
+// One lane per sample with the weights from memory and 128 workgroups of one
+// wavefront measured 866 us there, and its one-thread-per-parameter
+// reduction 31 us.
+constexpr int GRD_S = 32, GRD_THREADS = 512;
+constexpr int GRD_XP = MLP_IN + 9, GRD_HP = MLP_H + 1, GRD_YP = 33;   // padded LDS rows (128 input columns are read)
+__global__ __launch_bounds__(GRD_THREADS) void mlp_grad_kernel(const float *__restrict__ P,
+                                                               const float *__restrict__ X,
+                                                               const float *__restrict__ Tg,
+                                                               const int32_t *__restrict__ idx,
+                                                               int64_t n, const float *__restrict__ stats,
+                                                               float *__restrict__ partial) {
+    __shared__ float Xs[GRD_S][GRD_XP];
+    __shared__ float H1[GRD_S][GRD_HP], H2[GRD_S][GRD_HP], D1[GRD_S][GRD_HP], D2[GRD_S][GRD_HP];
+    __shared__ float St[MLP_NSTATS];                 // statistics (no statistics: 0 and 1, which change no value)
+    __shared__ float DY[GRD_S][GRD_YP];              // targets, then 2 (y - t) / n; columns past the 20 outputs zero
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+    const int sb = 16 * (w & 1), jb = w >> 1;        // first sample, unit block of this wavefront
+    const int unit = 16 * jb + r16;                  // the unit of this lane's accumulator column
+    constexpr int K1 = MLP_IN / 4, K2 = MLP_H / 4, K3 = MLP_OUT / 4;
+
+    // weight fragments: forward W_l[16 jb + lane % 16][4 kb + lane / 16],
+    // backward (transposed products) W_l[4 kb + lane / 16][16 jb + lane % 16]
+    float w1[K1], w2[K2], w3[K2], t3[K3], t2[K2];
+#pragma unroll
+    for (int kb = 0; kb < K1; ++kb) w1[kb] = opaque(P[OW1 + unit * MLP_IN + 4 * kb + g]);
+#pragma unroll
+    for (int kb = 0; kb < K2; ++kb) {
+        w2[kb] = opaque(P[OW2 + unit * MLP_H + 4 * kb + g]);
+        w3[kb] = opaque(unit < MLP_OUT ? P[OW3 + unit * MLP_H + 4 * kb + g] : 0.0f);
+        t2[kb] = opaque(P[OW2 + (4 * kb + g) * MLP_H + unit]);
     }
+#pragma unroll
+    for (int kb = 0; kb < K3; ++kb) t3[kb] = opaque(P[OW3 + (4 * kb + g) * MLP_H + unit]);
+    const float bias1 = P[OB1 + unit], bias2 = P[OB2 + unit], bias3 = unit < MLP_OUT ? P[OB3 + unit] : 0.0f;
+
+    for (int i = tid; i < MLP_NSTATS; i += GRD_THREADS)
+        St[i] = stats ? stats[i] : (i < MLP_IN || (i >= 2 * MLP_IN && i < 2 * MLP_IN + MLP_OUT)) ? 0.0f : 1.0f;
+    for (int i = tid; i < GRD_S * GRD_YP; i += GRD_THREADS) (&DY[0][0])[i] = 0.0f;
+    for (int i = tid; i < GRD_S * GRD_XP; i += GRD_THREADS) (&Xs[0][0])[i] = 0.0f;
+
+    f32x4 g1[4], g2[2], g3;                          // weight-gradient blocks
+#pragma unroll
+    for (int c = 0; c < 4; ++c) g1[c] = f32x4{0, 0, 0, 0};
+    g2[0] = g2[1] = g3 = f32x4{0, 0, 0, 0};
+    float gb = 0.0f, loss = 0.0f;                    // one bias gradient per thread (148 threads), the lane's losses
+
+    const float inv_n = 1.0f / float(n);
+    const int64_t ntiles = (n + GRD_S - 1) / GRD_S;
+    // the tile's inputs and targets, fetched one tile ahead: 16 threads per
+    // sample, input k = 16 q + tid % 16 (one row address per thread)
+    const int fs = tid >> 4, fk = tid & 15;
+    constexpr int NX = (MLP_IN + 15) / 16, NT = (MLP_OUT + 15) / 16;
+    float xr[NX], tr[NT];
+    auto fetch = [&](int64_t tile) {
+        const int64_t s = tile * GRD_S + fs;
+        const int64_t row = s < n ? (idx ? int64_t(idx[s]) : s) : 0;
+        const float *x = X + row * MLP_IN + fk, *t = Tg + row * MLP_OUT + fk;
+#pragma unroll
+        for (int q = 0; q < NX; ++q) xr[q] = s < n && 16 * q + fk < MLP_IN ? x[16 * q] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) tr[q] = s < n && 16 * q + fk < MLP_OUT ? t[16 * q] : 0.0f;
+    };
+    // block of A[16 rows of LDS array a from sample sb][K] x fragments
+    auto product = [&](const float *a, int stride, const float *frag, auto kc) {
+        f32x4 acc{0, 0, 0, 0};
+        constexpr int K = decltype(kc)::value;
+#pragma unroll
+        for (int kb = 0; kb < K; ++kb)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[(sb + r16) * stride + 4 * kb + g], frag[kb], acc, 0, 0, 0);
+        return acc;
+    };
+    fetch(blockIdx.x);
+    for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        __syncthreads();                             // the previous tile's arrays are free (and zeroed at first)
+        const bool live = tile * GRD_S + fs < n;     // inputs of samples past n are zero
+#pragma unroll
+        for (int q = 0; q < NX; ++q) {
+            const int k = 16 * q + fk;
+            if (k < MLP_IN) Xs[fs][k] = live ? (xr[q] - St[k]) / St[MLP_IN + k] : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const int o = 16 * q + fk;
+            if (o < MLP_OUT) DY[fs][o] = (tr[q] - St[2 * MLP_IN + o]) / St[2 * MLP_IN + MLP_OUT + o];
+        }
+        __syncthreads();
+        if (tile + gridDim.x < ntiles) fetch(tile + gridDim.x);
+        const f32x4 z1 = product(&Xs[0][0], GRD_XP, w1, std::integral_constant<int, K1>{});
+        float h1[4], h2[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) H1[sb + 4 * g + r][unit] = h1[r] = tanhf(z1[r] + bias1);
+        __syncthreads();
+        const f32x4 z2 = product(&H1[0][0], GRD_HP, w2, std::integral_constant<int, K2>{});
+#pragma unroll
+        for (int r = 0; r < 4; ++r) H2[sb + 4 * g + r][unit] = h2[r] = tanhf(z2[r] + bias2);
+        __syncthreads();
+        if (jb < 2) {
+            const f32x4 y = product(&H2[0][0], GRD_HP, w3, std::integral_constant<int, K2>{});
+            if (unit < MLP_OUT) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int s = sb + 4 * g + r;
+                    const float d = tile * GRD_S + s < n ? y[r] + bias3 - DY[s][unit] : 0.0f;
+                    loss += d * d;
+                    DY[s][unit] = 2.0f * d * inv_n;
+                }
+            }
+        }
+        __syncthreads();
+        // dz2 = (W3^T dy) (1 - h2^2), dz1 = (W2^T dz2) (1 - h1^2)
+        const f32x4 e2 = product(&DY[0][0], GRD_YP, t3, std::integral_constant<int, K3>{});
+#pragma unroll
+        for (int r = 0; r < 4; ++r) D2[sb + 4 * g + r][unit] = e2[r] * (1.0f - h2[r] * h2[r]);
+        __syncthreads();
+        const f32x4 e1 = product(&D2[0][0], GRD_HP, t2, std::integral_constant<int, K2>{});
+#pragma unroll
+        for (int r = 0; r < 4; ++r) D1[sb + 4 * g + r][unit] = e1[r] * (1.0f - h1[r] * h1[r]);
+        // weight gradients: row block jb of dW2 and dW1, two and four column
+        // blocks; block (w % 2, w / 2) of dW3
+#pragma unroll
+        for (int kb = 0; kb < GRD_S / 4; ++kb) {
+            const int s = 4 * kb + g;
+            const float a2 = D2[s][unit], a3 = DY[s][16 * (w & 1) + r16];
+            g3 = __builtin_amdgcn_mfma_f32_16x16x4f32(a3, H2[s][unit], g3, 0, 0, 0);
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                g2[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a2, H1[s][16 * (2 * (w & 1) + c) + r16], g2[c], 0, 0, 0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int kb = 0; kb < GRD_S / 4; ++kb) {
+            const int s = 4 * kb + g;
+            const float a1 = D1[s][unit];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                g1[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, Xs[s][16 * (4 * (w & 1) + c) + r16], g1[c], 0, 0, 0);
+        }
+        if (tid < 2 * MLP_H + MLP_OUT)
+            for (int s = 0; s < GRD_S; ++s)
+                gb += tid < MLP_H ? D1[s][tid] : tid < 2 * MLP_H ? D2[s][tid - MLP_H] : DY[s][tid - 2 * MLP_H];
+    }
+    float *part = partial + int64_t(blockIdx.x) * (MLP_NPARAM + 1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 16 * jb + 4 * g + r;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int k = 16 * (4 * (w & 1) + c) + r16;
+            if (k < MLP_IN) part[OW1 + row * MLP_IN + k] = g1[c][r];
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) part[OW2 + row * MLP_H + 16 * (2 * (w & 1) + c) + r16] = g2[c][r];
+        const int o = 16 * (w & 1) + 4 * g + r;
+        if (o < MLP_OUT) part[OW3 + o * MLP_H + unit] = g3[r];
+    }
+    if (tid < 2 * MLP_H + MLP_OUT)
+        part[tid < MLP_H ? OB1 + tid : tid < 2 * MLP_H ? OB2 + tid - MLP_H : OB3 + tid - 2 * MLP_H] = gb;
+    // the workgroup's loss: lanes in a fixed tree, then the four wavefronts
+    // that hold outputs in order
+    for (int o = 32; o; o >>= 1) loss += __shfl_down(loss, o);
+    __syncthreads();
+    if (lane == 0) H1[0][w] = loss;
+    __syncthreads();
+    if (tid == 0) part[MLP_NPARAM] = (((H1[0][0] + H1[0][1]) + H1[0][2]) + H1[0][3]) * inv_n;
 }
 
-// grad[p] = sum over blocks of partial[b][p], blocks in order
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float *__restrict__ partial,
-                                                         int nblk, float *__restrict__ grad) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > MLP_NPARAM) return;
+// grad[p] = sum over blocks of partial[b][p]: 64 parameters per workgroup,
+// each of its 16 wavefronts sums a run of blocks in order and the runs are
+// added in order (deterministic)
+constexpr int RDC_WAVES = 16;
+__global__ __launch_bounds__(64 * RDC_WAVES) void mlp_reduce_kernel(const float *__restrict__ partial,
+                                                                    int nblk, float *__restrict__ grad) {
+    __shared__ float sh[RDC_WAVES][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, p = blockIdx.x * 64 + lane;
+    const int run = (nblk + RDC_WAVES - 1) / RDC_WAVES, b1 = min(nblk, (w + 1) * run);
     float s = 0.0f;
-    for (int b = 0; b < nblk; ++b) s += partial[int64_t(b) * (MLP_NPARAM + 1) + p];
+    if (p <= MLP_NPARAM)
+#pragma unroll 8
+        for (int b = w * run; b < b1; ++b) s += partial[int64_t(b) * (MLP_NPARAM + 1) + p];
+    sh[w][lane] = s;
+    __syncthreads();
+    if (w || p > MLP_NPARAM) return;
+    s = sh[0][lane];
+    for (int q = 1; q < RDC_WAVES; ++q) s += sh[q][lane];
     grad[p] = s;
 }
 
@@ -415,10 +514,10 @@ hipError_t launch_mlp_forward(const float *P, const uint16_t *Pb, bool bf16, con
 hipError_t launch_mlp_grad(const float *P, const float *X, const float *Tg, const int32_t *idx, int64_t n,
                            const float *stats, float *partial, int nblk, float *grad, hipStream_t s) {
     if (n <= 0) return hipErrorInvalidValue;
-    const int64_t chunks = (n + 63) / 64;
-    const int g = int(chunks < nblk ? chunks : nblk);
-    mlp_grad_kernel<<<g, 64, 0, s>>>(P, X, Tg, idx, n, stats, partial);
-    mlp_reduce_kernel<<<(MLP_NPARAM + 256) / 256, 256, 0, s>>>(partial, g, grad);
+    const int64_t tiles = (n + GRD_S - 1) / GRD_S;
+    const int g = int(tiles < nblk ? tiles : nblk);
+    mlp_grad_kernel<<<g, GRD_THREADS, 0, s>>>(P, X, Tg, idx, n, stats, partial);
+    mlp_reduce_kernel<<<(MLP_NPARAM + 1 + 63) / 64, 64 * RDC_WAVES, 0, s>>>(partial, g, grad);
     return hipGetLastError();
 }
 
