@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -46,7 +47,13 @@ struct DevType {
     int nu = 0, nf = 0;
     int64_t nelem = 0, ld = 0;
     frd::Op<T> Aint, Agint, Agrad, Adiv;          // Agint: M0 for the gradients
-    frd::Op<T> Fgrad, Fgint;                      // fused gradient stage (step lists, one row block per group)
+    // operators of the kernels on element tiles (gathered): gradient stage [G_k | L_k] and M0, its volume part of the
+    // divergence [G'_0 G'_1 G'_2], and the divergence stage's operator (Euler
+    // [G'_k | L], Navier-Stokes L)
+    frd::Op<T> Fgrad, Fgint, Tvol, Tdiv;
+    // divergence stage on tiles (it fits a CU, and no product variant was
+    // forced); tile_interp: it also interpolates the next stage's input
+    bool tile = false, tile_interp = true;
     // fused gradient stage: bit f of qmask[e] is set when an interface or
     // boundary kernel reads the gradient on face f of element e (the other
     // flux points are not written); fbit[s] = 1 << face of the flux point in
@@ -304,7 +311,108 @@ frd::Op<T> fragment(const std::vector<double> &A_in, int M, int K, std::vector<T
     return op;
 }
 
-// Device copy of a fragment array (and, stages 5 and 6, its step lists); the
+// Gathered layout of an operator for the kernels on element tiles (frd::Op
+// stage 7).  A step of a row block multiplies any four columns, so a block
+// costs a quarter of the columns that any of its rows touches; with steps of
+// four consecutive columns a block of a tensor-product operator also pays for
+// the zeros between its lines (p = 4, matrix instructions per column block:
+// prism gradient 191 -> 100, hexahedron gradient 285 -> 130).  Rows are
+// grouped greedily by the columns they touch, in groups of the size that
+// gives the fewest steps: blocks of 15 leave a row slot empty but fit the
+// layers and lines of order 4.
+template <typename T>
+frd::Op<T> fragment_gathered(const std::vector<double> &A, int M, int K, std::vector<T> &f,
+                             std::vector<int32_t> &idx) {
+    constexpr int WORDS = 8;                           // K <= 512 columns
+    using Mask = std::array<uint64_t, WORDS>;
+    std::vector<Mask> mask(M);
+    for (int r = 0; r < M; ++r) {
+        mask[r].fill(0);
+        for (int c = 0; c < K; ++c)
+            if (A[size_t(r) * K + c] != 0.0) mask[r][c / 64] |= uint64_t(1) << (c % 64);
+    }
+    struct Block {
+        std::vector<int> rows;
+        Mask cols;
+    };
+    auto count = [](const Mask &x) {
+        int n = 0;
+        for (uint64_t w : x) n += __builtin_popcountll(w);
+        return n;
+    };
+    auto group = [&](int size) {
+        std::vector<Block> blocks;
+        std::vector<char> used(M, 0);
+        for (int done = 0; done < M;) {
+            Block b;
+            b.cols.fill(0);
+            for (; int(b.rows.size()) < size && done < M; ++done) {
+                int best = -1, best_add = 1 << 30;
+                for (int r = 0; r < M; ++r) {
+                    if (used[r]) continue;
+                    int add = 0;
+                    for (int w = 0; w < WORDS; ++w) add += __builtin_popcountll(mask[r][w] & ~b.cols[w]);
+                    if (add < best_add) {
+                        best_add = add;
+                        best = r;
+                    }
+                }
+                used[best] = 1;
+                b.rows.push_back(best);
+                for (int w = 0; w < WORDS; ++w) b.cols[w] |= mask[best][w];
+            }
+            blocks.push_back(std::move(b));
+        }
+        return blocks;
+    };
+    std::vector<Block> blocks;
+    int best = 1 << 30;
+    for (int size = 16; size >= 8; --size) {
+        std::vector<Block> b = group(size);
+        int steps = 0;
+        for (const Block &x : b) steps += std::max(1, (count(x.cols) + 3) / 4);
+        if (steps < best) {
+            best = steps;
+            blocks = std::move(b);
+        }
+    }
+    frd::Op<T> op;
+    op.stage = 7;
+    op.M = M;
+    op.Kb = (K + 3) / 4;
+    op.mbw = 1;
+    op.nmg = int(blocks.size());
+    constexpr int SLACK = 12;                          // steps a walk may read past a block
+    f.clear();
+    std::vector<int32_t> koff = {0}, rowmap;
+    std::vector<uint16_t> cols;
+    for (const Block &b : blocks) {
+        std::vector<int> ks;
+        for (int c = 0; c < K; ++c)
+            if (b.cols[c / 64] >> (c % 64) & 1) ks.push_back(c);
+        const size_t nreal = ks.size();
+        if (ks.empty()) ks.push_back(0);
+        while (ks.size() % 4) ks.push_back(ks.back());  // with zero entries
+        for (size_t st = 0; st < ks.size() / 4; ++st) {
+            for (int j = 0; j < 4; ++j) cols.push_back(uint16_t(ks[4 * st + j]));
+            for (int l = 0; l < 64; ++l) {
+                const size_t r = l % 16, k = 4 * st + l / 16;
+                f.push_back(r < b.rows.size() && k < nreal ? T(A[size_t(b.rows[r]) * K + ks[k]]) : T(0));
+            }
+        }
+        koff.push_back(int32_t(cols.size() / 4));
+        for (size_t r = 0; r < 16; ++r) rowmap.push_back(r < b.rows.size() ? b.rows[r] : -1);
+    }
+    cols.resize(cols.size() + 4 * SLACK, 0);
+    f.resize(f.size() + 64 * SLACK, T(0));
+    idx.assign(cols.size() / 2, 0);
+    std::memcpy(idx.data(), cols.data(), cols.size() * 2);
+    idx.insert(idx.end(), koff.begin(), koff.end());
+    idx.insert(idx.end(), rowmap.begin(), rowmap.end());
+    return op;
+}
+
+// Device copy of a fragment array (and, stages 5 to 7, its step lists); the
 // allocations are appended to `allocs`.
 template <typename T>
 hipError_t upload_op(frd::Op<T> &op, const std::vector<T> &f, const std::vector<int32_t> &idx,
@@ -323,6 +431,14 @@ hipError_t upload_op(frd::Op<T> &op, const std::vector<T> &f, const std::vector<
         op.koff = static_cast<int32_t *>(p);
         op.klist = op.koff + op.nmg + 1;
         op.rowmap = op.klist + idx[op.nmg];
+    } else if (op.stage == 7) {
+        if ((e = hipMalloc(&p, idx.size() * sizeof(int32_t))) != hipSuccess) return e;
+        allocs.push_back(p);
+        if ((e = hipMemcpy(p, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
+            return e;
+        op.klist = static_cast<int32_t *>(p);          // 64-bit aligned
+        op.rowmap = op.klist + idx.size() - 16 * size_t(op.nmg);
+        op.koff = op.rowmap - (op.nmg + 1);
     }
     return hipSuccess;
 }
@@ -421,6 +537,14 @@ void folded_ops(const frh::RefOps &R, std::vector<double> &grad, std::vector<dou
     }
 }
 
+// Columns [c0, c1) of a row-major M x K matrix.
+std::vector<double> columns(const std::vector<double> &A, int M, int K, int c0, int c1) {
+    std::vector<double> out;
+    for (int r = 0; r < M; ++r)
+        out.insert(out.end(), A.begin() + size_t(r) * K + c0, A.begin() + size_t(r) * K + c1);
+    return out;
+}
+
 template <typename T>
 fr_status dev_alloc(fr_mesh m, Dev<T> &d, T *&p, size_t n) {
     void *q = nullptr;
@@ -480,14 +604,28 @@ fr_status setup_device(fr_mesh m, hipStream_t s) {
         FR_TRY(dev_upload(m, d, p, f, s));
         D.Adiv.frag = p;
         D.Agint = D.Aint;
-        if (ns && (m->precision == FR_FP32 || m->precision == FR_FP64)) {
-            // the fused gradient stage walks the step lists of one row block
+        if (m->precision == FR_FP32 || m->precision == FR_FP64) {
+            // operators of the kernels on tiles
             std::vector<int32_t> idx;
-            D.Fgrad = fragment<T>(grad, 3 * nu, nu + nf, f, 1, 6, &idx);
-            FR_HIP(m, upload_op(D.Fgrad, f, idx, d.allocs));
-            D.Fgint = fragment<T>(R.M0, nf, nu, f, 1, 6, &idx);
+            D.Fgint = fragment_gathered<T>(R.M0, nf, nu, f, idx);
             FR_HIP(m, upload_op(D.Fgint, f, idx, d.allocs));
-            gint_rows[t].assign(idx.end() - 16 * D.Fgint.nmg, idx.end());
+            if (ns) gint_rows[t].assign(idx.end() - 16 * D.Fgint.nmg, idx.end());
+            const int Kd = 3 * nu + nf, k0 = ns ? 3 * nu : 0;
+            const std::vector<double> part = columns(div, nu, Kd, k0, Kd);
+            D.Tdiv = fragment_gathered<T>(part, nu, Kd - k0, f, idx);
+            FR_HIP(m, upload_op(D.Tdiv, f, idx, d.allocs));
+            frd::DivTileArgs<T> ta;
+            ta.A = D.Tdiv;
+            ta.nu = nu;
+            ta.nf = nf;
+            D.tile = frd::divtile_supported<T>(t, ta, !ns);
+        }
+        if (ns && (m->precision == FR_FP32 || m->precision == FR_FP64)) {
+            std::vector<int32_t> idx;
+            D.Fgrad = fragment_gathered<T>(grad, 3 * nu, nu + nf, f, idx);
+            FR_HIP(m, upload_op(D.Fgrad, f, idx, d.allocs));
+            D.Tvol = fragment_gathered<T>(columns(div, nu, 3 * nu + nf, 0, 3 * nu), nu, 3 * nu, f, idx);
+            FR_HIP(m, upload_op(D.Tvol, f, idx, d.allocs));
             // before autotuning: the fused stage where its gradient product
             // has work for at least half of the workgroup's wavefronts
             // (measured on the mixed Taylor-Green mesh: it loses for tets at
@@ -728,9 +866,31 @@ frd::GradFluxArgs<T> gradflux_args(fr_mesh m, const DevType<T> &D, const T *U) {
     ga.pref = T(m->pref);
     ga.G = D.Fgrad;
     ga.M = D.Fgint;
+    ga.V = D.Tvol;
     ga.qmask = D.qmask;
     ga.fbit = D.fbit;
     return ga;
+}
+
+// Arguments of the divergence stage on tiles (without the last step's).
+template <typename T>
+frd::DivTileArgs<T> divtile_args(fr_mesh m, const DevType<T> &D, const T *U) {
+    frd::DivTileArgs<T> ta;
+    ta.U = U;
+    ta.D = D.Ft;              // the volume part takes the transformed flux's place
+    ta.Fn = D.Fn;
+    ta.geom = D.geom;
+    ta.xi = D.xi;
+    ta.padj = D.padj;
+    ta.ld = D.ld;
+    ta.nelem = D.nelem;
+    ta.nu = D.nu;
+    ta.nf = D.nf;
+    ta.gamma = T(m->gamma);
+    ta.pref = T(m->pref);
+    ta.A = D.Tdiv;
+    ta.M = D.Fgint;
+    return ta;
 }
 
 // Solution-point kernel arguments of one element type on state U.
@@ -744,15 +904,18 @@ frd::UptsArgs<T> upts_args(fr_mesh m, const DevType<T> &D, const T *U) {
     return ua;
 }
 
+// uf: for a run of stages inside one call, per type whether Uf already holds
+// the interpolation of U[t] (in) and that of the state this stage writes
+// (out); next: whether another stage follows on that state.
 template <typename T>
 fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T> so[frh::NTYPE],
-                       hipStream_t s) {
+                       hipStream_t s, bool *uf = nullptr, bool next = false) {
     Dev<T> &d = dev_of<T>(m);
     const bool ns = m->system == FR_NAVIER_STOKES;
     const T gamma = T(m->gamma), mu = T(m->mu), pr = T(m->prandtl);
     for (int t = 0; t < frh::NTYPE; ++t) {
         DevType<T> &D = d.t[t];
-        if (!D.nelem) continue;
+        if (!D.nelem || (uf && uf[t])) continue;
         const int64_t w5 = 5 * D.ld;
         FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
                   opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U[t], w5, D.nu, nullptr, 0, 0, D.Uf, w5, w5, s));
@@ -796,10 +959,15 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     ba.pref = T(m->pref);
     // Navier-Stokes tets and prisms: corrected gradient, point-wise work and
     // gradient interpolation in one kernel (FR_SEPARATE_GRADIENT: three)
-    bool fused[frh::NTYPE] = {false, false, false};
-    for (int t = 0; t < frh::NTYPE; ++t)
+    bool fused[frh::NTYPE] = {false, false, false}, tile[frh::NTYPE];
+    for (int t = 0; t < frh::NTYPE; ++t) {
         fused[t] = ns && d.t[t].nelem && d.t[t].Fgrad.frag && d.t[t].grad_form > 0 &&
                    !(m->flags & FR_SEPARATE_GRADIENT);
+        // the divergence stage on tiles: for Navier-Stokes it takes the
+        // volume part from the fused gradient stage
+        tile[t] = d.t[t].nelem && d.t[t].tile && !(m->flags & FR_SEPARATE_UPDATE) &&
+                  (!ns || (fused[t] && d.t[t].grad_form == 1));
+    }
     if (ns) {
         FR_LAUNCH(m, 10, s, frd::launch_common_solution<T>(pa, s));
         if (d.nb) FR_LAUNCH(m, 22, s, frd::launch_boundary_solution<T>(ba, s));
@@ -807,7 +975,8 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
             DevType<T> &D = d.t[t];
             if (!D.nelem) continue;
             if (fused[t]) {
-                const frd::GradFluxArgs<T> ga = gradflux_args<T>(m, D, U[t]);
+                frd::GradFluxArgs<T> ga = gradflux_args<T>(m, D, U[t]);
+                if (tile[t]) ga.D = D.Ft;
                 FR_LAUNCH(m, prof_gradflux(t), s, frd::launch_gradflux<T>(t, ga, s, D.grad_form == 2));
                 continue;
             }
@@ -819,7 +988,7 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     for (int t = 0; t < frh::NTYPE; ++t) {
         DevType<T> &D = d.t[t];
         if (!D.nelem) continue;
-        if (fused[t]) continue;
+        if (fused[t] || tile[t]) continue;
         const frd::UptsArgs<T> ua = upts_args<T>(m, D, U[t]);
         FR_LAUNCH(m, prof_upts(t), s, frd::launch_upts<T>(t, ns, ua, s));
         if (ns) {
@@ -859,6 +1028,14 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
             na.cys = d.t[0].nelem + d.t[1].nelem;
             na.clift = cl->lift[t];
             na.goff = t ? d.t[0].nelem : 0;
+        }
+        if (uf) uf[t] = tile[t] && D.tile_interp && next;
+        if (tile[t]) {
+            frd::DivTileArgs<T> ta = divtile_args<T>(m, D, U[t]);
+            ta.ep = na;
+            if (uf && uf[t]) ta.Uf = D.Uf;
+            FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s, frd::launch_divtile<T>(t, !ns, ta, s));
+            continue;
         }
         // -R~/J and the register update ride in the divergence product's
         // store (R~ never reaches memory) unless the closure or
@@ -956,7 +1133,9 @@ fr_status rk_impl(fr_mesh m, int scheme, double dt, int nsteps, hipStream_t s,
     static const double rk4_b[4] = {1.0 / 6, 1.0 / 3, 1.0 / 3, 1.0 / 6};
     // RK45[2R+]: a[i][j] = b[j] for j < i-1, so two registers suffice
     const double *rk45_a = RK45_A, *rk45_b = RK45_B;
+    bool uf[frh::NTYPE] = {false, false, false};   // Uf holds the next stage's input at the flux points
     for (int step = 0; step < nsteps; ++step) {
+        const bool last = step + 1 == nsteps;
         if (scheme == FR_FWD_EULER) {
             const T *U[frh::NTYPE] = {d.t[0].reg[0], d.t[1].reg[0], d.t[2].reg[0]};
             StageOut<T> so[frh::NTYPE];
@@ -965,7 +1144,7 @@ fr_status rk_impl(fr_mesh m, int scheme, double dt, int nsteps, hipStream_t s,
                 so[t].a = T(dt);
                 so[t].per_elem_dt = per_elem_dt;
             }
-            fr_status st = rhs_pipeline<T>(m, U, so, s);
+            fr_status st = rhs_pipeline<T>(m, U, so, s, uf, !last);
             if (st) return st;
         } else if (scheme == FR_RK4) {
             for (int t = 0; t < frh::NTYPE; ++t)
@@ -984,7 +1163,7 @@ fr_status rk_impl(fr_mesh m, int scheme, double dt, int nsteps, hipStream_t s,
                     so[t].b = T(rk4_a[st_i] * dt);
                     so[t].per_elem_dt = per_elem_dt;
                 }
-                fr_status st = rhs_pipeline<T>(m, U, so, s);
+                fr_status st = rhs_pipeline<T>(m, U, so, s, uf, st_i < 3 || !last);
                 if (st) return st;
             }
             for (int t = 0; t < frh::NTYPE; ++t) std::swap(d.t[t].reg[0], d.t[t].reg[2]);
@@ -1000,7 +1179,7 @@ fr_status rk_impl(fr_mesh m, int scheme, double dt, int nsteps, hipStream_t s,
                     so[t].b = st_i < 4 ? T((rk45_a[st_i] - rk45_b[st_i]) * dt) : T(0);
                     so[t].per_elem_dt = per_elem_dt;
                 }
-                fr_status st = rhs_pipeline<T>(m, U, so, s);
+                fr_status st = rhs_pipeline<T>(m, U, so, s, uf, st_i < 4 || !last);
                 if (st) return st;
             }
         } else {
@@ -1040,6 +1219,7 @@ fr_status rk_adaptive_impl(fr_mesh m, double t_end, double state[3], double atol
         for (int ty = 0; ty < frh::NTYPE; ++ty)
             if (d.t[ty].nelem)
                 FR_HIP(m, frd::launch_copy<T>(d.t[ty].reg[2], d.t[ty].reg[0], int64_t(d.t[ty].nu) * 5 * d.t[ty].ld, s));
+        bool uf[frh::NTYPE] = {false, false, false};
         for (int st_i = 0; st_i < 5; ++st_i) {
             const T *U[frh::NTYPE];
             StageOut<T> so[frh::NTYPE];
@@ -1053,7 +1233,7 @@ fr_status rk_adaptive_impl(fr_mesh m, double t_end, double state[3], double atol
                 so[ty].c = T((RK45_B[st_i] - RK45_BHAT[st_i]) * h);
                 so[ty].err_set = st_i == 0;
             }
-            fr_status st = rhs_pipeline<T>(m, U, so, s);
+            fr_status st = rhs_pipeline<T>(m, U, so, s, uf, st_i < 4);
             if (st) return st;
         }
         // fused error norm: sum (e / (atol + rtol max(|u_old|, |u_new|)))^2 in FP64
@@ -1274,40 +1454,86 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
                       std::to_string(best_cap) + " stage " + std::to_string(best_stage) + " " +
                       std::to_string(best / 3 * 1e3) + " us; ";
         }
-        // the gradient stage (Navier-Stokes): the fused kernel
-        // against the three separate kernels with the variants just chosen
-        if (ns && D.Fgrad.frag && !(m->flags & FR_SEPARATE_GRADIENT)) {
-            const T *U = D.reg[0];
-            auto run = [&](int form) -> hipError_t {
-                if (form > 0) return frd::launch_gradflux<T>(t, gradflux_args<T>(m, D, U), s, form == 2);
-                hipError_t e = opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U, w5, nu, D.Cf, w5, nf, D.Qt,
-                                        w5, w5, s);
-                if (e == hipSuccess) e = frd::launch_upts<T>(t, true, upts_args<T>(m, D, U), s);
-                if (e == hipSuccess)
-                    e = opmul<T>(m, 4 * t + frd::OP_GRADINTERP, D.Agint, D.Sgint, D.Q, w15, nu, nullptr, 0, 0,
-                                 D.Qf, w15, w15, s);
-                return e;
-            };
-            const int nform = sizeof(T) == 4 && t < 2 ? 3 : 2;   // streaming: FP32 tets and prisms
-            float ms[3] = {0, 0, 0};
-            for (int form = 0; form < nform; ++form) {
-                FR_HIP(m, run(form));
-                FR_HIP(m, hipEventRecord(e0, s));
-                for (int r = 0; r < 3; ++r) FR_HIP(m, run(form));
-                FR_HIP(m, hipEventRecord(e1, s));
-                FR_HIP(m, hipEventSynchronize(e1));
-                FR_HIP(m, hipEventElapsedTime(&ms[form], e0, e1));
+        // the whole stage of this type inside a time step, with the variants
+        // just chosen: separate kernels against the kernels on tiles (the
+        // fused gradient stage, Navier-Stokes, with the divergence stage;
+        // form 2: the streaming gradient stage, FP32 tets and prisms)
+        if (!D.Fgint.frag) continue;
+        const bool sep_update = (m->flags & FR_SEPARATE_UPDATE) != 0;
+        const bool fused_ok = ns && D.Fgrad.frag && !(m->flags & FR_SEPARATE_GRADIENT);
+        const bool tile_ok = D.tile && !sep_update && (!ns || fused_ok);
+        struct Form {
+            int grad;
+            bool tile;
+            const char *name;
+        };
+        std::vector<Form> forms = {{0, false, "separate"}};
+        if (fused_ok && !tile_ok) forms.push_back({1, false, "fused"});
+        if (tile_ok) forms.push_back({ns ? 1 : 0, true, "tiles"});
+        if (fused_ok && sizeof(T) == 4 && t < 2) forms.push_back({2, false, "streaming"});
+        if (forms.size() == 1) continue;
+        const T *U = D.reg[0];
+        frd::NegArgs<T> na{};
+        na.Rt = D.Rt;
+        na.out = D.R;
+        na.acc = D.Rt;
+        na.b = T(1);
+        na.jinv = D.jinv;
+        na.ld = D.ld;
+        na.nelem = D.nelem;
+        na.nu = nu;
+        auto run = [&](const Form &fm) -> hipError_t {
+            hipError_t e = hipSuccess;
+            const bool interp = !(fm.tile && D.tile_interp);
+            if (interp)
+                e = opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U, w5, nu, nullptr, 0, 0, D.Uf, w5, w5, s);
+            if (ns && fm.grad > 0) {
+                frd::GradFluxArgs<T> ga = gradflux_args<T>(m, D, U);
+                if (fm.tile) ga.D = D.Ft;
+                if (e == hipSuccess) e = frd::launch_gradflux<T>(t, ga, s, fm.grad == 2);
+            } else if (!fm.tile) {
+                if (ns && e == hipSuccess)
+                    e = opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U, w5, nu, D.Cf, w5, nf, D.Qt, w5, w5, s);
+                if (e == hipSuccess) e = frd::launch_upts<T>(t, ns, upts_args<T>(m, D, U), s);
+                if (ns && e == hipSuccess)
+                    e = opmul<T>(m, 4 * t + frd::OP_GRADINTERP, D.Agint, D.Sgint, D.Q, w15, nu, nullptr, 0, 0, D.Qf,
+                                 w15, w15, s);
             }
-            int best = 0;
-            for (int form = 1; form < nform; ++form)
-                if (ms[form] < ms[best]) best = form;
-            D.grad_form = best;
-            static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
-            report += sn[t] + std::string(" gradient stage: separate ") + std::to_string(ms[0] / 3 * 1e3) +
-                      " us, fused " + std::to_string(ms[1] / 3 * 1e3) + " us" +
-                      (nform > 2 ? ", streaming " + std::to_string(ms[2] / 3 * 1e3) + " us" : std::string()) +
-                      ", form " + std::to_string(best) + "; ";
+            if (e != hipSuccess) return e;
+            if (fm.tile) {
+                frd::DivTileArgs<T> ta = divtile_args<T>(m, D, U);
+                ta.ep = na;
+                ta.Uf = D.tile_interp ? D.Uf : nullptr;
+                return frd::launch_divtile<T>(t, !ns, ta, s);
+            }
+            frd::NegArgs<T> nf_ = na;
+            nf_.fuse = !sep_update;
+            e = opmul<T>(m, 4 * t + frd::OP_DIV, D.Adiv, D.Sdiv, D.Ft, w5, 3 * nu, D.Fn, w5, nf, D.Rt, w5, w5, s,
+                         sep_update ? nullptr : &nf_);
+            if (e == hipSuccess && sep_update) e = frd::launch_negdivconf<T>(t, na, s);
+            return e;
+        };
+        size_t best = 0;
+        float best_ms = 1e30f;
+        static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
+        report += sn[t] + std::string(" stage:");
+        for (size_t i = 0; i < forms.size(); ++i) {
+            float ms = 0;
+            FR_HIP(m, run(forms[i]));
+            FR_HIP(m, hipEventRecord(e0, s));
+            for (int r = 0; r < 3; ++r) FR_HIP(m, run(forms[i]));
+            FR_HIP(m, hipEventRecord(e1, s));
+            FR_HIP(m, hipEventSynchronize(e1));
+            FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
+            if (ms < best_ms) {
+                best_ms = ms;
+                best = i;
+            }
+            report += std::string(" ") + forms[i].name + " " + std::to_string(ms / 3 * 1e3) + " us";
         }
+        if (ns) D.grad_form = forms[best].grad;
+        D.tile = forms[best].tile;
+        report += std::string(", ") + forms[best].name + "; ";
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -1722,6 +1948,9 @@ fr_status set_blocking_impl(fr_mesh m, int t, int op, int cap, int stage) {
     FR_HIP(m, upload_op(o, f, idx, d.allocs));
     frd::Op<T> *dst[4] = {&D.Aint, &D.Agrad, &D.Agint, &D.Adiv};
     *dst[op] = o;
+    // a forced product variant runs as a product of its own
+    if (op == frd::OP_DIV) D.tile = false;
+    if (op == frd::OP_INTERP) D.tile_interp = false;
     return FR_OK;
 }
 }  // namespace

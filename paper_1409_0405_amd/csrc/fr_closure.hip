@@ -282,18 +282,31 @@ __global__ __launch_bounds__(GRD_THREADS) void mlp_grad_kernel(const float *__re
 
     // weight fragments: forward W_l[16 jb + lane % 16][4 kb + lane / 16],
     // backward (transposed products) W_l[4 kb + lane / 16][16 jb + lane % 16]
+    // (all loads are issued before the first is waited for)
     float w1[K1], w2[K2], w3[K2], t3[K3], t2[K2];
+    const int unit3 = min(unit, MLP_OUT - 1);        // rows past the outputs: a real row, zeroed below
 #pragma unroll
-    for (int kb = 0; kb < K1; ++kb) w1[kb] = opaque(P[OW1 + unit * MLP_IN + 4 * kb + g]);
+    for (int kb = 0; kb < K1; ++kb) w1[kb] = P[OW1 + unit * MLP_IN + 4 * kb + g];
 #pragma unroll
     for (int kb = 0; kb < K2; ++kb) {
-        w2[kb] = opaque(P[OW2 + unit * MLP_H + 4 * kb + g]);
-        w3[kb] = opaque(unit < MLP_OUT ? P[OW3 + unit * MLP_H + 4 * kb + g] : 0.0f);
-        t2[kb] = opaque(P[OW2 + (4 * kb + g) * MLP_H + unit]);
+        w2[kb] = P[OW2 + unit * MLP_H + 4 * kb + g];
+        w3[kb] = P[OW3 + unit3 * MLP_H + 4 * kb + g];
+        t2[kb] = P[OW2 + (4 * kb + g) * MLP_H + unit];
     }
 #pragma unroll
-    for (int kb = 0; kb < K3; ++kb) t3[kb] = opaque(P[OW3 + (4 * kb + g) * MLP_H + unit]);
-    const float bias1 = P[OB1 + unit], bias2 = P[OB2 + unit], bias3 = unit < MLP_OUT ? P[OB3 + unit] : 0.0f;
+    for (int kb = 0; kb < K3; ++kb) t3[kb] = P[OW3 + (4 * kb + g) * MLP_H + unit];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kb = 0; kb < K1; ++kb) w1[kb] = opaque(w1[kb]);
+#pragma unroll
+    for (int kb = 0; kb < K2; ++kb) {
+        w2[kb] = opaque(w2[kb]);
+        w3[kb] = opaque(unit < MLP_OUT ? w3[kb] : 0.0f);
+        t2[kb] = opaque(t2[kb]);
+    }
+#pragma unroll
+    for (int kb = 0; kb < K3; ++kb) t3[kb] = opaque(t3[kb]);
+    const float bias1 = P[OB1 + unit], bias2 = P[OB2 + unit], bias3 = P[OB3 + unit3];
 
     for (int i = tid; i < MLP_NSTATS; i += GRD_THREADS)
         St[i] = stats ? stats[i] : (i < MLP_IN || (i >= 2 * MLP_IN && i < 2 * MLP_IN + MLP_OUT)) ? 0.0f : 1.0f;

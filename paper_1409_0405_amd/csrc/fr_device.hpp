@@ -34,6 +34,10 @@ struct Op {
     // rows touching the same columns share a group: fragment row r' is
     // operator row rowmap[r'] (-1 for padding).  All variants give identical
     // bits for finite B (skipped products are exact zeros).
+    // 7 = gathered, for the kernels on element tiles (mbw = 1): each step of a
+    // row block names the four columns it multiplies, the block's nonzero
+    // columns in ascending order (klist: four 16-bit columns per step,
+    // 64 bits; koff counts steps; both lists have slack at their end).
     int stage = 0;
     const int32_t *klist = nullptr, *koff = nullptr, *rowmap = nullptr;
 };
@@ -121,8 +125,12 @@ struct GradFluxArgs {
     int64_t ld = 0, nelem = 0;
     int nu = 0, nf = 0;
     T gamma = 0, mu = 0, prandtl = 0, pref = 0;
-    Op<T> G;             // [G_k | L_k], 3 nu x (nu + nf): step lists, one row block per group (stage 6)
-    Op<T> M;             // M0, nf x nu: step lists, one row block per group (stage 6)
+    Op<T> G;             // [G_k | L_k], 3 nu x (nu + nf): gathered (stage 7)
+    Op<T> M;             // M0, nf x nu: gathered (stage 7)
+    // when set, the volume part D = [G'_0 G'_1 G'_2] Ft of the divergence is
+    // written instead of Ft: V is that operator, nu x 3 nu (stage 7)
+    T *D = nullptr;      // [nu][5][ld]
+    Op<T> V;
     // Qf is written at the flux point of row slot s of M for element e only
     // where qmask[e] & fbit[s] (the faces whose gradient an interface or
     // boundary kernel reads); every point when qmask is null
@@ -210,6 +218,31 @@ struct NegArgs {
 };
 template <typename T>
 hipError_t launch_negdivconf(int etype, const NegArgs<T> &a, hipStream_t s);
+
+// Divergence stage of one element type on tiles of elements: the divergence
+// product with -Rt / J and the register update, for the Euler equations with
+// the flux evaluation in front of it, and inside a time step with the
+// interpolation of the next stage's input behind it.  Gives the bits of the
+// separate kernels.
+template <typename T>
+struct DivTileArgs {
+    const T *U = nullptr;    // Euler: [nu][5][ld] state of the stage
+    const T *D = nullptr;    // Navier-Stokes: [nu][5][ld] volume part [G'_0 G'_1 G'_2] Ft
+    const T *Fn = nullptr;   // [nf][5][ld] common normal flux
+    T *Uf = nullptr;         // [nf][5][ld] M0 (the state written), or null
+    const T *geom = nullptr, *xi = nullptr, *padj = nullptr;   // as in GradFluxArgs (Euler)
+    int64_t ld = 0, nelem = 0;
+    int nu = 0, nf = 0;
+    T gamma = 0, pref = 0;
+    Op<T> A;                 // Euler [G'_k | L], nu x (3 nu + nf); Navier-Stokes L, nu x nf (stage 7)
+    Op<T> M;                 // M0, nf x nu (stage 7)
+    NegArgs<T> ep;           // the last pipeline step (Rt unused)
+};
+// Whether a tile fits the LDS of a CU.
+template <typename T>
+bool divtile_supported(int etype, const DivTileArgs<T> &a, bool euler);
+template <typename T>
+hipError_t launch_divtile(int etype, bool euler, const DivTileArgs<T> &a, hipStream_t s);
 
 // FP64 reductions: per-block partial sums of nq quantities over one type,
 // written to partial[block][nq]; a second pass sums the blocks in order.

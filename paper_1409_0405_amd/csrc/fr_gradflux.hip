@@ -14,10 +14,10 @@
 //   4. Qf = M0 Q on the matrix cores -> memory.
 // Only U and Cf are read and only Ft and Qf are written, Qf only on the
 // faces whose gradient the interface and boundary kernels read (with the
-// usual LDG weights one side of each interface).  The operator
-// fragments are those of the step-list products (one row block per group),
-// walked in the same K order, and the point-wise arithmetic is the shared
-// upts_point, so every value has the bits of the separate kernels.
+// usual LDG weights one side of each interface).  The operators are walked
+// in the K order of the product kernels (gathered layout, below), and the
+// point-wise arithmetic is the shared one, so every value has the bits of the
+// separate kernels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,179 +26,35 @@
 #include "fr_device.hpp"
 #include "fr_opmul.hpp"
 #include "fr_pointwise.hpp"
+#include "fr_tile.hpp"
 
 namespace frd {
 namespace {
 
-template <int ET>
-constexpr int n_geom_coeffs() { return ET == 0 ? 9 : ET == 1 ? 15 : 21; }
-
-// Entry i of a step list through the scalar data cache: the lists are
-// read-only and the index is uniform in the wavefront, and a constant-space
-// load lets the compiler use a scalar load, which the vector-memory counter
-// (the operator fragments in flight) does not wait for.
-__device__ __forceinline__ int sload(const int32_t *p, int i) {
-    return ((const __attribute__((address_space(4))) int32_t *)p)[i];
-}
-
-// 16 (4) bytes from memory straight into LDS (global_load_lds): lane l of
-// the wavefront writes dst + 16 l (dst + 4 l), dst uniform in the wavefront.
-__device__ __forceinline__ void load_lds16(const void *src, void *dst) {
-    __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
-}
-__device__ __forceinline__ void load_lds4(const void *src, void *dst) {
-    __builtin_amdgcn_global_load_lds(src, dst, 4, 0, 0);
-}
-
-// acc[n] += A_g B[:, 16 n .. 16 n + 15] for row block g of a step-list
-// operator (one row block per group), B in LDS: brow(kb) points at row
-// 4 kb + krow, column lane % 16 of B.  The list is walked in chunks of CH
-// steps (lists are padded to a multiple of four; CH is 4 or 2): while the
-// CH NB matrix instructions of one chunk issue, the operator fragments
-// (memory) and the B values (LDS) of the next chunk are already on their
-// way, so a wave waits for neither.  The K order is the list order, as in
-// the step-list product kernel.
-template <typename T, int NB, int CH = 4, typename V4, typename RowFn>
-__device__ __forceinline__ void step_products(const Op<T> &A, int g, int lane, RowFn brow, V4 (&acc)[NB]) {
-    static_assert(CH == 2 || CH == 4, "chunks of 2 or 4 steps");
-    const int s0 = sload(A.koff, g), ns = sload(A.koff, g + 1) - s0;   // a multiple of 4, >= 4
-    const int32_t *kl = A.klist + s0;
-    const T *Af = A.frag + size_t(s0) * 64 + lane;
-    T a0[CH], b0[CH][NB];
-#pragma unroll
-    for (int d = 0; d < CH; ++d) {
-        a0[d] = Af[size_t(d) * 64];
-        const T *br = brow(sload(kl, d));
-#pragma unroll
-        for (int n = 0; n < NB; ++n) b0[d][n] = br[16 * n];
-    }
-    for (int st = 0; st < ns; st += CH) {
-        // the next chunk (the last chunk loads itself again: in bounds, unused)
-        const int nx = min(st + CH, ns - CH);
-        T a1[CH], b1[CH][NB];
-#pragma unroll
-        for (int d = 0; d < CH; ++d) {
-            a1[d] = Af[size_t(nx + d) * 64];
-            const T *br = brow(sload(kl, nx + d));
-#pragma unroll
-            for (int n = 0; n < NB; ++n) b1[d][n] = br[16 * n];
-        }
-        // keep the scheduler from sinking the loads above next to their use
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int d = 0; d < CH; ++d)
-#pragma unroll
-            for (int n = 0; n < NB; ++n) acc[n] = mfma16(a0[d], b0[d][n], acc[n]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int d = 0; d < CH; ++d) {
-            a0[d] = a1[d];
-#pragma unroll
-            for (int n = 0; n < NB; ++n) b0[d][n] = b1[d][n];
-        }
-    }
-}
-
-// Steps of a list that carry operator entries: the list is padded to a
-// multiple of 4 by repeating its last step with zero fragments (a real
-// step names each K step once, so a repeat can only be padding).  The deep
-// walkers below stop there; an accumulator that starts at +0 is never -0
-// (a sum of opposite zeros rounds to +0), so the products they leave out
-// (exact zeros) would not have changed any bit of it.
-__device__ __forceinline__ int real_steps(const int32_t *kl, int ns) {
-    int n = ns;
-    while (n > 1 && sload(kl, n - 1) == sload(kl, n - 2)) --n;
-    return n;
-}
-
-// acc[n] += A_g B[:, 16 n .. 16 n + 15] like step_products, with the
-// operator fragments (memory) 4 steps ahead of their use and the B values
-// (LDS) one step ahead.
-template <typename T, int NB, typename V4, typename RowFn>
-__device__ __forceinline__ void step_products_deep(const Op<T> &A, int g, int lane, RowFn brow, V4 (&acc)[NB]) {
-    const int s0 = sload(A.koff, g), ns = sload(A.koff, g + 1) - s0;   // a multiple of 4, >= 4
-    const int32_t *kl = A.klist + s0;
-    const T *Af = A.frag + size_t(s0) * 64 + lane;
-    T a[4], b0[NB], b1[NB];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) a[d] = Af[size_t(d) * 64];
-    {
-        const T *br = brow(sload(kl, 0));
-#pragma unroll
-        for (int n = 0; n < NB; ++n) b0[n] = br[16 * n];
-    }
-    const int nr = real_steps(kl, ns);
-    for (int st = 0; st < nr; st += 4) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            if (st + d >= nr) break;
-            const T *br = brow(sload(kl, min(st + d + 1, ns - 1)));
-#pragma unroll
-            for (int n = 0; n < NB; ++n) b1[n] = br[16 * n];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int n = 0; n < NB; ++n) acc[n] = mfma16(a[d], b0[n], acc[n]);
-            __builtin_amdgcn_sched_barrier(0);
-            a[d] = Af[size_t(min(st + d + 4, ns - 1)) * 64];
-#pragma unroll
-            for (int n = 0; n < NB; ++n) b0[n] = b1[n];
-        }
-    }
-}
-
 // acc[j][i] += A_g Q_j[:, column block NH i + h] for row block g of a
-// step-list operator and all three gradient directions j: one operator
+// gathered operator and all three gradient directions j: one operator
 // fragment feeds 3 NBI matrix instructions.  q points at row 0, column
-// 16 h + lane % 16 of Q_0 in LDS, Q_j is jstride values further on; rows
-// past the last solution point are clamped to it (times zero columns of A).
-// The fragments (memory) travel 4 steps ahead of their use, the Q values
-// (LDS) one step; the K order is the list order, as in step_products.
+// 16 h + lane % 16 of Q_0 in LDS, Q_j is jstride values further on.
 template <typename T, int NBI, int NH, int W5, typename V4>
-__device__ __forceinline__ void interp3_products(const Op<T> &A, int g, int lane, int krow, const T *q,
-                                                 int jstride, int nu, V4 (&acc)[3][NBI]) {
-    const int s0 = sload(A.koff, g), ns = sload(A.koff, g + 1) - s0;   // a multiple of 4, >= 4
-    const int32_t *kl = A.klist + s0;
-    const T *Af = A.frag + size_t(s0) * 64 + lane;
-    auto qload = [&](int s, T (&b)[3][NBI]) {
-        const T *br = q + min(4 * sload(kl, s) + krow, nu - 1) * W5;
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-#pragma unroll
-            for (int i = 0; i < NBI; ++i) b[j][i] = br[j * jstride + 16 * NH * i];
-    };
-    T a[4], b0[3][NBI], b1[3][NBI];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) a[d] = Af[size_t(d) * 64];
-    qload(0, b0);
-    const int nr = real_steps(kl, ns);
-    for (int st = 0; st < nr; st += 4) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            if (st + d >= nr) break;
-            qload(min(st + d + 1, ns - 1), b1);
-            __builtin_amdgcn_sched_barrier(0);
+__device__ __forceinline__ void interp3_products(const Op<T> &A, int g, int lane, const T *q, int jstride,
+                                                 V4 (&acc)[3][NBI]) {
+    BVals<T, 3 * NBI> b0, b1;
+    GatherWalk<T>(A, g, lane).run(
+        b0, b1,
+        [&](int row, BVals<T, 3 * NBI> &x) {
+            const T *p = q + row * W5;
 #pragma unroll
             for (int j = 0; j < 3; ++j)
 #pragma unroll
-                for (int i = 0; i < NBI; ++i) acc[j][i] = mfma16(a[d], b0[j][i], acc[j][i]);
-            __builtin_amdgcn_sched_barrier(0);
-            a[d] = Af[size_t(min(st + d + 4, ns - 1)) * 64];
+                for (int i = 0; i < NBI; ++i) x.v[NBI * j + i] = p[j * jstride + 16 * NH * i];
+        },
+        [&](T a, const BVals<T, 3 * NBI> &x) {
 #pragma unroll
             for (int j = 0; j < 3; ++j)
 #pragma unroll
-                for (int i = 0; i < NBI; ++i) b0[j][i] = b1[j][i];
-        }
-    }
+                for (int i = 0; i < NBI; ++i) acc[j][i] = mfma16(a, x.v[NBI * j + i], acc[j][i]);
+        });
 }
-
-// Tile of NE elements with all five fields: row r of a tile in LDS holds W5
-// columns, (field v, element e) at v NE + e and zeros up to W5; column block
-// n of the matrix instructions is columns 16 n .. 16 n + 15.
-template <int NE>
-struct TileShape {
-    static constexpr int W5 = (5 * NE + 15) / 16 * 16;
-    static constexpr int NB = W5 / 16;
-};
 
 // Elements per tile.  The wider the tile, the more matrix instructions each
 // operator fragment feeds (NE / 16 x 5 in FP32), which the measurements
@@ -214,17 +70,18 @@ constexpr int tile_elems() { return sizeof(T) == 4 ? (ET == 2 ? 16 : 32) : 4; }
 // operator per wavefront (>= nmg / NW); their accumulators stay in registers
 // until every wavefront has finished reading B, so that Qt takes B's place in
 // LDS and a tile needs max(B, Qt) of it.
-template <typename T, int ET, int NE, int NW, int MG>
+// VD: the volume part D = [G'_0 G'_1 G'_2] Ft of the divergence is written
+// instead of Ft: Q stays in LDS until it is interpolated, then Ft takes its
+// place (phase 5) and is multiplied there (phase 6).
+template <typename T, int ET, int NE, int NW, int MG, bool VD>
 __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
     using v4 = typename Vec4<T>::type;
     constexpr int W5 = TileShape<NE>::W5, NB = TileShape<NE>::NB;
     constexpr int NG = n_geom_coeffs<ET>();
     constexpr int VPR = NE * int(sizeof(T)) / 16;       // 16-byte vectors per (row, field)
-    constexpr int CH = NB > 5 ? 2 : 4;                   // step-list chunk: B values in flight fit registers
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int Kp = 4 * a.G.Kb;
-    const int nu = a.nu;
-    // one region: B = [U; Cf] ([Kp][W5]) for the gradient product, then Qt
+    const int nu = a.nu, Kp = nu + a.nf;
+    // one region: B = [U; Cf] ([nu + nf][W5]) for the gradient product, then Qt
     // and, in place, Q ([3 nu][W5], row k nu + i)
     T *Bs = reinterpret_cast<T *>(lds_raw);
     T *QT = Bs;
@@ -240,7 +97,7 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
     const int krow = lane >> 4, c16 = lane & 15;
     const int64_t ld = a.ld;
 
-    // 1. B rows: U (k < nu), Cf (nu <= k < nu + nf), zero up to Kp
+    // 1. B rows: U (k < nu), Cf (nu <= k < nu + nf)
     if constexpr (sizeof(T) == 4 && W5 == 5 * NE) {
         // straight from memory into LDS (global_load_lds: no registers, and
         // every load of the tile in flight before the one wait): chunk c
@@ -268,7 +125,6 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
             const int c = base + lane;
             if (c < 3 * nu) load_lds4(a.xi + c, Xs + base);
         }
-        for (int idx = (nu + a.nf) * W5 + tid; idx < Kp * W5; idx += 64 * NW) Bs[idx] = T(0);
         __builtin_amdgcn_s_waitcnt(0);                   // this wavefront's direct loads are in LDS
     } else {
         for (int idx = tid; idx < 3 * nu; idx += 64 * NW) Xs[idx] = a.xi[idx];
@@ -276,13 +132,8 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
         for (int idx = tid; idx < nvec; idx += 64 * NW) {
             const int q = idx % VPR, kv = idx / VPR;
             const int v = kv % 5, k = kv / 5;
-            floatx4 val = {0, 0, 0, 0};
-            if (k < nu)
-                val = *reinterpret_cast<const floatx4 *>(a.U + (int64_t(k) * 5 + v) * ld + e0 +
-                                                         q * (16 / sizeof(T)));
-            else if (k < nu + a.nf)
-                val = *reinterpret_cast<const floatx4 *>(a.Cf + (int64_t(k - nu) * 5 + v) * ld + e0 +
-                                                         q * (16 / sizeof(T)));
+            const T *row = k < nu ? a.U + (int64_t(k) * 5 + v) * ld : a.Cf + (int64_t(k - nu) * 5 + v) * ld;
+            const floatx4 val = *reinterpret_cast<const floatx4 *>(row + e0 + q * (16 / sizeof(T)));
             *reinterpret_cast<floatx4 *>(Bs + k * W5 + v * NE + q * (16 / sizeof(T))) = val;
         }
         if constexpr (W5 > 5 * NE) {
@@ -314,25 +165,23 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
         for (int n = 0; n < NB; ++n) acc[m][n] = v4{0, 0, 0, 0};
         const int g = w + m * NW;
         if (g < a.G.nmg) {
-            auto brow = [&](int kb) { return Bs + (4 * kb + krow) * W5 + c16; };
-            if constexpr (sizeof(T) == 4)
-                step_products_deep<T, NB>(a.G, g, lane, brow, acc[m]);
-            else
-                step_products<T, NB, CH>(a.G, g, lane, brow, acc[m]);
+            gather_products<T, NB>(a.G, g, lane, Bs + c16, W5, acc[m]);
         }
     }
     // the states of this thread's first PI points of the point-wise phase,
     // from B while it is still in LDS (at p = 4 three cover every point of
     // an FP32 tet or prism tile)
     constexpr int PI = sizeof(T) == 4 && ET < 2 ? 3 : 2;
-    T u0[PI][5];
+    T u0[VD ? 1 : PI][5];
+    if constexpr (!VD) {
 #pragma unroll
-    for (int q = 0; q < PI; ++q) {
-        const int it = q * 64 * NW + tid;
-        const int i = it / NE, e = it - i * NE;
-        if (it < nu * NE) {
+        for (int q = 0; q < PI; ++q) {
+            const int it = q * 64 * NW + tid;
+            const int i = it / NE, e = it - i * NE;
+            if (it < nu * NE) {
 #pragma unroll
-            for (int v = 0; v < 5; ++v) u0[q][v] = Bs[i * W5 + v * NE + e];
+                for (int v = 0; v < 5; ++v) u0[q][v] = Bs[i * W5 + v * NE + e];
+            }
         }
     }
     __syncthreads();                                     // every wavefront is done with B
@@ -349,64 +198,86 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
     }
     __syncthreads();
 
+    // the metric of point i and element e of the tile: the adjugate, returns 1 / J
+    auto point_metric = [&](int i, int e, T (&adj)[3][3]) -> T {
+        if (!a.padj) return T(1) / metric<T, ET>(Gs, NE, e, Xs + 3 * i, adj);
+        // (the metric is waited for inside this branch: left in flight, it
+        // would make the straight elements wait at the join, and with it for
+        // the previous point's stores)
+        const int64_t eg = e0 + e;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) adj[k][j] = a.padj[(int64_t(3 * k + j) * nu + i) * ld + eg];
+        const T Jinv = a.pjinv[int64_t(i) * ld + eg];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) adj[k][j] = opaque(adj[k][j]);
+        return opaque(Jinv);
+    };
+    // the 15 values of a point in LDS (Qt, Q or Ft)
+    auto point_read = [&](int i, int e, T (&x)[3][5]) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int v = 0; v < 5; ++v) x[k][v] = QT[(k * nu + i) * W5 + v * NE + e];
+    };
+    auto point_write = [&](int i, int e, const T (&x)[3][5]) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int v = 0; v < 5; ++v) QT[(k * nu + i) * W5 + v * NE + e] = x[k][v];
+    };
+
     // 3. point-wise: one (solution point, element) per thread; Q replaces Qt
-    // in place, Ft goes to memory.  A thread's first PI states came from B
-    // above; further ones (B's place in LDS holds Qt now) come again from
-    // memory, where L2 serves them, and a thread loads those of its next PI
-    // points first, so that no load queues behind the Ft stores of the
-    // points before it (memory operations of a wavefront retire in order).
-    for (int base = 0; base < nu * NE; base += PI * 64 * NW) {
-        T uu[PI][5];
-#pragma unroll
-        for (int q = 0; q < PI; ++q) {
-            const int it = base + q * 64 * NW + tid;
+    // in place
+    if constexpr (VD) {
+        for (int it = tid; it < nu * NE; it += 64 * NW) {
             const int i = it / NE, e = it - i * NE;
-            if (base == 0) {
-#pragma unroll
-                for (int v = 0; v < 5; ++v) uu[q][v] = u0[q][v];
-            } else if (it < nu * NE && e0 + e < a.nelem) {
-#pragma unroll
-                for (int v = 0; v < 5; ++v) uu[q][v] = a.U[(int64_t(i) * 5 + v) * ld + e0 + e];
-            }
+            if (e0 + e >= a.nelem) continue;
+            T adj[3][3], qt[3][5], q3[3][5];
+            const T Jinv = point_metric(i, e, adj);
+            point_read(i, e, qt);
+            upts_gradient(qt, adj, Jinv, q3);
+            point_write(i, e, q3);
         }
+    } else {
+        // and Ft goes to memory.  A thread's first PI states came from B
+        // above; further ones (B's place in LDS holds Qt now) come again from
+        // memory, where L2 serves them, and a thread loads those of its next
+        // PI points first, so that no load queues behind the Ft stores of the
+        // points before it (memory operations of a wavefront retire in order).
+        for (int base = 0; base < nu * NE; base += PI * 64 * NW) {
+            T uu[PI][5];
 #pragma unroll
-        for (int q = 0; q < PI; ++q) {
-            const int it = base + q * 64 * NW + tid;
-            const int i = it / NE, e = it - i * NE;
-            const int64_t eg = e0 + e;
-            if (it >= nu * NE || eg >= a.nelem) continue;
-            T adj[3][3], Jinv;
-            if (a.padj) {
-                // (the metric is waited for inside this branch: left in
-                // flight, it would make the straight elements wait at the
-                // join, and with it for the previous point's Ft stores)
+            for (int q = 0; q < PI; ++q) {
+                const int it = base + q * 64 * NW + tid;
+                const int i = it / NE, e = it - i * NE;
+                if (base == 0) {
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
+                    for (int v = 0; v < 5; ++v) uu[q][v] = u0[q][v];
+                } else if (it < nu * NE && e0 + e < a.nelem) {
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) adj[k][j] = a.padj[(int64_t(3 * k + j) * nu + i) * ld + eg];
-                Jinv = a.pjinv[int64_t(i) * ld + eg];
-#pragma unroll
-                for (int k = 0; k < 3; ++k)
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) adj[k][j] = opaque(adj[k][j]);
-                Jinv = opaque(Jinv);
-            } else {
-                Jinv = T(1) / metric<T, ET>(Gs, NE, e, Xs + 3 * i, adj);
+                    for (int v = 0; v < 5; ++v) uu[q][v] = a.U[(int64_t(i) * 5 + v) * ld + e0 + e];
+                }
             }
-            T qt[3][5], q3[3][5], Ft[3][5];
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
+            for (int q = 0; q < PI; ++q) {
+                const int it = base + q * 64 * NW + tid;
+                const int i = it / NE, e = it - i * NE;
+                const int64_t eg = e0 + e;
+                if (it >= nu * NE || eg >= a.nelem) continue;
+                T adj[3][3], qt[3][5], q3[3][5], Ft[3][5];
+                const T Jinv = point_metric(i, e, adj);
+                point_read(i, e, qt);
+                upts_point<T, true>(uu[q], qt, adj, Jinv, a.gamma, a.mu, a.prandtl, a.pref, q3, Ft);
+                point_write(i, e, q3);
 #pragma unroll
-                for (int v = 0; v < 5; ++v) qt[k][v] = QT[(k * nu + i) * W5 + v * NE + e];
-            upts_point<T, true>(uu[q], qt, adj, Jinv, a.gamma, a.mu, a.prandtl, a.pref, q3, Ft);
+                for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int j = 0; j < 3; ++j)
-#pragma unroll
-                for (int v = 0; v < 5; ++v) QT[(j * nu + i) * W5 + v * NE + e] = q3[j][v];
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int v = 0; v < 5; ++v) a.Ft[((int64_t(k) * nu + i) * 5 + v) * ld + eg] = Ft[k][v];
+                    for (int v = 0; v < 5; ++v) a.Ft[((int64_t(k) * nu + i) * 5 + v) * ld + eg] = Ft[k][v];
+            }
         }
     }
     __syncthreads();
@@ -429,7 +300,8 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
         // items per direction below: with one item per row block, 10 items
         // would leave 6 of the 16 wavefronts idle.)
         constexpr int NH = 2, NBI = 5;
-        for (int it = w; it < a.M.nmg * NH; it += NW) {
+        const int nit = a.M.nmg * NH;
+        for (int it = w; it < nit; it += NW) {
             const int g = it / NH, h = it - NH * g;
             int frow[4];
             unsigned fb[4];
@@ -444,7 +316,7 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
             for (int j = 0; j < 3; ++j)
 #pragma unroll
                 for (int i = 0; i < NBI; ++i) acc3[j][i] = v4{0, 0, 0, 0};
-            interp3_products<T, NBI, NH, W5>(a.M, g, lane, krow, QT + 16 * h + c16, nu * W5, nu, acc3);
+            interp3_products<T, NBI, NH, W5>(a.M, g, lane, QT + 16 * h + c16, nu * W5, acc3);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int f = frow[r];
@@ -461,43 +333,88 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
                 }
             }
         }
-        return;
-    }
-    for (int it = w; it < a.M.nmg * 3; it += NW) {
-        const int g = it / 3, j = it - 3 * g;
-        int frow[4];
-        unsigned fb[4];
+    } else {
+        const int nit = a.M.nmg * 3;
+        for (int it = w; it < nit; it += NW) {
+            const int g = it / 3, j = it - 3 * g;
+            int frow[4];
+            unsigned fb[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int slot = 16 * g + acc_row<T>(krow, r);
-            frow[r] = a.M.rowmap[slot];
-            fb[r] = a.qmask ? unsigned(a.fbit[slot]) : 1u;
+            for (int r = 0; r < 4; ++r) {
+                const int slot = 16 * g + acc_row<T>(krow, r);
+                frow[r] = a.M.rowmap[slot];
+                fb[r] = a.qmask ? unsigned(a.fbit[slot]) : 1u;
+            }
+            const T *Qj = QT + size_t(j) * nu * W5 + c16;
+            v4 acc2[NB];
+#pragma unroll
+            for (int n = 0; n < NB; ++n) acc2[n] = v4{0, 0, 0, 0};
+            gather_products<T, NB>(a.M, g, lane, Qj, W5, acc2);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int f = frow[r];
+                if (f < 0) continue;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    const int flat = 16 * n + c16, v = flat / NE, e = flat - v * NE;
+                    if (v < 5 && e0 + e < a.nelem && (qm[n % NQ] & fb[r]))
+                        a.Qf[(int64_t(f) * 15 + j * 5 + v) * ld + e0 + e] = acc2[n][r];
+                }
+            }
         }
-        const T *Qj = QT + size_t(j) * nu * W5 + c16;
-        v4 acc2[NB];
+    }
+    if constexpr (!VD) return;
+    __syncthreads();                                     // every wavefront is done with Q
+
+    // 5. Ft takes the place of Q (the states again from memory, where L2
+    // serves them, PI points at a time)
+    for (int base = 0; base < nu * NE; base += PI * 64 * NW) {
+        T uu[PI][5];
 #pragma unroll
-        for (int n = 0; n < NB; ++n) acc2[n] = v4{0, 0, 0, 0};
-        // rows of B past K are clamped to a real row (times zero columns of A)
-        auto qrowp = [&](int kb) { return Qj + min(4 * kb + krow, nu - 1) * W5; };
-        if constexpr (sizeof(T) == 4)
-            step_products_deep<T, NB>(a.M, g, lane, qrowp, acc2);
-        else
-            step_products<T, NB, CH>(a.M, g, lane, qrowp, acc2);
+        for (int q = 0; q < PI; ++q) {
+            const int it = base + q * 64 * NW + tid;
+            const int i = it / NE, e = it - i * NE;
+            if (it < nu * NE && e0 + e < a.nelem) {
+#pragma unroll
+                for (int v = 0; v < 5; ++v) uu[q][v] = a.U[(int64_t(i) * 5 + v) * ld + e0 + e];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < PI; ++q) {
+            const int it = base + q * 64 * NW + tid;
+            const int i = it / NE, e = it - i * NE;
+            if (it >= nu * NE || e0 + e >= a.nelem) continue;
+            T adj[3][3], q3[3][5], Ft[3][5];
+            point_metric(i, e, adj);
+            point_read(i, e, q3);
+            upts_flux<T, true>(uu[q], q3, adj, a.gamma, a.mu, a.prandtl, a.pref, Ft);
+            point_write(i, e, Ft);
+        }
+    }
+    __syncthreads();
+
+    // 6. D = [G'_k] Ft: items (row block, part of the column blocks)
+    constexpr int ND = NB % 5 == 0 ? 5 : NB, DH = NB / ND;
+    for (int it = w; it < a.V.nmg * DH; it += NW) {
+        const int g = it / DH, h = it - DH * g;
+        int drow[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) drow[r] = a.V.rowmap[16 * g + acc_row<T>(krow, r)];
+        v4 accd[ND];
+#pragma unroll
+        for (int n = 0; n < ND; ++n) accd[n] = v4{0, 0, 0, 0};
+        gather_products<T, ND, DH>(a.V, g, lane, QT + 16 * h + c16, W5, accd);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int f = frow[r];
-            if (f < 0) continue;
+            if (drow[r] < 0) continue;
 #pragma unroll
-            for (int n = 0; n < NB; ++n) {
-                const int flat = 16 * n + c16, v = flat / NE, e = flat - v * NE;
-                if (v < 5 && e0 + e < a.nelem && (qm[n % NQ] & fb[r]))
-                    a.Qf[(int64_t(f) * 15 + j * 5 + v) * ld + e0 + e] = acc2[n][r];
+            for (int n = 0; n < ND; ++n) {
+                const int flat = 16 * (DH * n + h) + c16, v = flat / NE, e = flat - v * NE;
+                if (v < 5 && e0 + e < a.nelem) a.D[(int64_t(drow[r]) * 5 + v) * ld + e0 + e] = accd[n][r];
             }
         }
     }
 }
-
-constexpr size_t GRADFLUX_LDS_MAX = 160 * 1024;
 
 // Streaming form (FP32): a workgroup takes a contiguous run of tiles and,
 // while it works on one, the next tile's B = [U; Cf] and Jacobian
@@ -512,11 +429,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
     constexpr int NE = 16, W5 = 80, NB = 5;
     constexpr int NG = n_geom_coeffs<ET>();
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int Kp = 4 * a.G.Kb;
     const int nu = a.nu, nf = a.nf;
     float *QT = reinterpret_cast<float *>(lds_raw);      // [3 nu][W5]
-    float *Bs = QT + size_t(3 * nu) * W5;                // [Kp][W5]
-    float *Gs = Bs + size_t(Kp) * W5;                    // [2][NG][NE]
+    float *Bs = QT + size_t(3 * nu) * W5;                // [nu + nf][W5]
+    float *Gs = Bs + size_t(nu + nf) * W5;               // [2][NG][NE]
     float *Xs = Gs + 2 * NG * NE;                        // [nu][3]
 
     const int64_t ntiles = (a.nelem + NE - 1) / NE;
@@ -527,8 +443,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
     const int krow = lane >> 4, c16 = lane & 15;
     const int64_t ld = a.ld;
 
-    // rows of B past K stay zero (the direct loads skip them)
-    for (int idx = tid; idx < (Kp - nu - nf) * W5; idx += 64 * NW) Bs[(nu + nf) * W5 + idx] = 0.0f;
     for (int idx = tid; idx < 3 * nu; idx += 64 * NW) Xs[idx] = a.xi[idx];
 
     // B and the coefficients of tile `tile` into LDS: chunk c (16 bytes) of
@@ -564,7 +478,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
             v4 acc[NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n) acc[n] = v4{0, 0, 0, 0};
-            step_products<float, NB>(a.G, g, lane, [&](int kb) { return Bs + (4 * kb + krow) * W5 + c16; }, acc);
+            gather_products<float, NB>(a.G, g, lane, Bs + c16, W5, acc);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = a.G.rowmap[16 * g + acc_row<float>(krow, r)];
@@ -619,8 +533,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
             v4 acc2[NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n) acc2[n] = v4{0, 0, 0, 0};
-            step_products<float, NB>(a.M, g, lane, [&](int kb) { return Qj + min(4 * kb + krow, nu - 1) * W5; },
-                                     acc2);
+            gather_products<float, NB>(a.M, g, lane, Qj, W5, acc2);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int slot = 16 * g + acc_row<float>(krow, r), f = a.M.rowmap[slot];
@@ -635,32 +548,37 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
 }
 
 
-template <typename T, int ET, int NE, int NW, int MG>
+template <typename T, int ET, int NE, int NW, int MG, bool VD>
 hipError_t launch_gf_mg(const GradFluxArgs<T> &a, size_t lds, hipStream_t s) {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_kernel<T, ET, NE, NW, MG>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(GRADFLUX_LDS_MAX));
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_kernel<T, ET, NE, NW, MG, VD>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int64_t ntiles = (a.nelem + NE - 1) / NE;
-    gradflux_kernel<T, ET, NE, NW, MG><<<xcd_grid(ntiles), 64 * NW, lds, s>>>(a);
+    gradflux_kernel<T, ET, NE, NW, MG, VD><<<xcd_grid(ntiles), 64 * NW, lds, s>>>(a);
     return hipGetLastError();
+}
+
+template <typename T, int ET, int NE, int NW, bool VD>
+hipError_t launch_gf_vd(const GradFluxArgs<T> &a, size_t lds, hipStream_t s) {
+    const int mg = (a.G.nmg + NW - 1) / NW;
+    if (mg <= 1) return launch_gf_mg<T, ET, NE, NW, 1, VD>(a, lds, s);
+    if (mg <= 2) return launch_gf_mg<T, ET, NE, NW, 2, VD>(a, lds, s);
+    if (mg <= 4) return launch_gf_mg<T, ET, NE, NW, 4, VD>(a, lds, s);
+    return hipErrorInvalidValue;
 }
 
 template <typename T, int ET, int NE, int NW>
 hipError_t launch_gf(const GradFluxArgs<T> &a, size_t lds, hipStream_t s) {
-    const int mg = (a.G.nmg + NW - 1) / NW;
-    if (mg <= 1) return launch_gf_mg<T, ET, NE, NW, 1>(a, lds, s);
-    if (mg <= 2) return launch_gf_mg<T, ET, NE, NW, 2>(a, lds, s);
-    if (mg <= 4) return launch_gf_mg<T, ET, NE, NW, 4>(a, lds, s);
-    return hipErrorInvalidValue;
+    return a.D ? launch_gf_vd<T, ET, NE, NW, true>(a, lds, s) : launch_gf_vd<T, ET, NE, NW, false>(a, lds, s);
 }
 
 size_t gradflux_stream_lds_bytes(int etype, const GradFluxArgs<float> &a) {
     const int ng = etype == 0 ? 9 : 15;
-    return (size_t(3 * a.nu) * 80 + size_t(4 * a.G.Kb) * 80 + 2 * size_t(ng) * 16 + size_t(3 * a.nu)) * 4;
+    return (size_t(3 * a.nu) * 80 + size_t(a.nu + a.nf) * 80 + 2 * size_t(ng) * 16 + size_t(3 * a.nu)) * 4;
 }
 
 template <int ET, int NW>
@@ -669,7 +587,7 @@ hipError_t launch_gf_stream(const GradFluxArgs<float> &a, size_t lds, hipStream_
     static int ncu = 0;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_stream_kernel<ET, NW>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(GRADFLUX_LDS_MAX));
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
         if (e != hipSuccess) return e;
         int dev = 0;
         if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
@@ -677,7 +595,7 @@ hipError_t launch_gf_stream(const GradFluxArgs<float> &a, size_t lds, hipStream_
         attr_set = true;
     }
     // as many workgroups as fit at once (LDS-bound), each a contiguous run of tiles
-    const int per_cu = std::max(1, int(GRADFLUX_LDS_MAX / lds));
+    const int per_cu = std::max(1, int(TILE_LDS_MAX / lds));
     const int64_t ntiles = (a.nelem + 15) / 16;
     int64_t nwg = std::min<int64_t>(ntiles, int64_t(ncu) * per_cu);
     const int tiles_per_wg = int((ntiles + nwg - 1) / nwg);
@@ -693,10 +611,10 @@ template <typename T, int ET>
 size_t gradflux_lds_t(const GradFluxArgs<T> &a) {
     constexpr int NE = tile_elems<T, ET>();
     constexpr int W5 = TileShape<NE>::W5;
-    const size_t n = size_t(std::max(4 * a.G.Kb, 3 * a.nu)) * W5 + size_t(n_geom_coeffs<ET>()) * NE +
+    const size_t n = size_t(std::max(a.nu + a.nf, 3 * a.nu)) * W5 + size_t(n_geom_coeffs<ET>()) * NE +
                      size_t(3 * a.nu);
     const size_t bytes = n * sizeof(T);
-    return bytes <= GRADFLUX_LDS_MAX ? bytes : 0;
+    return bytes <= TILE_LDS_MAX ? bytes : 0;
 }
 }  // namespace
 
@@ -713,15 +631,13 @@ hipError_t launch_gradflux(int etype, const GradFluxArgs<T> &a, hipStream_t s, b
         if (stream) {
             if (etype > 1) return hipErrorInvalidValue;   // the streaming form covers tets and prisms
             lds = gradflux_stream_lds_bytes(etype, a);
-            if (lds > GRADFLUX_LDS_MAX) return hipErrorInvalidValue;
+            if (lds > TILE_LDS_MAX) return hipErrorInvalidValue;
         }
     } else {
         if (stream) return hipErrorInvalidValue;
     }
-    // operator layout: step lists (4 steps in flight), one row block per group
-    if (!lds || a.G.stage != 6 || a.M.stage != 6 || a.G.mbw != 1 || a.M.mbw != 1 || !a.G.klist ||
-        !a.G.koff || !a.G.rowmap || !a.M.klist || !a.M.koff || !a.M.rowmap || a.G.M != 3 * a.nu ||
-        a.M.M != a.nf || 4 * a.G.Kb < a.nu + a.nf || 4 * a.M.Kb < a.nu || a.ld % 64 || a.nelem > a.ld ||
+    if (!lds || !gathered(a.G, 3 * a.nu) || !gathered(a.M, a.nf) || (a.D && (stream || !gathered(a.V, a.nu))) ||
+        a.ld % 64 || a.nelem > a.ld ||
         (reinterpret_cast<uintptr_t>(a.U) | reinterpret_cast<uintptr_t>(a.Cf) |
          reinterpret_cast<uintptr_t>(a.geom)) % 16 ||
         reinterpret_cast<uintptr_t>(a.xi) % 4)   // 16- and 4-byte direct loads into LDS

@@ -73,12 +73,13 @@ inline unsigned xcd_grid(int64_t nblocks) { return unsigned((nblocks + 7) / 8 * 
 // The last pipeline step at one (solution point i, field v, element e), with
 // o = (5 i + v) ld + e: k = -r / J (plus the learned closure's lifted
 // correction), times the element's step size, into the error, accumulator
-// and output registers (frd::NegArgs).  negdivconf_kernel and the fused
-// store of the divergence products both call it, so the two give the same
-// bits.
+// and output registers (frd::NegArgs).  negdivconf_kernel, the fused store
+// of the divergence products and the divergence stage on tiles all go through
+// it, so they give the same bits.  Returns the value left in the output
+// register (the accumulator's where there is no output).
 template <typename T>
-__device__ __forceinline__ void neg_update(const NegArgs<T> &a, int i, int v, int64_t e, int64_t o,
-                                           T r) {
+__device__ __forceinline__ T neg_update(const NegArgs<T> &a, int i, int v, int64_t e, int64_t o,
+                                        T r) {
     const T Jinv = a.jinv[int64_t(i) * a.ld + e];
     const T sc = a.dte ? a.dte[e] : T(1);
     T k = -r * Jinv;
@@ -94,58 +95,68 @@ __device__ __forceinline__ void neg_update(const NegArgs<T> &a, int i, int v, in
         accv = a.acc[o] + a.a * k;
         a.acc[o] = accv;
     }
-    if (a.out) a.out[o] = (a.base ? a.base[o] : accv) + a.b * k;
+    if (!a.out) return accv;
+    const T outv = (a.base ? a.base[o] : accv) + a.b * k;
+    a.out[o] = outv;
+    return outv;
+}
+
+// neg_update for the four consecutive elements e0 .. e0 + 3 of solution point
+// i and field v (o0 = (5 i + v) ld + e0), on 16-byte (FP32) / 32-byte (FP64)
+// loads and stores; elements past nelem are skipped.  The register pointers
+// are 4-element aligned (checked at entry).  Returns the values left in the
+// output register (the accumulator where there is no output).
+template <typename T, typename V4>
+__device__ __forceinline__ V4 update4(const NegArgs<T> &ep, int i, int v, int64_t e0, int64_t o0, const V4 &val) {
+    V4 res = V4{0, 0, 0, 0};
+    if (e0 + 3 < ep.nelem && !ep.cy) {
+        // four whole elements: the same arithmetic as neg_update
+        const V4 J = *reinterpret_cast<const V4 *>(ep.jinv + int64_t(i) * ep.ld + e0);
+        const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
+        V4 k;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            k[j] = -T(val[j]) * J[j];
+            k[j] *= S[j];
+        }
+        if (ep.err) {
+            V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) er[j] = er[j] + ep.c * k[j];
+            *reinterpret_cast<V4 *>(ep.err + o0) = er;
+        }
+        if (ep.acc) {
+            res = *reinterpret_cast<const V4 *>(ep.acc + o0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) res[j] = res[j] + ep.a * k[j];
+            *reinterpret_cast<V4 *>(ep.acc + o0) = res;
+        }
+        if (ep.out) {
+            if (ep.base) res = *reinterpret_cast<const V4 *>(ep.base + o0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) res[j] = res[j] + ep.b * k[j];
+            *reinterpret_cast<V4 *>(ep.out + o0) = res;
+        }
+        return res;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (e0 + j < ep.nelem) res[j] = neg_update(ep, i, v, e0 + j, o0 + j, T(val[j]));
+    return res;
 }
 
 // Store of four consecutive columns of one output row.  For a divergence
 // product with ep.fuse set the row is solution point i and the columns are
 // (field v, elements e .. e + 3) of the [point][field][ld] layout (ldc = 5
-// ld, checked at launch): the values go through neg_update's arithmetic
-// instead of being stored, and the padding elements past nelem are skipped.
-// The register pointers are 4-element aligned (checked at entry).
+// ld, checked at launch): the values go through the last pipeline step
+// instead of being stored.
 template <int TAG, typename T, typename V4>
 __device__ __forceinline__ void store_c(T *C, int64_t ldc, int row, int64_t col, const V4 &val,
                                         const NegArgs<T> &ep) {
     if constexpr (TAG % 4 == 3) {
         if (ep.fuse) {
             const int v = int(col / ep.ld);
-            const int64_t e0 = col - int64_t(v) * ep.ld;
-            const int64_t o0 = int64_t(row) * ldc + col;
-            if (e0 + 3 < ep.nelem && !ep.cy) {
-                // four whole elements: the same arithmetic as neg_update on
-                // 16-byte (FP32) / 32-byte (FP64) loads and stores
-                const V4 J = *reinterpret_cast<const V4 *>(ep.jinv + int64_t(row) * ep.ld + e0);
-                const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
-                V4 k;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    k[j] = -T(val[j]) * J[j];
-                    k[j] *= S[j];
-                }
-                if (ep.err) {
-                    V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) er[j] = er[j] + ep.c * k[j];
-                    *reinterpret_cast<V4 *>(ep.err + o0) = er;
-                }
-                V4 accv = V4{0, 0, 0, 0};
-                if (ep.acc) {
-                    accv = *reinterpret_cast<const V4 *>(ep.acc + o0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) accv[j] = accv[j] + ep.a * k[j];
-                    *reinterpret_cast<V4 *>(ep.acc + o0) = accv;
-                }
-                if (ep.out) {
-                    V4 o = ep.base ? *reinterpret_cast<const V4 *>(ep.base + o0) : accv;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) o[j] = o[j] + ep.b * k[j];
-                    *reinterpret_cast<V4 *>(ep.out + o0) = o;
-                }
-                return;
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (e0 + j < ep.nelem) neg_update(ep, row, v, e0 + j, o0 + j, T(val[j]));
+            update4(ep, row, v, col - int64_t(v) * ep.ld, int64_t(row) * ldc + col, val);
             return;
         }
     }

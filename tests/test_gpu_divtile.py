@@ -1,0 +1,111 @@
+"""The divergence stage on element tiles (flux evaluation for the Euler
+equations, divergence product, register update, interpolation of the next
+stage's input) against the separate kernels (FR_SEPARATE_UPDATE): the same
+arithmetic on the same values in the same order, so every result has the same
+bits (raw bits, a zero's sign included).  Orders 1 to 4, every element type,
+element counts below and ragged against the tiles (32 and 16 elements),
+straight and curved elements, walls, FP32 and FP64, several steps of every
+scheme (between which the stage fills the flux-point states), and the learned
+closure."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import fr, mesh as om
+from paper_1409_0405_amd import inputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+NAMES = ("tet", "pri", "hex")
+L3 = (2 * math.pi,) * 3
+P0 = 1.0 / (1.4 * 0.09)
+
+
+def _arrays(kind):
+    if kind == "tiny":           # 8 prisms and 24 tets
+        return inputs.small_mixed_box(nxy=2, n_pri_layers=1, n_tet_layers=1, jitter=0.1, seed=5)
+    if kind == "hybrid":         # 36 hexahedra, 144 prisms, 216 tets
+        return inputs.hybrid_box(6, 4, 6, 3, 3, L3, jitter=0.1, seed=5)
+    if kind == "curvedwall":
+        return inputs.curve(inputs.hybrid_box(6, 4, 6, 3, 3, L3, jitter=0.1, seed=5, y_bc="wall"), 0.03)
+    return inputs.small_mixed_box(nxy=5, n_pri_layers=3, n_tet_layers=3, jitter=0.1, seed=5)   # 150 prisms, 450 tets
+
+
+def _bits(x, y):
+    it = torch.int64 if x.dtype == torch.float64 else torch.int32
+    return torch.equal(x.view(it), y.view(it))
+
+
+def _results(arrays, p, system, prec, separate, closure=False):
+    from paper_1409_0405_amd import frlib
+    O = om.build_mesh(arrays, p)
+    U = fr.initial_state(O, inputs.taylor_green, mach=0.3)
+    for n in U:       # every field nonzero, so that no product vanishes
+        U[n][..., 3] += 0.3 * U[n][..., 0]
+        U[n] = U[n] * inputs.random_perturbation(U[n].shape, 4, 0.01)
+    ts = [NAMES.index(n) for n in O.types]
+    M = frlib.Mesh(arrays, p, system=system, precision=prec, mu=0.02, separate_update=separate, t_wall=P0, p_ref=P0)
+    net, out = None, []
+    if system == "ns":
+        for t in ts:
+            M.set_gradient_form(t, 1)
+    if closure:
+        rng = np.random.default_rng(3)
+        net = frlib.MLP(1)
+        stats = torch.as_tensor(np.concatenate([np.zeros(120), np.full(120, 5.0), np.zeros(20), np.full(20, 0.3)])
+                                .astype(np.float32) + 0.01 * rng.uniform(size=280).astype(np.float32), device="cuda")
+        M.closure_attach(net, stats.data_ptr())
+    u = {t: frlib.to_device_state(M, t, np.transpose(U[NAMES[t]], (1, 2, 0))) for t in ts}
+    r = {t: frlib.state_tensor(M, t) for t in ts}
+    M.rhs([u[t].data_ptr() if t in u else 0 for t in range(3)], [r[t].data_ptr() if t in r else 0 for t in range(3)])
+    out += [r[t] for t in ts]
+    for t in ts:
+        M.set_solution(t, u[t].data_ptr())
+
+    def keep():
+        for t in ts:
+            s = frlib.state_tensor(M, t)
+            M.get_solution(t, s.data_ptr())
+            q = M.query(t)
+            f = torch.zeros((q["nfpts"], 5, q["ld"]), dtype=s.dtype, device="cuda")
+            M.intermediate(t, 0, f.data_ptr())
+            torch.cuda.synchronize()
+            out.extend([s, f[:, :, :q["nelem"]]])
+    for scheme, n in ((frlib.FR_RK45_2RP, 2), (frlib.FR_RK4, 2), (frlib.FR_FWD_EULER, 3)):
+        M.rk_step(scheme, 1e-3, n)
+        keep()
+    state = [0.0, 1e-3, 1.0]
+    counts = M.rk45_adaptive(4e-3, state, 1e-5, 1e-5)
+    keep()
+    M.closure_attach(None)
+    M.close()
+    return out, counts, state
+
+
+CASES = [("mixed", p, s, q) for p in (1, 2, 3, 4) for s in ("euler", "ns") for q in ("fp32", "fp64")]
+CASES += [("hybrid", p, s, "fp32") for p in (1, 2, 3, 4) for s in ("euler", "ns")]
+CASES += [("hybrid", 4, "ns", "fp64"), ("hybrid", 3, "euler", "fp64"), ("tiny", 2, "euler", "fp32"),
+          ("tiny", 4, "ns", "fp32"), ("curvedwall", 3, "euler", "fp32"), ("curvedwall", 3, "ns", "fp32"),
+          ("curvedwall", 2, "euler", "fp64")]
+
+
+@pytest.mark.parametrize("kind,p,system,prec", CASES, ids=[f"{k}-p{p}-{s}-{q}" for k, p, s, q in CASES])
+def test_tiles_give_the_bits_of_the_separate_kernels(kind, p, system, prec):
+    print(f"{kind} p{p} {system} {prec}", flush=True)
+    arrays = _arrays(kind)
+    (a, ca, sa), (b, cb, sb) = (_results(arrays, p, system, prec, sep) for sep in (False, True))
+    assert ca == cb and sa == sb
+    assert all(bool(torch.isfinite(x).all()) for x in b)
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert _bits(x, y), i
+
+
+@pytest.mark.parametrize("prec", ("fp32", "fp64"))
+def test_tiles_with_the_closure(prec):
+    print(f"closure {prec}", flush=True)
+    (a, ca, sa), (b, cb, sb) = (_results(_arrays("mixed"), 1, "ns", prec, sep, closure=True) for sep in (False, True))
+    assert ca == cb and sa == sb
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert _bits(x, y), i
