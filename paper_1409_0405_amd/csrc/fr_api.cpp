@@ -382,10 +382,16 @@ frd::Op<T> fragment_gathered(const std::vector<double> &A, int M, int K, std::ve
     op.Kb = (K + 3) / 4;
     op.mbw = 1;
     op.nmg = int(blocks.size());
-    constexpr int SLACK = 12;                          // steps a walk may read past a block
+    constexpr int SLACK = 8;                           // steps a walk may read past a block
     f.clear();
     std::vector<int32_t> koff = {0}, rowmap;
-    std::vector<uint16_t> cols;
+    auto put = [&](T a, int col) {                     // frd::GatherStep<T>
+        f.push_back(a);
+        T c = T(0);
+        const int32_t c32 = col;
+        std::memcpy(&c, &c32, 4);
+        f.push_back(c);
+    };
     for (const Block &b : blocks) {
         std::vector<int> ks;
         for (int c = 0; c < K; ++c)
@@ -393,21 +399,16 @@ frd::Op<T> fragment_gathered(const std::vector<double> &A, int M, int K, std::ve
         const size_t nreal = ks.size();
         if (ks.empty()) ks.push_back(0);
         while (ks.size() % 4) ks.push_back(ks.back());  // with zero entries
-        for (size_t st = 0; st < ks.size() / 4; ++st) {
-            for (int j = 0; j < 4; ++j) cols.push_back(uint16_t(ks[4 * st + j]));
+        for (size_t st = 0; st < ks.size() / 4; ++st)
             for (int l = 0; l < 64; ++l) {
                 const size_t r = l % 16, k = 4 * st + l / 16;
-                f.push_back(r < b.rows.size() && k < nreal ? T(A[size_t(b.rows[r]) * K + ks[k]]) : T(0));
+                put(r < b.rows.size() && k < nreal ? T(A[size_t(b.rows[r]) * K + ks[k]]) : T(0), ks[k]);
             }
-        }
-        koff.push_back(int32_t(cols.size() / 4));
+        koff.push_back(koff.back() + int32_t(ks.size() / 4));
         for (size_t r = 0; r < 16; ++r) rowmap.push_back(r < b.rows.size() ? b.rows[r] : -1);
     }
-    cols.resize(cols.size() + 4 * SLACK, 0);
-    f.resize(f.size() + 64 * SLACK, T(0));
-    idx.assign(cols.size() / 2, 0);
-    std::memcpy(idx.data(), cols.data(), cols.size() * 2);
-    idx.insert(idx.end(), koff.begin(), koff.end());
+    for (int i = 0; i < 64 * SLACK; ++i) put(T(0), 0);
+    idx = koff;
     idx.insert(idx.end(), rowmap.begin(), rowmap.end());
     return op;
 }
@@ -436,9 +437,8 @@ hipError_t upload_op(frd::Op<T> &op, const std::vector<T> &f, const std::vector<
         allocs.push_back(p);
         if ((e = hipMemcpy(p, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
             return e;
-        op.klist = static_cast<int32_t *>(p);          // 64-bit aligned
-        op.rowmap = op.klist + idx.size() - 16 * size_t(op.nmg);
-        op.koff = op.rowmap - (op.nmg + 1);
+        op.koff = static_cast<int32_t *>(p);
+        op.rowmap = op.koff + op.nmg + 1;
     }
     return hipSuccess;
 }

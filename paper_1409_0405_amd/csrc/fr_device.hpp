@@ -35,9 +35,9 @@ struct Op {
     // operator row rowmap[r'] (-1 for padding).  All variants give identical
     // bits for finite B (skipped products are exact zeros).
     // 7 = gathered, for the kernels on element tiles (mbw = 1): each step of a
-    // row block names the four columns it multiplies, the block's nonzero
-    // columns in ascending order (klist: four 16-bit columns per step,
-    // 64 bits; koff counts steps; both lists have slack at their end).
+    // row block multiplies four columns of its own, the block's nonzero
+    // columns in ascending order; frag holds (value, column) pairs, lane l of
+    // step s at pair 64 s + l; koff counts steps.
     int stage = 0;
     const int32_t *klist = nullptr, *koff = nullptr, *rowmap = nullptr;
 };

@@ -32,35 +32,11 @@
 namespace frd {
 namespace {
 
-// Row stride of a tile in LDS.  A matrix instruction reads B at four
-// consecutive rows and 16 columns: with 80 values per row (tiles of 16) the
-// four rows fall into different banks, with 160 (tiles of 32) rows two apart
-// would share theirs, so those rows are 16 values longer.
-template <int NE>
-constexpr int tile_stride() { return NE == 32 ? 176 : TileShape<NE>::W5; }
-
-// Rows [0, rows) of a [rows][5][ld] array, elements e0 .. e0 + NE - 1, straight
-// into LDS rows of stride WS (no registers; the caller waits).
-template <typename T, int NE, int NW>
-__device__ __forceinline__ void tile_to_lds(const T *src, int64_t ld, int64_t e0, int rows, T *dst, int w, int lane) {
-    constexpr int V = 16 / int(sizeof(T)), VPR = NE / V, W5 = 5 * NE, WS = tile_stride<NE>();
-    if constexpr (WS == W5) {
-        const int nchunk = rows * 5 * VPR;
-        for (int base = w * 64; base < nchunk; base += NW * 64) {
-            const int c = base + lane, q = c % VPR, kv = c / VPR;     // kv = 5 row + field
-            if (c < nchunk) load_lds16(src + int64_t(kv) * ld + e0 + V * q, dst + size_t(base) * V);
-        }
-    } else {
-        // padded rows: one instruction per row, its 5 VPR 16-byte pieces
-        const int q = lane % VPR, v = lane / VPR;
-        for (int k = w; k < rows; k += NW)
-            if (lane < 5 * VPR) load_lds16(src + (int64_t(k) * 5 + v) * ld + e0 + V * q, dst + size_t(k) * WS);
-    }
-}
-
 // NE elements per workgroup of NW wavefronts; MI: work items (row block,
 // column half) of the divergence product per wavefront, whose accumulators
-// stay in registers until every wavefront has read B.
+// stay in registers until every wavefront has read B.  Column block n of half
+// h holds field n of elements 16 h .. 16 h + 15, so a lane's accumulators are
+// one element's.
 template <typename T, int ET, int NE, int NW, int MI, bool EULER>
 __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
     using v4 = typename Vec4<T>::type;
@@ -86,22 +62,31 @@ __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
         const int it = w + m * NW, g = it / NH, h = it - NH * g;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) rrow[m][r] = g < a.A.nmg ? a.A.rowmap[16 * g + acc_row<T>(krow, r)] : -1;
+        block_rows(a.A, g, krow, rrow[m]);
 #pragma unroll
         for (int i = 0; i < NBI; ++i) acc[m][i] = v4{0, 0, 0, 0};
         if constexpr (!EULER) {
+            // (rows past the last are read as row 0: their sums are not used)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (rrow[m][r] >= 0) {
+            for (int r = 0; r < 4; ++r) {
+                const T *d = a.D + int64_t(max(rrow[m][r], 0)) * 5 * ld + e0 + 16 * h + c16;
 #pragma unroll
-                    for (int i = 0; i < NBI; ++i) {
-                        const int col = 16 * (NH * i + h) + c16, v = col / NE, e = col - v * NE;
-                        acc[m][i][r] = a.D[(int64_t(rrow[m][r]) * 5 + v) * ld + e0 + e];
-                    }
-                }
+                for (int i = 0; i < NBI; ++i) acc[m][i][r] = d[i * ld];
+            }
         }
     }
+    // what this thread's first PU items of the update read (J and the
+    // registers), on its way while the tile is loaded and multiplied
+    constexpr int Q = NE / 4, PU = 1;
+    UpdateIn<T, v4> up[PU];
+#pragma unroll
+    for (int m = 0; m < PU; ++m) {
+        const int idx = tid + m * 64 * NW, q = idx % Q, iv = idx / Q;
+        const int64_t eg = e0 + 4 * q;
+        if (idx < nu * 5 * Q && update4_whole(a.ep, eg)) update4_load(a.ep, iv / 5, eg, int64_t(iv) * ld + eg, up[m]);
+    }
+    // (the first item's operator steps travel with the tile)
+    GatherWalk<T> walk(a.A, min(w / NH, a.A.nmg - 1), lane);
     if constexpr (EULER) {
         if (!a.padj)
             for (int base = w * 64; base < NG * VPR; base += NW * 64) {
@@ -143,8 +128,10 @@ __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
         const int it = w + m * NW, g = it / NH, h = it - NH * g;
-        if (g < a.A.nmg)
-            gather_products<T, NBI, NH>(a.A, g, lane, Bs + 16 * h + c16, WS, acc[m]);
+        if (g < a.A.nmg) {
+            if (m > 0) walk = GatherWalk<T>(a.A, g, lane);
+            gather_products<NH>(walk, Bs + 16 * h + c16, WS, acc[m]);
+        }
     }
     __syncthreads();                                     // every wavefront is done with B
 #pragma unroll
@@ -157,16 +144,30 @@ __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
                 for (int i = 0; i < NBI; ++i) Bs[rrow[m][r] * WS + 16 * (NH * i + h) + c16] = acc[m][i][r];
             }
     }
+    // (the interpolation's first operator steps travel during the update)
+    int frow[4];
+    block_rows(a.M, w / NH, krow, frow);
+    walk = GatherWalk<T>(a.M, min(w / NH, a.M.nmg - 1), lane);
     __syncthreads();
 
     // 3. the last pipeline step, four elements of one (point, field) at a time
-    constexpr int Q = NE / 4;
-    for (int idx = tid; idx < nu * 5 * Q; idx += 64 * NW) {
+    auto update = [&](int idx, const UpdateIn<T, v4> &x) {
         const int q = idx % Q, iv = idx / Q, v = iv % 5, i = iv / 5;
         v4 *p = reinterpret_cast<v4 *>(Bs + i * WS + v * NE + 4 * q);
-        const int64_t eg = e0 + 4 * q;
-        const v4 r = update4(a.ep, i, v, eg, int64_t(iv) * ld + eg, *p);
+        const int64_t eg = e0 + 4 * q, o0 = int64_t(iv) * ld + eg;
+        const v4 r = update4_whole(a.ep, eg) ? update4(a.ep, eg, o0, *p, x) : update4_tail(a.ep, i, v, eg, o0, *p);
         if (a.Uf) *p = r;
+    };
+#pragma unroll
+    for (int m = 0; m < PU; ++m) {
+        const int idx = tid + m * 64 * NW;
+        if (idx < nu * 5 * Q) update(idx, up[m]);
+    }
+    for (int idx = tid + PU * 64 * NW; idx < nu * 5 * Q; idx += 64 * NW) {
+        const int64_t eg = e0 + 4 * (idx % Q);
+        UpdateIn<T, v4> x;
+        if (update4_whole(a.ep, eg)) update4_load(a.ep, idx / Q / 5, eg, int64_t(idx / Q) * ld + eg, x);
+        update(idx, x);
     }
     if (!a.Uf) return;
     __syncthreads();
@@ -174,21 +175,22 @@ __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
     // 4. U_f = M0 r: items (row block, column half)
     for (int it = w; it < a.M.nmg * NH; it += NW) {
         const int g = it / NH, h = it - NH * g;
-        int frow[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) frow[r] = a.M.rowmap[16 * g + acc_row<T>(krow, r)];
         v4 af[NBI];
 #pragma unroll
         for (int i = 0; i < NBI; ++i) af[i] = v4{0, 0, 0, 0};
-        gather_products<T, NBI, NH>(a.M, g, lane, Bs + 16 * h + c16, WS, af);
+        if (it != w) {
+            block_rows(a.M, g, krow, frow);
+            walk = GatherWalk<T>(a.M, g, lane);
+        }
+        gather_products<NH>(walk, Bs + 16 * h + c16, WS, af);
+        const int64_t eg = e0 + 16 * h + c16;
+        if (eg >= a.nelem) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (frow[r] < 0) continue;
+            T *u = a.Uf + int64_t(frow[r]) * 5 * ld + eg;
 #pragma unroll
-            for (int i = 0; i < NBI; ++i) {
-                const int col = 16 * (NH * i + h) + c16, v = col / NE, e = col - v * NE;
-                if (e0 + e < a.nelem) a.Uf[(int64_t(frow[r]) * 5 + v) * ld + e0 + e] = af[i][r];
-            }
+            for (int i = 0; i < NBI; ++i) u[i * ld] = af[i][r];
         }
     }
 }

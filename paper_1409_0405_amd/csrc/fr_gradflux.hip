@@ -31,18 +31,17 @@
 namespace frd {
 namespace {
 
-// acc[j][i] += A_g Q_j[:, column block NH i + h] for row block g of a
-// gathered operator and all three gradient directions j: one operator
-// fragment feeds 3 NBI matrix instructions.  q points at row 0, column
-// 16 h + lane % 16 of Q_0 in LDS, Q_j is jstride values further on.
-template <typename T, int NBI, int NH, int W5, typename V4>
-__device__ __forceinline__ void interp3_products(const Op<T> &A, int g, int lane, const T *q, int jstride,
-                                                 V4 (&acc)[3][NBI]) {
-    BVals<T, 3 * NBI> b0, b1;
-    GatherWalk<T>(A, g, lane).run(
-        b0, b1,
+// acc[j][i] += A_g Q_j[:, column block NH i + h] for the row block of a walk
+// and all three gradient directions j: one operator fragment feeds 3 NBI
+// matrix instructions.  q points at row 0, column 16 h + lane % 16 of Q_0 in
+// LDS, Q_j is jstride values further on.
+template <int NBI, int NH, int W5, typename T, int AD, typename V4>
+__device__ __forceinline__ void interp3_products(GatherWalk<T, AD> &w, const T *q, int jstride, V4 (&acc)[3][NBI]) {
+    BVals<T, 3 * NBI> bb[2];
+    w.run(
+        bb,
         [&](int row, BVals<T, 3 * NBI> &x) {
-            const T *p = q + row * W5;
+            const T *p = q + __umul24(row, W5);
 #pragma unroll
             for (int j = 0; j < 3; ++j)
 #pragma unroll
@@ -57,14 +56,26 @@ __device__ __forceinline__ void interp3_products(const Op<T> &A, int g, int lane
 }
 
 // Elements per tile.  The wider the tile, the more matrix instructions each
-// operator fragment feeds (NE / 16 x 5 in FP32), which the measurements
-// favour over more workgroups per CU: FP32 tets and prisms take 32 (at
-// p = 4: 69 KB of LDS, two workgroups per CU for tets; 147 KB, one
-// workgroup of 16 wavefronts for prisms), hexahedra 16 (123 KB; 32 would not
-// fit, 8 was 24 % slower), FP64 4 (its LDS footprint per value is twice as
-// large).
+// operator fragment feeds and the longer the rows that memory accesses move,
+// which the measurements favour over more workgroups per CU: FP32 tets and
+// prisms take 32 (at p = 4: 74 KB of LDS, two workgroups per CU for tets;
+// 161 KB, one workgroup of 16 wavefronts for prisms; 16 elements measured
+// 572 -> 653 us and 497 -> 501 us), hexahedra 16 (123 KB), FP64 half of that.
 template <typename T, int ET>
-constexpr int tile_elems() { return sizeof(T) == 4 ? (ET == 2 ? 16 : 32) : 4; }
+constexpr int tile_elems() { return (ET == 2 ? 16 : 32) * 4 / int(sizeof(T)); }
+
+// Column block n of a tile, lane c16, is field v of element e: with at least
+// 16 elements, block NH i + h is field i of elements 16 h .. 16 h + 15.
+template <int NE>
+struct TileColumn {
+    int v, e;
+    __device__ __forceinline__ TileColumn(int n, int c16) {
+        constexpr int NH = NE >= 16 ? NE / 16 : 1;
+        const int flat = 16 * n + c16;
+        v = NE >= 16 ? n / NH : flat / NE;
+        e = NE >= 16 ? 16 * (n % NH) + c16 : flat - v * NE;
+    }
+};
 
 // One workgroup of NW wavefronts per tile.  MG: row blocks of the gradient
 // operator per wavefront (>= nmg / NW); their accumulators stay in registers
@@ -73,106 +84,69 @@ constexpr int tile_elems() { return sizeof(T) == 4 ? (ET == 2 ? 16 : 32) : 4; }
 // VD: the volume part D = [G'_0 G'_1 G'_2] Ft of the divergence is written
 // instead of Ft: Q stays in LDS until it is interpolated, then Ft takes its
 // place (phase 5) and is multiplied there (phase 6).
+// What bounds it (p = 4, 307,200-element box): the matrix cores and the waits
+// between the phases; the interpolation's and phase 6's first operator steps
+// and row numbers are loaded one phase ahead (tets 595 -> 571 us).
 template <typename T, int ET, int NE, int NW, int MG, bool VD>
-__global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(GradFluxArgs<T> a) {
     using v4 = typename Vec4<T>::type;
-    constexpr int W5 = TileShape<NE>::W5, NB = TileShape<NE>::NB;
+    constexpr int W5 = TileShape<NE>::W5, NB = TileShape<NE>::NB, WS = tile_stride<NE>();
     constexpr int NG = n_geom_coeffs<ET>();
-    constexpr int VPR = NE * int(sizeof(T)) / 16;       // 16-byte vectors per (row, field)
+    constexpr int V = 16 / int(sizeof(T)), VPR = NE / V;   // values per 16 bytes, 16-byte pieces per (row, field)
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int nu = a.nu, Kp = nu + a.nf;
-    // one region: B = [U; Cf] ([nu + nf][W5]) for the gradient product, then Qt
-    // and, in place, Q ([3 nu][W5], row k nu + i)
+    const int nu = a.nu, nf = a.nf;
+    // one region: B = [U; Cf] ([nu + nf][WS]) for the gradient product, then Qt
+    // and, in place, Q and Ft ([3 nu][WS], row k nu + i)
     T *Bs = reinterpret_cast<T *>(lds_raw);
     T *QT = Bs;
-    T *Gs = Bs + size_t(max(Kp, 3 * nu)) * W5;           // [NG][NE] Jacobian coefficients
+    T *Gs = Bs + size_t(max(nu + nf, 3 * nu)) * WS;      // [NG][NE] Jacobian coefficients
     T *Xs = Gs + NG * NE;                                // [nu][3] reference coordinates
 
     const int64_t e0 = int64_t(xcd_block()) * NE;
     if (e0 >= a.nelem) return;                           // whole workgroup: padding of the grid
     // the wavefront index is uniform in the wavefront: say so, so that the
-    // step lists are read through scalar loads and the loops branch on
-    // scalars
+    // loops branch on scalars
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int krow = lane >> 4, c16 = lane & 15;
     const int64_t ld = a.ld;
 
-    // 1. B rows: U (k < nu), Cf (nu <= k < nu + nf)
-    if constexpr (sizeof(T) == 4 && W5 == 5 * NE) {
-        // straight from memory into LDS (global_load_lds: no registers, and
-        // every load of the tile in flight before the one wait): chunk c
-        // (16 bytes) of B is row k, field v, elements 4 q .. 4 q + 3 with
-        // c = VPR (5 k + v) + q, and lane l of a wavefront instruction
-        // writes chunk base + l; the coefficients likewise, the reference
-        // coordinates value by value
-        const int nchunk = (nu + a.nf) * 5 * VPR;
-        for (int base = w * 64; base < nchunk; base += NW * 64) {
+    // 1. B rows: U (k < nu), Cf (nu <= k < nu + nf), straight from memory into
+    // LDS (no registers, every load of the tile in flight before the one wait)
+    tile_to_lds<T, NE, NW>(a.U, ld, e0, nu, Bs, w, lane);
+    tile_to_lds<T, NE, NW>(a.Cf, ld, e0, nf, Bs + size_t(nu) * WS, w, lane);
+    if (!a.padj)
+        for (int base = w * 64; base < NG * VPR; base += NW * 64) {
             const int c = base + lane;
-            if (c < nchunk) {
-                const int q = c % VPR, kv = c / VPR, v = kv % 5, k = kv / 5;
-                const T *src = k < nu ? a.U + (int64_t(k) * 5 + v) * ld + e0 + 4 * q
-                                      : a.Cf + (int64_t(k - nu) * 5 + v) * ld + e0 + 4 * q;
-                load_lds16(src, Bs + size_t(base) * 4);
-            }
+            if (c < NG * VPR) load_lds16(a.geom + int64_t(c / VPR) * ld + e0 + V * (c % VPR), Gs + size_t(base) * V);
         }
-        if (!a.padj)
-            for (int base = w * 64; base < NG * VPR; base += NW * 64) {
-                const int c = base + lane;
-                if (c < NG * VPR)
-                    load_lds16(a.geom + int64_t(c / VPR) * ld + e0 + 4 * (c % VPR), Gs + size_t(base) * 4);
-            }
-        for (int base = w * 64; base < 3 * nu; base += NW * 64) {
-            const int c = base + lane;
-            if (c < 3 * nu) load_lds4(a.xi + c, Xs + base);
-        }
-        __builtin_amdgcn_s_waitcnt(0);                   // this wavefront's direct loads are in LDS
-    } else {
-        for (int idx = tid; idx < 3 * nu; idx += 64 * NW) Xs[idx] = a.xi[idx];
-        const int nvec = Kp * 5 * VPR;
-        for (int idx = tid; idx < nvec; idx += 64 * NW) {
-            const int q = idx % VPR, kv = idx / VPR;
-            const int v = kv % 5, k = kv / 5;
-            const T *row = k < nu ? a.U + (int64_t(k) * 5 + v) * ld : a.Cf + (int64_t(k - nu) * 5 + v) * ld;
-            const floatx4 val = *reinterpret_cast<const floatx4 *>(row + e0 + q * (16 / sizeof(T)));
-            *reinterpret_cast<floatx4 *>(Bs + k * W5 + v * NE + q * (16 / sizeof(T))) = val;
-        }
-        if constexpr (W5 > 5 * NE) {
-            constexpr int PADC = W5 - 5 * NE;
-            for (int idx = tid; idx < Kp * PADC; idx += 64 * NW)
-                Bs[(idx / PADC) * W5 + 5 * NE + idx % PADC] = T(0);
-        }
-        if (!a.padj)
-            for (int idx = tid; idx < NG * NE; idx += 64 * NW)
-                Gs[idx] = a.geom[int64_t(idx / NE) * ld + e0 + idx % NE];
-    }
-    __syncthreads();
+    for (int idx = tid; idx < 3 * nu; idx += 64 * NW) Xs[idx] = a.xi[idx];
+    if constexpr (WS == W5 && W5 > 5 * NE)               // unused columns of the last block
+        for (int idx = tid; idx < (nu + nf) * (W5 - 5 * NE); idx += 64 * NW)
+            Bs[(idx / (W5 - 5 * NE)) * WS + 5 * NE + idx % (W5 - 5 * NE)] = T(0);
 
     // 2. Qt = [G_k | L_k] B: wavefront w takes row blocks w, w + NW, ..., each
     // against every column block
-    // (the Qt row of each accumulator is loaded before the products, so
-    // that its latency hides behind them)
     v4 acc[MG][NB];
     int qrow[MG][4];
 #pragma unroll
-    for (int m = 0; m < MG; ++m) {
-        const int g = w + m * NW;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) qrow[m][r] = g < a.G.nmg ? a.G.rowmap[16 * g + acc_row<T>(krow, r)] : -1;
-    }
+    for (int m = 0; m < MG; ++m) block_rows(a.G, w + m * NW, krow, qrow[m]);
+    __builtin_amdgcn_s_waitcnt(0);                       // this wavefront's direct loads are in LDS
+    __syncthreads();
 #pragma unroll
     for (int m = 0; m < MG; ++m) {
 #pragma unroll
         for (int n = 0; n < NB; ++n) acc[m][n] = v4{0, 0, 0, 0};
         const int g = w + m * NW;
         if (g < a.G.nmg) {
-            gather_products<T, NB>(a.G, g, lane, Bs + c16, W5, acc[m]);
+            GatherWalk<T> gwalk(a.G, g, lane);
+            gather_products(gwalk, Bs + c16, WS, acc[m]);
         }
     }
     // the states of this thread's first PI points of the point-wise phase,
     // from B while it is still in LDS (at p = 4 three cover every point of
     // an FP32 tet or prism tile)
     constexpr int PI = sizeof(T) == 4 && ET < 2 ? 3 : 2;
-    T u0[VD ? 1 : PI][5];
+    T uu[PI][5];
     if constexpr (!VD) {
 #pragma unroll
         for (int q = 0; q < PI; ++q) {
@@ -180,7 +154,7 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
             const int i = it / NE, e = it - i * NE;
             if (it < nu * NE) {
 #pragma unroll
-                for (int v = 0; v < 5; ++v) u0[q][v] = Bs[i * W5 + v * NE + e];
+                for (int v = 0; v < 5; ++v) uu[q][v] = Bs[i * WS + v * NE + e];
             }
         }
     }
@@ -192,10 +166,26 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
             const int row = qrow[m][r];
             if (row >= 0) {
 #pragma unroll
-                for (int n = 0; n < NB; ++n) QT[row * W5 + 16 * n + c16] = acc[m][n][r];
+                for (int n = 0; n < NB; ++n) QT[row * WS + 16 * n + c16] = acc[m][n][r];
             }
         }
     }
+    // the interpolation's work items: (row block g, part h of the column
+    // blocks) with the three directions together, so an operator fragment
+    // feeds 3 NBI matrix instructions; the first item's operator steps, flux
+    // points and faces are on their way during the point-wise phase
+    constexpr int NBI = NB % 5 == 0 ? 5 : NB, NH = NB / NBI;
+    const int nit = a.M.nmg * NH;
+    int frow[4];
+    unsigned fb[4];
+    auto item_rows = [&](int it) {
+        block_rows(a.M, it / NH, krow, frow);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            fb[r] = a.qmask ? unsigned(a.fbit[16 * min(it / NH, a.M.nmg - 1) + acc_row<T>(krow, r)]) : 1u;
+    };
+    item_rows(w);
+    GatherWalk<T> mwalk(a.M, min(w, nit - 1) / NH, lane);
     __syncthreads();
 
     // the metric of point i and element e of the tile: the adjugate, returns 1 / J
@@ -221,13 +211,26 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) x[k][v] = QT[(k * nu + i) * W5 + v * NE + e];
+            for (int v = 0; v < 5; ++v) x[k][v] = QT[(k * nu + i) * WS + v * NE + e];
     };
     auto point_write = [&](int i, int e, const T (&x)[3][5]) {
 #pragma unroll
         for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) QT[(k * nu + i) * W5 + v * NE + e] = x[k][v];
+            for (int v = 0; v < 5; ++v) QT[(k * nu + i) * WS + v * NE + e] = x[k][v];
+    };
+    // the states of this thread's points base + q 64 NW + tid, from memory
+    // (L2 serves them)
+    auto load_states = [&](int base) {
+#pragma unroll
+        for (int q = 0; q < PI; ++q) {
+            const int it = base + q * 64 * NW + tid;
+            const int i = it / NE, e = it - i * NE;
+            if (it < nu * NE && e0 + e < a.nelem) {
+#pragma unroll
+                for (int v = 0; v < 5; ++v) uu[q][v] = a.U[(int64_t(i) * 5 + v) * ld + e0 + e];
+            }
+        }
     };
 
     // 3. point-wise: one (solution point, element) per thread; Q replaces Qt
@@ -245,23 +248,11 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
     } else {
         // and Ft goes to memory.  A thread's first PI states came from B
         // above; further ones (B's place in LDS holds Qt now) come again from
-        // memory, where L2 serves them, and a thread loads those of its next
-        // PI points first, so that no load queues behind the Ft stores of the
-        // points before it (memory operations of a wavefront retire in order).
+        // memory, PI points at a time, so that no load queues behind the Ft
+        // stores of the points before it (memory operations of a wavefront
+        // retire in order).
         for (int base = 0; base < nu * NE; base += PI * 64 * NW) {
-            T uu[PI][5];
-#pragma unroll
-            for (int q = 0; q < PI; ++q) {
-                const int it = base + q * 64 * NW + tid;
-                const int i = it / NE, e = it - i * NE;
-                if (base == 0) {
-#pragma unroll
-                    for (int v = 0; v < 5; ++v) uu[q][v] = u0[q][v];
-                } else if (it < nu * NE && e0 + e < a.nelem) {
-#pragma unroll
-                    for (int v = 0; v < 5; ++v) uu[q][v] = a.U[(int64_t(i) * 5 + v) * ld + e0 + e];
-                }
-            }
+            if (base > 0) load_states(base);
 #pragma unroll
             for (int q = 0; q < PI; ++q) {
                 const int it = base + q * 64 * NW + tid;
@@ -282,103 +273,73 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
     }
     __syncthreads();
 
-    // 4. Qf = M0 Q for each gradient direction j: work items (row block, j).
-    // Column block n of lane l is element (16 n + l) % NE of the tile, stored
-    // only on the faces of it whose gradient is read (qm); the flux point
-    // and face of each accumulator row are loaded before the products,
-    // behind which their latency hides.
-    // (column blocks n and n + NE / 16 hold the same element)
+    // 4. Qf = M0 Q for the three gradient directions, stored only on the faces
+    // of an element whose gradient is read (qm of this lane's elements; none
+    // past the last element)
     constexpr int NQ = NE >= 16 ? NE / 16 : 1;
     unsigned qm[NQ];
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) qm[n] = a.qmask ? unsigned(a.qmask[e0 + (16 * n + c16) % NE]) : 0xffu;
-    if constexpr (sizeof(T) == 4 && NB == 10) {
-        // tiles of 32 (tets, prisms): work items (row block, column half)
-        // with the three directions together, so each operator fragment is
-        // loaded once for 15 matrix instructions and every wavefront takes
-        // at most one item at p = 4.  (Hexahedra, tiles of 16, keep the
-        // items per direction below: with one item per row block, 10 items
-        // would leave 6 of the 16 wavefronts idle.)
-        constexpr int NH = 2, NBI = 5;
-        const int nit = a.M.nmg * NH;
-        for (int it = w; it < nit; it += NW) {
-            const int g = it / NH, h = it - NH * g;
-            int frow[4];
-            unsigned fb[4];
+    for (int n = 0; n < NQ; ++n) {
+        const int64_t eg = e0 + (16 * n + c16) % NE;
+        qm[n] = eg >= a.nelem ? 0u : a.qmask ? unsigned(a.qmask[eg]) : 0xffu;
+    }
+    v4 acc3[3][NBI];
+    auto zero3 = [&]() {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int slot = 16 * g + acc_row<T>(krow, r);
-                frow[r] = a.M.rowmap[slot];
-                fb[r] = a.qmask ? unsigned(a.fbit[slot]) : 1u;
-            }
-            v4 acc3[3][NBI];
+        for (int j = 0; j < 3; ++j)
 #pragma unroll
-            for (int j = 0; j < 3; ++j)
+            for (int i = 0; i < NBI; ++i) acc3[j][i] = v4{0, 0, 0, 0};
+    };
+    auto store3 = [&](int it) {
+        const int h = it % NH;
 #pragma unroll
-                for (int i = 0; i < NBI; ++i) acc3[j][i] = v4{0, 0, 0, 0};
-            interp3_products<T, NBI, NH, W5>(a.M, g, lane, QT + 16 * h + c16, nu * W5, acc3);
+        for (int r = 0; r < 4; ++r) {
+            if (frow[r] < 0) continue;
+            T *qf = a.Qf + int64_t(frow[r]) * 15 * ld + e0;
+            if constexpr (NE >= 16) {
+                const TileColumn<NE> c(h, c16);
+                if (!(qm[h] & fb[r])) continue;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int f = frow[r];
-                if (f < 0) continue;
+                for (int j = 0; j < 3; ++j)
+#pragma unroll
+                    for (int i = 0; i < NBI; ++i) qf[(j * 5 + i) * ld + c.e] = acc3[j][i][r];
+            } else {
 #pragma unroll
                 for (int i = 0; i < NBI; ++i) {
-                    const int n = NH * i + h;
-                    const int flat = 16 * n + c16, v = flat / NE, e = flat - v * NE;
-                    if (v < 5 && e0 + e < a.nelem && (qm[n % NQ] & fb[r])) {
+                    const TileColumn<NE> c(NH * i + h, c16);
+                    if (c.v >= 5 || !(qm[0] & fb[r])) continue;
 #pragma unroll
-                        for (int j = 0; j < 3; ++j)
-                            a.Qf[(int64_t(f) * 15 + j * 5 + v) * ld + e0 + e] = acc3[j][i][r];
-                    }
+                    for (int j = 0; j < 3; ++j) qf[(j * 5 + c.v) * ld + c.e] = acc3[j][i][r];
                 }
             }
         }
-    } else {
-        const int nit = a.M.nmg * 3;
-        for (int it = w; it < nit; it += NW) {
-            const int g = it / 3, j = it - 3 * g;
-            int frow[4];
-            unsigned fb[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int slot = 16 * g + acc_row<T>(krow, r);
-                frow[r] = a.M.rowmap[slot];
-                fb[r] = a.qmask ? unsigned(a.fbit[slot]) : 1u;
-            }
-            const T *Qj = QT + size_t(j) * nu * W5 + c16;
-            v4 acc2[NB];
-#pragma unroll
-            for (int n = 0; n < NB; ++n) acc2[n] = v4{0, 0, 0, 0};
-            gather_products<T, NB>(a.M, g, lane, Qj, W5, acc2);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int f = frow[r];
-                if (f < 0) continue;
-#pragma unroll
-                for (int n = 0; n < NB; ++n) {
-                    const int flat = 16 * n + c16, v = flat / NE, e = flat - v * NE;
-                    if (v < 5 && e0 + e < a.nelem && (qm[n % NQ] & fb[r]))
-                        a.Qf[(int64_t(f) * 15 + j * 5 + v) * ld + e0 + e] = acc2[n][r];
-                }
-            }
+    };
+    int it4 = w;
+    zero3();
+    if (it4 < nit) {
+        interp3_products<NBI, NH, WS>(mwalk, QT + 16 * (it4 % NH) + c16, nu * WS, acc3);
+        for (; it4 + NW < nit; it4 += NW) {
+            store3(it4);
+            zero3();
+            item_rows(it4 + NW);
+            mwalk = GatherWalk<T>(a.M, (it4 + NW) / NH, lane);
+            interp3_products<NBI, NH, WS>(mwalk, QT + 16 * ((it4 + NW) % NH) + c16, nu * WS, acc3);
         }
     }
-    if constexpr (!VD) return;
+    if constexpr (!VD) {
+        if (it4 < nit) store3(it4);
+        return;
+    }
+    // (phase 6's first operator steps, ahead of the last Qf stores)
+    constexpr int ND = NBI, DH = NH;
+    const int ndt = a.V.nmg * DH;
+    GatherWalk<T> vwalk(a.V, min(w, ndt - 1) / DH, lane);
+    if (it4 < nit) store3(it4);
     __syncthreads();                                     // every wavefront is done with Q
 
-    // 5. Ft takes the place of Q (the states again from memory, where L2
-    // serves them, PI points at a time)
+    // 5. Ft takes the place of Q
     for (int base = 0; base < nu * NE; base += PI * 64 * NW) {
-        T uu[PI][5];
-#pragma unroll
-        for (int q = 0; q < PI; ++q) {
-            const int it = base + q * 64 * NW + tid;
-            const int i = it / NE, e = it - i * NE;
-            if (it < nu * NE && e0 + e < a.nelem) {
-#pragma unroll
-                for (int v = 0; v < 5; ++v) uu[q][v] = a.U[(int64_t(i) * 5 + v) * ld + e0 + e];
-            }
-        }
+        load_states(base);
 #pragma unroll
         for (int q = 0; q < PI; ++q) {
             const int it = base + q * 64 * NW + tid;
@@ -394,24 +355,22 @@ __global__ __launch_bounds__(64 * NW) void gradflux_kernel(GradFluxArgs<T> a) {
     __syncthreads();
 
     // 6. D = [G'_k] Ft: items (row block, part of the column blocks)
-    constexpr int ND = NB % 5 == 0 ? 5 : NB, DH = NB / ND;
-    for (int it = w; it < a.V.nmg * DH; it += NW) {
+    for (int it = w; it < ndt; it += NW) {
         const int g = it / DH, h = it - DH * g;
         int drow[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) drow[r] = a.V.rowmap[16 * g + acc_row<T>(krow, r)];
+        block_rows(a.V, g, krow, drow);
         v4 accd[ND];
 #pragma unroll
         for (int n = 0; n < ND; ++n) accd[n] = v4{0, 0, 0, 0};
-        gather_products<T, ND, DH>(a.V, g, lane, QT + 16 * h + c16, W5, accd);
+        if (it != w) vwalk = GatherWalk<T>(a.V, g, lane);
+        gather_products<DH>(vwalk, QT + 16 * h + c16, WS, accd);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (drow[r] < 0) continue;
+        for (int n = 0; n < ND; ++n) {
+            const TileColumn<NE> c(DH * n + h, c16);
+            if (c.v >= 5 || e0 + c.e >= a.nelem) continue;
 #pragma unroll
-            for (int n = 0; n < ND; ++n) {
-                const int flat = 16 * (DH * n + h) + c16, v = flat / NE, e = flat - v * NE;
-                if (v < 5 && e0 + e < a.nelem) a.D[(int64_t(drow[r]) * 5 + v) * ld + e0 + e] = accd[n][r];
-            }
+            for (int r = 0; r < 4; ++r)
+                if (drow[r] >= 0) a.D[(int64_t(drow[r]) * 5 + c.v) * ld + e0 + c.e] = accd[n][r];
         }
     }
 }
@@ -478,7 +437,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
             v4 acc[NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n) acc[n] = v4{0, 0, 0, 0};
-            gather_products<float, NB>(a.G, g, lane, Bs + c16, W5, acc);
+            GatherWalk<float> walk(a.G, g, lane);
+            gather_products(walk, Bs + c16, W5, acc);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = a.G.rowmap[16 * g + acc_row<float>(krow, r)];
@@ -533,7 +493,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
             v4 acc2[NB];
 #pragma unroll
             for (int n = 0; n < NB; ++n) acc2[n] = v4{0, 0, 0, 0};
-            gather_products<float, NB>(a.M, g, lane, Qj, W5, acc2);
+            GatherWalk<float> walk(a.M, g, lane);
+            gather_products(walk, Qj, W5, acc2);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int slot = 16 * g + acc_row<float>(krow, r), f = a.M.rowmap[slot];
@@ -566,8 +527,10 @@ template <typename T, int ET, int NE, int NW, bool VD>
 hipError_t launch_gf_vd(const GradFluxArgs<T> &a, size_t lds, hipStream_t s) {
     const int mg = (a.G.nmg + NW - 1) / NW;
     if (mg <= 1) return launch_gf_mg<T, ET, NE, NW, 1, VD>(a, lds, s);
-    if (mg <= 2) return launch_gf_mg<T, ET, NE, NW, 2, VD>(a, lds, s);
-    if (mg <= 4) return launch_gf_mg<T, ET, NE, NW, 4, VD>(a, lds, s);
+    if constexpr (sizeof(T) == 8 || ET == 2)
+        if (mg <= 2) return launch_gf_mg<T, ET, NE, NW, 2, VD>(a, lds, s);
+    if constexpr (sizeof(T) == 8 && ET == 2)
+        if (mg <= 4) return launch_gf_mg<T, ET, NE, NW, 4, VD>(a, lds, s);
     return hipErrorInvalidValue;
 }
 
@@ -610,7 +573,7 @@ namespace {
 template <typename T, int ET>
 size_t gradflux_lds_t(const GradFluxArgs<T> &a) {
     constexpr int NE = tile_elems<T, ET>();
-    constexpr int W5 = TileShape<NE>::W5;
+    constexpr int W5 = tile_stride<NE>();
     const size_t n = size_t(std::max(a.nu + a.nf, 3 * a.nu)) * W5 + size_t(n_geom_coeffs<ET>()) * NE +
                      size_t(3 * a.nu);
     const size_t bytes = n * sizeof(T);
@@ -646,11 +609,11 @@ hipError_t launch_gradflux(int etype, const GradFluxArgs<T> &a, hipStream_t s, b
     if constexpr (std::is_same<T, float>::value) {
         if (stream) return etype == 0 ? launch_gf_stream<0, 8>(a, lds, s) : launch_gf_stream<1, 8>(a, lds, s);
     }
-    // wavefronts per workgroup: tets 8 in FP32 (7 row blocks of the
-    // gradient operator at p = 4), prisms 16 (15 row blocks), hexahedra 16
-    // (24: two per wavefront); FP64 4, 4 and 8
+    // wavefronts per workgroup (row blocks of the gradient operator at p = 4:
+    // tets 7, prisms 15, hexahedra 25): FP32 8, 16 and 16; FP64, whose
+    // accumulators are twice as large, 4, 8 and 8
     if (etype == 0) return launch_gf<T, 0, tile_elems<T, 0>(), sizeof(T) == 4 ? 8 : 4>(a, lds, s);
-    if (etype == 1) return launch_gf<T, 1, tile_elems<T, 1>(), sizeof(T) == 4 ? 16 : 4>(a, lds, s);
+    if (etype == 1) return launch_gf<T, 1, tile_elems<T, 1>(), sizeof(T) == 4 ? 16 : 8>(a, lds, s);
     return launch_gf<T, 2, tile_elems<T, 2>(), sizeof(T) == 4 ? 16 : 8>(a, lds, s);
 }
 

@@ -101,44 +101,63 @@ __device__ __forceinline__ T neg_update(const NegArgs<T> &a, int i, int v, int64
     return outv;
 }
 
-// neg_update for the four consecutive elements e0 .. e0 + 3 of solution point
-// i and field v (o0 = (5 i + v) ld + e0), on 16-byte (FP32) / 32-byte (FP64)
-// loads and stores; elements past nelem are skipped.  The register pointers
-// are 4-element aligned (checked at entry).  Returns the values left in the
-// output register (the accumulator where there is no output).
+// What neg_update reads for the four consecutive elements e0 .. e0 + 3 of
+// solution point i and field v (o0 = (5 i + v) ld + e0), on 16-byte (FP32) /
+// 32-byte (FP64) loads, so that a kernel can issue them long before the
+// product they are combined with is there.  The register pointers are
+// 4-element aligned (checked at entry).
 template <typename T, typename V4>
-__device__ __forceinline__ V4 update4(const NegArgs<T> &ep, int i, int v, int64_t e0, int64_t o0, const V4 &val) {
-    V4 res = V4{0, 0, 0, 0};
-    if (e0 + 3 < ep.nelem && !ep.cy) {
-        // four whole elements: the same arithmetic as neg_update
-        const V4 J = *reinterpret_cast<const V4 *>(ep.jinv + int64_t(i) * ep.ld + e0);
-        const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
-        V4 k;
+struct UpdateIn {
+    V4 J, acc, base;
+};
+// Whether the four elements go through update4 (else element by element).
+template <typename T>
+__device__ __forceinline__ bool update4_whole(const NegArgs<T> &ep, int64_t e0) {
+    return e0 + 3 < ep.nelem && !ep.cy;
+}
+template <typename T, typename V4>
+__device__ __forceinline__ void update4_load(const NegArgs<T> &ep, int i, int64_t e0, int64_t o0,
+                                             UpdateIn<T, V4> &x) {
+    x.J = *reinterpret_cast<const V4 *>(ep.jinv + int64_t(i) * ep.ld + e0);
+    if (ep.acc) x.acc = *reinterpret_cast<const V4 *>(ep.acc + o0);
+    if (ep.out && ep.base) x.base = *reinterpret_cast<const V4 *>(ep.base + o0);
+}
+// The arithmetic of neg_update on them (the step sizes of a batch and the
+// error register of the adaptive scheme are read here).  Returns the values
+// left in the output register (the accumulator where there is no output).
+template <typename T, typename V4>
+__device__ __forceinline__ V4 update4(const NegArgs<T> &ep, int64_t e0, int64_t o0, const V4 &val,
+                                      const UpdateIn<T, V4> &x) {
+    V4 res = V4{0, 0, 0, 0}, k;
+    const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            k[j] = -T(val[j]) * J[j];
-            k[j] *= S[j];
-        }
-        if (ep.err) {
-            V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) er[j] = er[j] + ep.c * k[j];
-            *reinterpret_cast<V4 *>(ep.err + o0) = er;
-        }
-        if (ep.acc) {
-            res = *reinterpret_cast<const V4 *>(ep.acc + o0);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) res[j] = res[j] + ep.a * k[j];
-            *reinterpret_cast<V4 *>(ep.acc + o0) = res;
-        }
-        if (ep.out) {
-            if (ep.base) res = *reinterpret_cast<const V4 *>(ep.base + o0);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) res[j] = res[j] + ep.b * k[j];
-            *reinterpret_cast<V4 *>(ep.out + o0) = res;
-        }
-        return res;
+    for (int j = 0; j < 4; ++j) {
+        k[j] = -T(val[j]) * x.J[j];
+        k[j] *= S[j];
     }
+    if (ep.err) {
+        V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) er[j] = er[j] + ep.c * k[j];
+        *reinterpret_cast<V4 *>(ep.err + o0) = er;
+    }
+    if (ep.acc) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) res[j] = x.acc[j] + ep.a * k[j];
+        *reinterpret_cast<V4 *>(ep.acc + o0) = res;
+    }
+    if (ep.out) {
+        if (ep.base) res = x.base;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) res[j] = res[j] + ep.b * k[j];
+        *reinterpret_cast<V4 *>(ep.out + o0) = res;
+    }
+    return res;
+}
+// The same element by element; elements past nelem are skipped.
+template <typename T, typename V4>
+__device__ __forceinline__ V4 update4_tail(const NegArgs<T> &ep, int i, int v, int64_t e0, int64_t o0, const V4 &val) {
+    V4 res = V4{0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         if (e0 + j < ep.nelem) res[j] = neg_update(ep, i, v, e0 + j, o0 + j, T(val[j]));
@@ -156,7 +175,14 @@ __device__ __forceinline__ void store_c(T *C, int64_t ldc, int row, int64_t col,
     if constexpr (TAG % 4 == 3) {
         if (ep.fuse) {
             const int v = int(col / ep.ld);
-            update4(ep, row, v, col - int64_t(v) * ep.ld, int64_t(row) * ldc + col, val);
+            const int64_t e0 = col - int64_t(v) * ep.ld, o0 = int64_t(row) * ldc + col;
+            if (update4_whole(ep, e0)) {
+                UpdateIn<T, V4> x;
+                update4_load(ep, row, e0, o0, x);
+                update4(ep, e0, o0, val, x);
+            } else {
+                update4_tail(ep, row, v, e0, o0, val);
+            }
             return;
         }
     }

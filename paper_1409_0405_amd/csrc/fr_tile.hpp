@@ -5,6 +5,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "fr_device.hpp"
 #include "fr_opmul.hpp"
 
@@ -23,6 +25,15 @@ __device__ __forceinline__ V sload(const V *p, int i) {
     return ((const __attribute__((address_space(4))) V *)p)[i];
 }
 
+// f(0), f(1), ..., f(N - 1) with the index as a compile-time constant
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unrolled<N, I + 1>(f);
+    }
+}
+
 // 16 (4) bytes from memory straight into LDS (global_load_lds): lane l of
 // the wavefront writes dst + 16 l (dst + 4 l), dst uniform in the wavefront.
 __device__ __forceinline__ void load_lds16(const void *src, void *dst) {
@@ -32,58 +43,59 @@ __device__ __forceinline__ void load_lds4(const void *src, void *dst) {
     __builtin_amdgcn_global_load_lds(src, dst, 4, 0, 0);
 }
 
-// Walk of a gathered operator (Op stage 7) over one row block: the K steps of
-// the block, each naming the four rows of B that its fragment multiplies.
-// The lists are read through the scalar cache four steps at a time and one
-// group ahead (both lists have slack at their end, so the walk reads past a
-// block without a test), the fragments travel four steps ahead of their use
-// and the B values (LDS) one step.
+// One lane's share of a step of a gathered operator (Op stage 7): its
+// fragment value and the row of B it multiplies, loaded together.
 template <typename T>
+struct GatherStep {
+    T a;
+    int row;
+};
+
+// Walk of a gathered operator over one row block.  The first AD steps are
+// loaded when the walk is made (before a barrier or a wait that comes
+// anyway), later ones AD steps ahead of their use; the B values (LDS) one
+// step ahead.  The loop has no exit between its steps, so the compiler counts
+// the loads in flight instead of waiting for all of them, and the lane's rows
+// come with the fragments: read through the scalar cache, their loads shared
+// the counter of the LDS reads and every step waited for both.
+template <typename T, int AD = 4>
 struct GatherWalk {
-    const uint64_t *kl;
-    const T *frag;      // this lane's fragment of step 0
-    int ns, sel, sh;    // steps; this lane's row of a step: dword sel, bits sh .. sh + 15
+    static_assert(AD % 2 == 0, "two B buffers take turns");
+    using Step = GatherStep<T>;
+    const Step *p;
+    int ns;
+    Step s[AD];
     __device__ __forceinline__ GatherWalk(const Op<T> &A, int g, int lane) {
         const int s0 = sload(A.koff, g);
         ns = sload(A.koff, g + 1) - s0;
-        kl = reinterpret_cast<const uint64_t *>(A.klist) + s0;
-        frag = A.frag + size_t(s0) * 64 + lane;
-        sel = lane >> 5;
-        sh = 16 * ((lane >> 4) & 1);
+        p = reinterpret_cast<const Step *>(A.frag) + size_t(s0) * 64 + lane;
+#pragma unroll
+        for (int d = 0; d < AD; ++d) s[d] = p[size_t(d) * 64];
     }
-    __device__ __forceinline__ int row(uint64_t q) const {
-        const unsigned d = sel ? unsigned(q >> 32) : unsigned(q);
-        return int((d >> sh) & 0xffffu);
-    }
-    // for each step in order: load(row, buffer) fills the next step's B
-    // values, mul(fragment, buffer) multiplies the current one's
+    // load(row, buffer) fills the B values of a step, mul(fragment, buffer)
+    // multiplies them; steps in order.  Reads up to AD steps past the block
+    // (the lists have slack).
     template <typename Buf, typename Load, typename Mul>
-    __device__ __forceinline__ void run(Buf &b0, Buf &b1, Load load, Mul mul) const {
-        T a[4];
-        uint64_t q[4];
+    __device__ __forceinline__ void run(Buf (&b)[2], Load load, Mul mul) {
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            a[d] = frag[size_t(d) * 64];
-            q[d] = sload(kl, d + 1);
+        for (int d = 0; d < AD; ++d) {
+            s[d].a = opaque(s[d].a);
+            s[d].row = opaque(s[d].row);
         }
-        load(row(sload(kl, 0)), b0);
-        for (int st = 0; st < ns; st += 4) {
-            uint64_t qn[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) qn[d] = sload(kl, st + d + 5);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                if (st + d >= ns) break;
-                load(row(q[d]), b1);
-                __builtin_amdgcn_sched_barrier(0);
-                mul(a[d], b0);
-                __builtin_amdgcn_sched_barrier(0);
-                a[d] = frag[size_t(st + d + 4) * 64];
-                b0 = b1;
-            }
-#pragma unroll
-            for (int d = 0; d < 4; ++d) q[d] = qn[d];
-        }
+        load(s[0].row, b[0]);
+        auto step = [&](auto dc, int st) {
+            constexpr int d = decltype(dc)::value;
+            load(s[(d + 1) % AD].row, b[(d + 1) % 2]);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(s[d].a, b[d % 2]);
+            __builtin_amdgcn_sched_barrier(0);
+            s[d] = p[size_t(st + d + AD) * 64];
+        };
+        int st = 0;
+        for (; st + AD <= ns; st += AD) unrolled<AD>([&](auto dc) { step(dc, st); });
+        unrolled<AD - 1>([&](auto dc) {
+            if (st + decltype(dc)::value < ns) step(dc, st);
+        });
     }
 };
 
@@ -92,19 +104,18 @@ struct BVals {
     T v[N];
 };
 
-// acc[n] += A_g B[:, 16 ST n .. 16 ST n + 15] for row block g of a gathered
-// operator; b points at row 0 of B in LDS (rows ws values apart), column
-// lane % 16 of the first column block.  The K order is the operator's column
-// order, as in the product kernels, and an accumulator that starts at +0 is
-// never -0, so the exact-zero products that a step leaves out or adds change
-// no bit.
-template <typename T, int NB, int ST = 1, typename V4>
-__device__ __forceinline__ void gather_products(const Op<T> &A, int g, int lane, const T *b, int ws, V4 (&acc)[NB]) {
-    BVals<T, NB> b0, b1;
-    GatherWalk<T>(A, g, lane).run(
-        b0, b1,
+// acc[n] += A_g B[:, 16 ST n .. 16 ST n + 15] for the row block of a walk; b
+// points at row 0 of B in LDS (rows ws values apart), column lane % 16 of the
+// first column block.  The K order is the operator's column order, as in the
+// product kernels, and an accumulator that starts at +0 is never -0, so the
+// exact-zero products that a step leaves out or adds change no bit.
+template <int ST = 1, typename T, int AD, int NB, typename V4>
+__device__ __forceinline__ void gather_products(GatherWalk<T, AD> &w, const T *b, int ws, V4 (&acc)[NB]) {
+    BVals<T, NB> bb[2];
+    w.run(
+        bb,
         [&](int row, BVals<T, NB> &x) {
-            const T *p = b + row * ws;
+            const T *p = b + __umul24(row, ws);
 #pragma unroll
             for (int n = 0; n < NB; ++n) x.v[n] = p[16 * ST * n];
         },
@@ -114,10 +125,21 @@ __device__ __forceinline__ void gather_products(const Op<T> &A, int g, int lane,
         });
 }
 
+// The operator rows of this lane's accumulator elements in row block g (-1:
+// none), and -1 for a block past the operator's last.
+template <typename T>
+__device__ __forceinline__ void block_rows(const Op<T> &A, int g, int krow, int (&row)[4]) {
+    const int gc = min(g, A.nmg - 1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) row[r] = A.rowmap[16 * gc + acc_row<T>(krow, r)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) row[r] = g < A.nmg ? row[r] : -1;
+}
+
 // Whether op is a gathered operator of M rows.
 template <typename T>
 bool gathered(const Op<T> &op, int M) {
-    return op.stage == 7 && op.mbw == 1 && op.M == M && op.nmg > 0 && op.frag && op.klist && op.koff && op.rowmap;
+    return op.stage == 7 && op.mbw == 1 && op.M == M && op.nmg > 0 && op.frag && op.koff && op.rowmap;
 }
 
 // Tile of NE elements with all five fields: row r of a tile in LDS holds W5
@@ -128,6 +150,32 @@ struct TileShape {
     static constexpr int W5 = (5 * NE + 15) / 16 * 16;
     static constexpr int NB = W5 / 16;
 };
+
+// Row stride of a tile in LDS.  A matrix instruction reads B at four
+// consecutive rows and 16 columns: with 80 values per row (tiles of 16) the
+// four rows fall into different banks, with 160 (tiles of 32) rows two apart
+// would share theirs, so those rows are 16 values longer.
+template <int NE>
+constexpr int tile_stride() { return NE == 32 ? 176 : TileShape<NE>::W5; }
+
+// Rows [0, rows) of a [rows][5][ld] array, elements e0 .. e0 + NE - 1, straight
+// into LDS rows of stride WS (no registers; the caller waits).
+template <typename T, int NE, int NW>
+__device__ __forceinline__ void tile_to_lds(const T *src, int64_t ld, int64_t e0, int rows, T *dst, int w, int lane) {
+    constexpr int V = 16 / int(sizeof(T)), VPR = NE / V, W5 = 5 * NE, WS = tile_stride<NE>();
+    if constexpr (WS == W5) {
+        const int nchunk = rows * 5 * VPR;
+        for (int base = w * 64; base < nchunk; base += NW * 64) {
+            const int c = base + lane, q = c % VPR, kv = c / VPR;     // kv = 5 row + field
+            if (c < nchunk) load_lds16(src + int64_t(kv) * ld + e0 + V * q, dst + size_t(base) * V);
+        }
+    } else {
+        // padded rows: one instruction per row, its 5 VPR 16-byte pieces
+        const int q = lane % VPR, v = lane / VPR;
+        for (int k = w; k < rows; k += NW)
+            if (lane < 5 * VPR) load_lds16(src + (int64_t(k) * 5 + v) * ld + e0 + V * q, dst + size_t(k) * WS);
+    }
+}
 
 constexpr size_t TILE_LDS_MAX = 160 * 1024;   // LDS of a CU
 
