@@ -319,12 +319,14 @@ frd::Op<T> fragment(const std::vector<double> &A_in, int M, int K, std::vector<T
 // prism gradient 191 -> 100, hexahedron gradient 285 -> 130).  Rows are
 // grouped greedily by the columns they touch, in groups of the size that
 // gives the fewest steps: blocks of 15 leave a row slot empty but fit the
-// layers and lines of order 4.
+// layers and lines of order 4.  split > 0: the columns before and from split
+// on make two lists per block.
 template <typename T>
 frd::Op<T> fragment_gathered(const std::vector<double> &A, int M, int K, std::vector<T> &f,
-                             std::vector<int32_t> &idx) {
-    constexpr int WORDS = 8;                           // K <= 512 columns
+                             std::vector<int32_t> &idx, int split = 0) {
+    constexpr int WORDS = 16;                           // K <= 1024 columns
     using Mask = std::array<uint64_t, WORDS>;
+    const int words = (K + 63) / 64;
     std::vector<Mask> mask(M);
     for (int r = 0; r < M; ++r) {
         mask[r].fill(0);
@@ -351,7 +353,7 @@ frd::Op<T> fragment_gathered(const std::vector<double> &A, int M, int K, std::ve
                 for (int r = 0; r < M; ++r) {
                     if (used[r]) continue;
                     int add = 0;
-                    for (int w = 0; w < WORDS; ++w) add += __builtin_popcountll(mask[r][w] & ~b.cols[w]);
+                    for (int w = 0; w < words; ++w) add += __builtin_popcountll(mask[r][w] & ~b.cols[w]);
                     if (add < best_add) {
                         best_add = add;
                         best = r;
@@ -359,7 +361,7 @@ frd::Op<T> fragment_gathered(const std::vector<double> &A, int M, int K, std::ve
                 }
                 used[best] = 1;
                 b.rows.push_back(best);
-                for (int w = 0; w < WORDS; ++w) b.cols[w] |= mask[best][w];
+                for (int w = 0; w < words; ++w) b.cols[w] |= mask[best][w];
             }
             blocks.push_back(std::move(b));
         }
@@ -392,19 +394,23 @@ frd::Op<T> fragment_gathered(const std::vector<double> &A, int M, int K, std::ve
         std::memcpy(&c, &c32, 4);
         f.push_back(c);
     };
+    op.parts = split ? 2 : 1;
     for (const Block &b : blocks) {
-        std::vector<int> ks;
-        for (int c = 0; c < K; ++c)
-            if (b.cols[c / 64] >> (c % 64) & 1) ks.push_back(c);
-        const size_t nreal = ks.size();
-        if (ks.empty()) ks.push_back(0);
-        while (ks.size() % 4) ks.push_back(ks.back());  // with zero entries
-        for (size_t st = 0; st < ks.size() / 4; ++st)
-            for (int l = 0; l < 64; ++l) {
-                const size_t r = l % 16, k = 4 * st + l / 16;
-                put(r < b.rows.size() && k < nreal ? T(A[size_t(b.rows[r]) * K + ks[k]]) : T(0), ks[k]);
-            }
-        koff.push_back(koff.back() + int32_t(ks.size() / 4));
+        for (int part = 0; part < op.parts; ++part) {
+            const int c0 = part ? split : 0, c1 = part || !split ? K : split;
+            std::vector<int> ks;
+            for (int c = c0; c < c1; ++c)
+                if (b.cols[c / 64] >> (c % 64) & 1) ks.push_back(c);
+            const size_t nreal = ks.size();
+            if (ks.empty()) ks.push_back(c0);
+            while (ks.size() % 4) ks.push_back(ks.back());  // with zero entries
+            for (size_t st = 0; st < ks.size() / 4; ++st)
+                for (int l = 0; l < 64; ++l) {
+                    const size_t r = l % 16, k = 4 * st + l / 16;
+                    put(r < b.rows.size() && k < nreal ? T(A[size_t(b.rows[r]) * K + ks[k]]) : T(0), ks[k] - c0);
+                }
+            koff.push_back(koff.back() + int32_t(ks.size() / 4));
+        }
         for (size_t r = 0; r < 16; ++r) rowmap.push_back(r < b.rows.size() ? b.rows[r] : -1);
     }
     for (int i = 0; i < 64 * SLACK; ++i) put(T(0), 0);
@@ -438,7 +444,7 @@ hipError_t upload_op(frd::Op<T> &op, const std::vector<T> &f, const std::vector<
         if ((e = hipMemcpy(p, idx.data(), idx.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess)
             return e;
         op.koff = static_cast<int32_t *>(p);
-        op.rowmap = op.koff + op.nmg + 1;
+        op.rowmap = op.koff + op.nmg * op.parts + 1;
     }
     return hipSuccess;
 }
@@ -612,7 +618,7 @@ fr_status setup_device(fr_mesh m, hipStream_t s) {
             if (ns) gint_rows[t].assign(idx.end() - 16 * D.Fgint.nmg, idx.end());
             const int Kd = 3 * nu + nf, k0 = ns ? 3 * nu : 0;
             const std::vector<double> part = columns(div, nu, Kd, k0, Kd);
-            D.Tdiv = fragment_gathered<T>(part, nu, Kd - k0, f, idx);
+            D.Tdiv = fragment_gathered<T>(part, nu, Kd - k0, f, idx, ns ? 0 : 3 * nu);
             FR_HIP(m, upload_op(D.Tdiv, f, idx, d.allocs));
             frd::DivTileArgs<T> ta;
             ta.A = D.Tdiv;
@@ -916,6 +922,11 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     for (int t = 0; t < frh::NTYPE; ++t) {
         DevType<T> &D = d.t[t];
         if (!D.nelem || (uf && uf[t])) continue;
+        if (D.Fgint.frag && D.tile_interp) {
+            FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
+                      frd::launch_interptile<T>(D.Fgint, U[t], D.Uf, D.ld, D.nelem, D.nu, s));
+            continue;
+        }
         const int64_t w5 = 5 * D.ld;
         FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
                   opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U[t], w5, D.nu, nullptr, 0, 0, D.Uf, w5, w5, s));

@@ -37,8 +37,10 @@ struct Op {
     // 7 = gathered, for the kernels on element tiles (mbw = 1): each step of a
     // row block multiplies four columns of its own, the block's nonzero
     // columns in ascending order; frag holds (value, column) pairs, lane l of
-    // step s at pair 64 s + l; koff counts steps.
-    int stage = 0;
+    // step s at pair 64 s + l; koff counts steps.  With parts = 2 a block has
+    // two lists, 2 g and 2 g + 1, for two ranges of columns (the second
+    // counted from its first column).
+    int stage = 0, parts = 1;
     const int32_t *klist = nullptr, *koff = nullptr, *rowmap = nullptr;
 };
 
@@ -234,7 +236,8 @@ struct DivTileArgs {
     int64_t ld = 0, nelem = 0;
     int nu = 0, nf = 0;
     T gamma = 0, pref = 0;
-    Op<T> A;                 // Euler [G'_k | L], nu x (3 nu + nf); Navier-Stokes L, nu x nf (stage 7)
+    // Euler [G'_k | L], nu x (3 nu + nf) in two parts; Navier-Stokes L, nu x nf (stage 7)
+    Op<T> A;
     Op<T> M;                 // M0, nf x nu (stage 7)
     NegArgs<T> ep;           // the last pipeline step (Rt unused)
 };
@@ -243,6 +246,9 @@ template <typename T>
 bool divtile_supported(int etype, const DivTileArgs<T> &a, bool euler);
 template <typename T>
 hipError_t launch_divtile(int etype, bool euler, const DivTileArgs<T> &a, hipStream_t s);
+// Uf [nf][5][ld] = M0 U, U [nu][5][ld] (M0 gathered, stage 7).
+template <typename T>
+hipError_t launch_interptile(const Op<T> &M, const T *U, T *Uf, int64_t ld, int64_t nelem, int nu, hipStream_t s);
 
 // FP64 reductions: per-block partial sums of nq quantities over one type,
 // written to partial[block][nq]; a second pass sums the blocks in order.

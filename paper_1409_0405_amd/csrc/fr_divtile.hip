@@ -6,13 +6,12 @@
 // the point-wise kernel), and, between two Runge-Kutta stages, the next
 // stage's input, which the interpolation to the flux points reads back.  One
 // workgroup takes a tile of NE elements with all five fields:
-//   1. B -> LDS: the common normal flux Fn, and for the Euler equations in
-//      front of it Ft = adj F(U), evaluated from the state (15 values per
-//      point that never reach memory).  For Navier-Stokes the fused gradient
-//      stage has left the volume part D = [G'_0 G'_1 G'_2] Ft in memory, five
-//      values per point instead of fifteen, and the sums start from it;
-//   2. Rt = [G'_k | L] [Ft; Fn] (Navier-Stokes: D + L Fn) on the matrix cores
-//      -> LDS;
+//   1. the volume part [G'_0 G'_1 G'_2] Ft.  Euler: Ft = adj F(U) -> LDS,
+//      evaluated from the state (15 values per point that never reach
+//      memory), and its product on the matrix cores.  For Navier-Stokes the
+//      fused gradient stage has left it in memory as D, five values per point
+//      instead of fifteen, and the sums start from it;
+//   2. the common normal flux Fn -> LDS, Rt = volume part + L Fn -> LDS;
 //   3. -Rt / J and the Runge-Kutta register update on 16-byte rows;
 //   4. inside a time step, U_f = M0 r of the state r just written (the next
 //      stage's input, still in LDS) -> memory, so the next stage needs no
@@ -32,21 +31,57 @@
 namespace frd {
 namespace {
 
-// NE elements per workgroup of NW wavefronts; MI: work items (row block,
-// column half) of the divergence product per wavefront, whose accumulators
-// stay in registers until every wavefront has read B.  Column block n of half
-// h holds field n of elements 16 h .. 16 h + 15, so a lane's accumulators are
-// one element's.
-template <typename T, int ET, int NE, int NW, int MI, bool EULER>
-__global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
+// U_f = M0 U for the tile in LDS: wavefront w takes items w, w + NW, ... (row
+// block, every NH-th column block); walk and frow hold the first one's.
+template <typename T, int NE, int NBI, int NW>
+__device__ __forceinline__ void interp_items(const Op<T> &M, const T *Bs, T *Uf, int64_t ld, int64_t e0, int64_t nelem,
+                                             int w, int lane, GatherWalk<T> &walk, int (&frow)[4]) {
     using v4 = typename Vec4<T>::type;
-    constexpr int W5 = TileShape<NE>::W5, WS = tile_stride<NE>(), NH = W5 / 80, NBI = 5;
-    static_assert(W5 == 5 * NE && W5 % 80 == 0, "whole column blocks");
-    constexpr int NG = n_geom_coeffs<ET>(), VPR = NE * int(sizeof(T)) / 16;
+    constexpr int WS = tile_stride<NE>(), NH = TileShape<NE>::NB / NBI;
+    const int krow = lane >> 4, c16 = lane & 15;
+    for (int it = w; it < M.nmg * NH; it += NW) {
+        const int g = it / NH, h = it - NH * g;
+        v4 af[NBI];
+#pragma unroll
+        for (int i = 0; i < NBI; ++i) af[i] = v4{0, 0, 0, 0};
+        if (it != w) {
+            block_rows(M, g, krow, frow);
+            walk = GatherWalk<T>(M, g, lane);
+        }
+        gather_products<NH>(walk, Bs + 16 * h + c16, WS, af);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (frow[r] < 0) continue;
+            T *u = Uf + int64_t(frow[r]) * 5 * ld + e0;
+#pragma unroll
+            for (int i = 0; i < NBI; ++i) {
+                const TileColumn<NE> c(NH * i + h, c16);
+                if (e0 + c.e < nelem) u[c.v * ld + c.e] = af[i][r];
+            }
+        }
+    }
+}
+
+// A workgroup of NW wavefronts takes NE elements.  NBI column blocks make a
+// work item (row block, every (NB / NBI)-th column block); MI: items of the
+// divergence product per wavefront, whose accumulators stay in registers
+// until every wavefront has read B.
+//
+// Euler: Ft and Fn take turns in LDS, so a tile needs the larger of the two
+// (Fn travels in registers while G' Ft is multiplied): at p = 3 a prism tile
+// of 16 elements needs 38 KB instead of 61 KB and four workgroups share a CU.
+// Order 3, FP32, 13,824 prisms and 24,576 tets: 92.0 -> 76.2 us for the right-hand side.
+// The register bounds keep two workgroups of eight wavefronts (FP32) on a CU.
+template <typename T, int ET, int NE, int NBI, int NW, int MI, bool EULER>
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? NW == 4 ? 3 : 4 : 2) void divtile_kernel(DivTileArgs<T> a) {
+    using v4 = typename Vec4<T>::type;
+    constexpr int W5 = TileShape<NE>::W5, WS = tile_stride<NE>(), NB = W5 / 16, NH = NB / NBI;
+    static_assert(W5 == 5 * NE && NB % NBI == 0, "whole column blocks");
+    constexpr int NG = n_geom_coeffs<ET>(), V = 16 / int(sizeof(T)), VPR = NE / V;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int nu = a.nu, nf = a.nf, k0 = EULER ? 3 * nu : 0;
-    T *Bs = reinterpret_cast<T *>(lds_raw);              // [max(k0 + nf, nu)][WS]
-    T *Gs = Bs + size_t(max(k0 + nf, nu)) * WS;          // Euler: [NG][NE] Jacobian coefficients
+    const int nu = a.nu, nf = a.nf;
+    T *Bs = reinterpret_cast<T *>(lds_raw);              // [divtile_rows][WS]
+    T *Gs = Bs + size_t(EULER ? max(3 * nu, nf) : max(nf, nu)) * WS;   // Euler: [NG][NE] Jacobian coefficients
     T *Xs = Gs + NG * NE;                                // Euler: [nu][3] reference coordinates
 
     const int64_t e0 = int64_t(xcd_block()) * NE;
@@ -55,8 +90,40 @@ __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
     const int krow = lane >> 4, c16 = lane & 15;
     const int64_t ld = a.ld;
 
-    // 1. B
-    tile_to_lds<T, NE, NW>(a.Fn, ld, e0, nf, Bs + size_t(k0) * WS, w, lane);
+    // Fn: straight into LDS (Navier-Stokes); the first FR 16-byte pieces per
+    // thread into registers (Euler; the piece's row, field and position in it)
+    constexpr int FR = NW == 16 ? 2 : 6;
+    floatx4 fr[EULER ? FR : 1];
+    auto piece = [&](int c, int &dst) -> const T * {
+        const int row = c / (5 * VPR), q = c - row * (5 * VPR);
+        dst = row * WS + V * q;
+        return a.Fn + (int64_t(row) * 5 + q / VPR) * ld + e0 + V * (q % VPR);
+    };
+    // the first PT solution points of this thread (Euler)
+    constexpr int PT = NW == 16 ? 1 : 2;
+    T u[EULER ? PT : 1][5];
+    auto load_points = [&](int base) {
+#pragma unroll
+        for (int q = 0; q < PT; ++q) {
+            const int it = base + q * 64 * NW + tid, i = it / NE, e = it - i * NE;
+            if (it < nu * NE && e0 + e < a.nelem) {
+#pragma unroll
+                for (int v = 0; v < 5; ++v) u[q][v] = a.U[(int64_t(i) * 5 + v) * ld + e0 + e];
+            }
+        }
+    };
+    if constexpr (EULER) {
+        if (!a.padj)
+            for (int base = w * 64; base < NG * VPR; base += NW * 64) {
+                const int c = base + lane;
+                if (c < NG * VPR)
+                    load_lds16(a.geom + int64_t(c / VPR) * ld + e0 + V * (c % VPR), Gs + size_t(base) * V);
+            }
+        for (int idx = tid; idx < 3 * nu; idx += 64 * NW) Xs[idx] = a.xi[idx];
+        load_points(0);
+    } else {
+        tile_to_lds<T, NE, NW>(a.Fn, ld, e0, nf, Bs, w, lane);
+    }
     v4 acc[MI][NBI];
     int rrow[MI][4];
 #pragma unroll
@@ -64,79 +131,101 @@ __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
         const int it = w + m * NW, g = it / NH, h = it - NH * g;
         block_rows(a.A, g, krow, rrow[m]);
 #pragma unroll
-        for (int i = 0; i < NBI; ++i) acc[m][i] = v4{0, 0, 0, 0};
-        if constexpr (!EULER) {
-            // (rows past the last are read as row 0: their sums are not used)
+        for (int i = 0; i < NBI; ++i) {
+            acc[m][i] = v4{0, 0, 0, 0};
+            if constexpr (!EULER) {
+                // (rows past the last are read as row 0: their sums are not used)
+                const TileColumn<NE> c(NH * i + h, c16);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const T *d = a.D + int64_t(max(rrow[m][r], 0)) * 5 * ld + e0 + 16 * h + c16;
-#pragma unroll
-                for (int i = 0; i < NBI; ++i) acc[m][i][r] = d[i * ld];
+                for (int r = 0; r < 4; ++r)
+                    acc[m][i][r] = a.D[(int64_t(max(rrow[m][r], 0)) * 5 + c.v) * ld + e0 + c.e];
             }
         }
     }
-    // what this thread's first PU items of the update read (J and the
-    // registers), on its way while the tile is loaded and multiplied
-    constexpr int Q = NE / 4, PU = 1;
-    UpdateIn<T, v4> up[PU];
-#pragma unroll
-    for (int m = 0; m < PU; ++m) {
-        const int idx = tid + m * 64 * NW, q = idx % Q, iv = idx / Q;
-        const int64_t eg = e0 + 4 * q;
-        if (idx < nu * 5 * Q && update4_whole(a.ep, eg)) update4_load(a.ep, iv / 5, eg, int64_t(iv) * ld + eg, up[m]);
-    }
-    // (the first item's operator steps travel with the tile)
-    GatherWalk<T> walk(a.A, min(w / NH, a.A.nmg - 1), lane);
+    // what this thread's first item of the update reads (J and the registers)
+    // and the first product item's operator steps travel with the tile
+    // (Euler: with Fn's product)
+    constexpr int Q = NE / 4;
+    UpdateIn<T, v4> up;
+    auto first_update = [&] {
+        const int64_t eg = e0 + 4 * (tid % Q);
+        if (tid < nu * 5 * Q && update4_whole(a.ep, eg)) update4_load(a.ep, tid / Q / 5, eg, int64_t(tid / Q) * ld + eg, up);
+    };
+    if constexpr (!EULER) first_update();
+    GatherWalk<T> walk(a.A, (EULER ? 2 : 1) * min(w / NH, a.A.nmg - 1), lane);
     if constexpr (EULER) {
-        if (!a.padj)
-            for (int base = w * 64; base < NG * VPR; base += NW * 64) {
-                const int c = base + lane;
-                if (c < NG * VPR)
-                    load_lds16(a.geom + int64_t(c / VPR) * ld + e0 + (16 / sizeof(T)) * (c % VPR),
-                               Gs + size_t(base) * (16 / sizeof(T)));
-            }
-        for (int idx = tid; idx < 3 * nu; idx += 64 * NW) Xs[idx] = a.xi[idx];
-        __builtin_amdgcn_s_waitcnt(0);
+        // 1. Ft = adj F(U) -> LDS
+        __builtin_amdgcn_s_waitcnt(0);                   // this wavefront's direct loads are in LDS
         __syncthreads();
-        for (int it = tid; it < nu * NE; it += 64 * NW) {
-            const int i = it / NE, e = it - i * NE;
-            const int64_t eg = e0 + e;
-            if (eg >= a.nelem) continue;                 // padding columns mix with no other
-            T u[5], adj[3][3], Ft[3][5];
 #pragma unroll
-            for (int v = 0; v < 5; ++v) u[v] = a.U[(int64_t(i) * 5 + v) * ld + eg];
-            if (a.padj) {
+        for (int m = 0; m < FR; ++m) {
+            const int c = tid + m * 64 * NW;
+            int dst;
+            if (c < nf * 5 * VPR) fr[m] = *reinterpret_cast<const floatx4 *>(piece(c, dst));
+        }
+        for (int base = 0; base < nu * NE; base += PT * 64 * NW) {
+            if (base > 0) load_points(base);
+#pragma unroll
+            for (int q = 0; q < PT; ++q) {
+                const int it = base + q * 64 * NW + tid, i = it / NE, e = it - i * NE;
+                const int64_t eg = e0 + e;
+                if (it >= nu * NE || eg >= a.nelem) continue;   // padding columns mix with no other
+                T adj[3][3], Ft[3][5];
+                if (a.padj) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) adj[k][j] = a.padj[(int64_t(3 * k + j) * nu + i) * ld + eg];
+                } else {
+                    metric<T, ET>(Gs, NE, e, Xs + 3 * i, adj);
+                }
+                upts_flux<T, false>(u[q], nullptr, adj, a.gamma, T(0), T(1), a.pref, Ft);
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) adj[k][j] = a.padj[(int64_t(3 * k + j) * nu + i) * ld + eg];
-            } else {
-                metric<T, ET>(Gs, NE, e, Xs + 3 * i, adj);
+                    for (int v = 0; v < 5; ++v) Bs[(k * nu + i) * WS + v * NE + e] = Ft[k][v];
             }
-            upts_flux<T, false>(u, nullptr, adj, a.gamma, T(0), T(1), a.pref, Ft);
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-#pragma unroll
-                for (int v = 0; v < 5; ++v) Bs[(k * nu + i) * WS + v * NE + e] = Ft[k][v];
         }
     } else {
-        __builtin_amdgcn_s_waitcnt(0);                   // this wavefront's direct loads are in LDS
+        __builtin_amdgcn_s_waitcnt(0);
     }
     __syncthreads();
 
-    // 2. Rt: wavefront w takes items w, w + NW, ...
+    // 2. Rt: wavefront w takes items w, w + NW, ... (Euler: first G' Ft, then
+    // L Fn on the same accumulators)
+    auto product = [&](int part) {
 #pragma unroll
-    for (int m = 0; m < MI; ++m) {
-        const int it = w + m * NW, g = it / NH, h = it - NH * g;
-        if (g < a.A.nmg) {
-            if (m > 0) walk = GatherWalk<T>(a.A, g, lane);
-            gather_products<NH>(walk, Bs + 16 * h + c16, WS, acc[m]);
+        for (int m = 0; m < MI; ++m) {
+            const int it = w + m * NW, g = it / NH, h = it - NH * g;
+            if (g < a.A.nmg) {
+                if (m > 0 || part > 0) walk = GatherWalk<T>(a.A, (EULER ? 2 : 1) * g + part, lane);
+                gather_products<NH>(walk, Bs + 16 * h + c16, WS, acc[m]);
+            }
         }
+    };
+    product(0);
+    if constexpr (EULER) {
+        __syncthreads();                                 // every wavefront is done with Ft
+#pragma unroll
+        for (int m = 0; m < FR; ++m) {
+            const int c = tid + m * 64 * NW;
+            int dst;
+            piece(c, dst);
+            if (c < nf * 5 * VPR) *reinterpret_cast<floatx4 *>(Bs + dst) = fr[m];
+        }
+        for (int c = tid + FR * 64 * NW; c < nf * 5 * VPR; c += 64 * NW) {
+            int dst;
+            const T *src = piece(c, dst);
+            *reinterpret_cast<floatx4 *>(Bs + dst) = *reinterpret_cast<const floatx4 *>(src);
+        }
+        first_update();
+        __syncthreads();
+        product(1);
     }
     __syncthreads();                                     // every wavefront is done with B
 #pragma unroll
     for (int m = 0; m < MI; ++m) {
-        const int it = w + m * NW, h = it % NH;
+        const int h = (w + m * NW) % NH;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (rrow[m][r] >= 0) {
@@ -151,54 +240,56 @@ __global__ __launch_bounds__(64 * NW) void divtile_kernel(DivTileArgs<T> a) {
     __syncthreads();
 
     // 3. the last pipeline step, four elements of one (point, field) at a time
-    auto update = [&](int idx, const UpdateIn<T, v4> &x) {
+    for (int idx = tid; idx < nu * 5 * Q; idx += 64 * NW) {
         const int q = idx % Q, iv = idx / Q, v = iv % 5, i = iv / 5;
         v4 *p = reinterpret_cast<v4 *>(Bs + i * WS + v * NE + 4 * q);
         const int64_t eg = e0 + 4 * q, o0 = int64_t(iv) * ld + eg;
-        const v4 r = update4_whole(a.ep, eg) ? update4(a.ep, eg, o0, *p, x) : update4_tail(a.ep, i, v, eg, o0, *p);
+        v4 r;
+        if (update4_whole(a.ep, eg)) {
+            if (idx != tid) update4_load(a.ep, i, eg, o0, up);
+            r = update4(a.ep, eg, o0, *p, up);
+        } else {
+            r = update4_tail(a.ep, i, v, eg, o0, *p);
+        }
         if (a.Uf) *p = r;
-    };
-#pragma unroll
-    for (int m = 0; m < PU; ++m) {
-        const int idx = tid + m * 64 * NW;
-        if (idx < nu * 5 * Q) update(idx, up[m]);
-    }
-    for (int idx = tid + PU * 64 * NW; idx < nu * 5 * Q; idx += 64 * NW) {
-        const int64_t eg = e0 + 4 * (idx % Q);
-        UpdateIn<T, v4> x;
-        if (update4_whole(a.ep, eg)) update4_load(a.ep, idx / Q / 5, eg, int64_t(idx / Q) * ld + eg, x);
-        update(idx, x);
     }
     if (!a.Uf) return;
     __syncthreads();
 
-    // 4. U_f = M0 r: items (row block, column half)
-    for (int it = w; it < a.M.nmg * NH; it += NW) {
-        const int g = it / NH, h = it - NH * g;
-        v4 af[NBI];
-#pragma unroll
-        for (int i = 0; i < NBI; ++i) af[i] = v4{0, 0, 0, 0};
-        if (it != w) {
-            block_rows(a.M, g, krow, frow);
-            walk = GatherWalk<T>(a.M, g, lane);
-        }
-        gather_products<NH>(walk, Bs + 16 * h + c16, WS, af);
-        const int64_t eg = e0 + 16 * h + c16;
-        if (eg >= a.nelem) continue;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (frow[r] < 0) continue;
-            T *u = a.Uf + int64_t(frow[r]) * 5 * ld + eg;
-#pragma unroll
-            for (int i = 0; i < NBI; ++i) u[i * ld] = af[i][r];
-        }
-    }
+    // 4. U_f = M0 r
+    interp_items<T, NE, NBI, NW>(a.M, Bs, a.Uf, ld, e0, a.nelem, w, lane, walk, frow);
+}
+
+// U_f = M0 U of a tile: the interpolation of a right-hand side's or a step's
+// first stage.
+template <typename T, int NE, int NBI, int NW>
+__global__ __launch_bounds__(64 * NW) void interptile_kernel(Op<T> M, const T *U, T *Uf, int64_t ld, int64_t nelem,
+                                                             int nu) {
+    constexpr int NH = TileShape<NE>::NB / NBI;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    T *Bs = reinterpret_cast<T *>(lds_raw);              // [nu][tile_stride]
+    const int64_t e0 = int64_t(xcd_block()) * NE;
+    if (e0 >= nelem) return;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    tile_to_lds<T, NE, NW>(U, ld, e0, nu, Bs, w, lane);
+    int frow[4];
+    block_rows(M, w / NH, lane >> 4, frow);
+    GatherWalk<T> walk(M, min(w / NH, M.nmg - 1), lane);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    interp_items<T, NE, NBI, NW>(M, Bs, Uf, ld, e0, nelem, w, lane, walk, frow);
+}
+
+template <typename T>
+size_t tile_bytes(int rows, int ne) {
+    return size_t(rows) * (ne == 32 ? 176 : 5 * ne) * sizeof(T);
 }
 
 template <typename T>
 size_t divtile_bytes(int etype, const DivTileArgs<T> &a, bool euler, int ne) {
-    const int ws = ne == 32 ? 176 : 5 * ne, ng = etype == 0 ? 9 : etype == 1 ? 15 : 21;
-    return (size_t(std::max((euler ? 3 * a.nu : 0) + a.nf, a.nu)) * ws + (euler ? size_t(ng) * ne + 3 * size_t(a.nu) : 0)) * sizeof(T);
+    const int ng = etype == 0 ? 9 : etype == 1 ? 15 : 21;
+    return tile_bytes<T>(euler ? std::max(3 * a.nu, a.nf) : std::max(a.nf, a.nu), ne) +
+           (euler ? size_t(ng) * ne + 3 * size_t(a.nu) : 0) * sizeof(T);
 }
 
 // Elements per workgroup (0: the shape does not fit).  Rows of 32 elements
@@ -210,39 +301,66 @@ int divtile_elems(int etype, const DivTileArgs<T> &a, bool euler) {
     return divtile_bytes(etype, a, euler, 16) <= TILE_LDS_MAX ? 16 : 0;
 }
 
-template <typename T, int ET, int NE, int NW, int MI, bool EULER>
+// Small meshes, at most one tile of 16 elements per CU: no second workgroup
+// fills a CU's waits, so the tile's own chain of steps is what counts, and
+// sixteen wavefronts with one column block each shorten it (384 elements,
+// order 2: 54.1 -> 52.6 us for a Navier-Stokes right-hand side; 1,296 tets, FP64, order 2:
+// 51.5 -> 47.8 us for an RK4 step).  With two to four tiles per CU the wider work items win
+// (FP64, order 4: 312 against 323 and 332 us; order 3, FP32: 76 against 92).
+constexpr int64_t NARROW_TILES = 256;
+inline bool narrow(int64_t nelem) { return (nelem + 15) / 16 <= NARROW_TILES; }
+
+template <typename K>
+hipError_t allow_lds(K *kernel, bool &set) {
+    if (set) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
+    set = e == hipSuccess;
+    return e;
+}
+
+template <typename T, int ET, int NE, int NBI, int NW, int MI, bool EULER>
 hipError_t launch_dt(const DivTileArgs<T> &a, hipStream_t s) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(divtile_kernel<T, ET, NE, NW, MI, EULER>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    divtile_kernel<T, ET, NE, NW, MI, EULER>
-        <<<xcd_grid((a.nelem + NE - 1) / NE), 64 * NW, divtile_bytes(ET, a, EULER, NE), s>>>(a);
+    static bool set = false;
+    const auto kernel = divtile_kernel<T, ET, NE, NBI, NW, MI, EULER>;
+    if (hipError_t e = allow_lds(kernel, set); e != hipSuccess) return e;
+    kernel<<<xcd_grid((a.nelem + NE - 1) / NE), 64 * NW, divtile_bytes(ET, a, EULER, NE), s>>>(a);
     return hipGetLastError();
 }
 
-// wavefronts per workgroup: four where the divergence product has at most
-// four items (row block, column half), else eight, with up to two items each
-template <typename T, int ET, int NE, bool EULER>
-hipError_t launch_dt_nw(const DivTileArgs<T> &a, hipStream_t s) {
-    const int items = a.A.nmg * (5 * NE / 80);
-    if (items <= 4) return launch_dt<T, ET, NE, 4, 1, EULER>(a, s);
-    if (items <= 8) return launch_dt<T, ET, NE, 8, 1, EULER>(a, s);
-    if (items <= 16) return launch_dt<T, ET, NE, 8, 2, EULER>(a, s);
+template <typename T, int ET, bool EULER>
+hipError_t launch_dt_et(const DivTileArgs<T> &a, hipStream_t s) {
+    const int nmg = a.A.nmg;
+    if (narrow(a.nelem) && nmg * 5 <= 48) {
+        // one column block per item over 16 wavefronts
+        if (nmg * 5 <= 16) return launch_dt<T, ET, 16, 1, 16, 1, EULER>(a, s);
+        return launch_dt<T, ET, 16, 1, 16, 3, EULER>(a, s);
+    }
+    // four wavefronts where the divergence product has at most four items
+    // (row block, five column blocks), else eight with up to two items each
+    const int ne = divtile_elems<T>(ET, a, EULER);
+    if constexpr (sizeof(T) == 4) {
+        if (ne == 32) {
+            if (nmg * 2 <= 4) return launch_dt<T, ET, 32, 5, 4, 1, EULER>(a, s);
+            if (nmg * 2 <= 8) return launch_dt<T, ET, 32, 5, 8, 1, EULER>(a, s);
+            if (nmg * 2 <= 16) return launch_dt<T, ET, 32, 5, 8, 2, EULER>(a, s);
+        }
+    }
+    if (ne == 16) {
+        if (nmg <= 4) return launch_dt<T, ET, 16, 5, 4, 1, EULER>(a, s);
+        if (nmg <= 8) return launch_dt<T, ET, 16, 5, 8, 1, EULER>(a, s);
+        if (nmg <= 16) return launch_dt<T, ET, 16, 5, 8, 2, EULER>(a, s);
+    }
     return hipErrorInvalidValue;
 }
 
-template <typename T, int ET>
-hipError_t launch_dt_et(bool euler, const DivTileArgs<T> &a, hipStream_t s) {
-    const int ne = divtile_elems<T>(ET, a, euler);
-    if constexpr (sizeof(T) == 4) {
-        if (ne == 32) return euler ? launch_dt_nw<T, ET, 32, true>(a, s) : launch_dt_nw<T, ET, 32, false>(a, s);
-    }
-    if (ne == 16) return euler ? launch_dt_nw<T, ET, 16, true>(a, s) : launch_dt_nw<T, ET, 16, false>(a, s);
-    return hipErrorInvalidValue;
+template <typename T, int NE, int NBI, int NW>
+hipError_t launch_it(const Op<T> &M, const T *U, T *Uf, int64_t ld, int64_t nelem, int nu, hipStream_t s) {
+    static bool set = false;
+    const auto kernel = interptile_kernel<T, NE, NBI, NW>;
+    if (hipError_t e = allow_lds(kernel, set); e != hipSuccess) return e;
+    kernel<<<xcd_grid((nelem + NE - 1) / NE), 64 * NW, tile_bytes<T>(nu, NE), s>>>(M, U, Uf, ld, nelem, nu);
+    return hipGetLastError();
 }
 
 bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
@@ -256,18 +374,40 @@ bool divtile_supported(int etype, const DivTileArgs<T> &a, bool euler) {
 
 template <typename T>
 hipError_t launch_divtile(int etype, bool euler, const DivTileArgs<T> &a, hipStream_t s) {
-    if (!gathered(a.A, a.nu) || !gathered(a.M, a.nf) || a.ld % 64 || a.nelem > a.ld || a.ep.ld != a.ld || a.ep.nelem != a.nelem ||
-        a.ep.nu != a.nu || !a.ep.jinv || !a.Fn || (euler ? !a.U : !a.D) || !aligned16(a.Fn) || !aligned16(a.geom))
+    if (!gathered(a.A, a.nu) || a.A.parts != (euler ? 2 : 1) || !gathered(a.M, a.nf) || a.M.parts != 1 ||
+        a.ld % 64 || a.nelem > a.ld || a.ep.ld != a.ld || a.ep.nelem != a.nelem || a.ep.nu != a.nu || !a.ep.jinv ||
+        !a.Fn || (euler ? !a.U : !a.D) || !aligned16(a.Fn) || !aligned16(a.geom))
         return hipErrorInvalidValue;
     if (!a.nelem) return hipSuccess;
-    if (etype == 0) return launch_dt_et<T, 0>(euler, a, s);
-    if (etype == 1) return launch_dt_et<T, 1>(euler, a, s);
-    return launch_dt_et<T, 2>(euler, a, s);
+    if (etype == 0) return euler ? launch_dt_et<T, 0, true>(a, s) : launch_dt_et<T, 0, false>(a, s);
+    if (etype == 1) return euler ? launch_dt_et<T, 1, true>(a, s) : launch_dt_et<T, 1, false>(a, s);
+    return euler ? launch_dt_et<T, 2, true>(a, s) : launch_dt_et<T, 2, false>(a, s);
+}
+
+template <typename T>
+hipError_t launch_interptile(const Op<T> &M, const T *U, T *Uf, int64_t ld, int64_t nelem, int nu, hipStream_t s) {
+    if (M.stage != 7 || M.parts != 1 || !gathered(M, M.M) || ld % 64 || nelem > ld || !U || !Uf || !aligned16(U))
+        return hipErrorInvalidValue;
+    if (!nelem) return hipSuccess;
+    if (narrow(nelem)) return launch_it<T, 16, 1, 16>(M, U, Uf, ld, nelem, nu, s);
+    if constexpr (sizeof(T) == 4) {
+        if (tile_bytes<T>(nu, 32) <= TILE_LDS_MAX / 2) {
+            if (M.nmg <= 2) return launch_it<T, 32, 5, 4>(M, U, Uf, ld, nelem, nu, s);
+            return launch_it<T, 32, 5, 8>(M, U, Uf, ld, nelem, nu, s);
+        }
+    }
+    if (tile_bytes<T>(nu, 16) > TILE_LDS_MAX) return hipErrorInvalidValue;
+    if (M.nmg <= 4) return launch_it<T, 16, 5, 4>(M, U, Uf, ld, nelem, nu, s);
+    return launch_it<T, 16, 5, 8>(M, U, Uf, ld, nelem, nu, s);
 }
 
 template bool divtile_supported<float>(int, const DivTileArgs<float> &, bool);
 template bool divtile_supported<double>(int, const DivTileArgs<double> &, bool);
 template hipError_t launch_divtile<float>(int, bool, const DivTileArgs<float> &, hipStream_t);
 template hipError_t launch_divtile<double>(int, bool, const DivTileArgs<double> &, hipStream_t);
+template hipError_t launch_interptile<float>(const Op<float> &, const float *, float *, int64_t, int64_t, int,
+                                             hipStream_t);
+template hipError_t launch_interptile<double>(const Op<double> &, const double *, double *, int64_t, int64_t, int,
+                                              hipStream_t);
 
 }  // namespace frd

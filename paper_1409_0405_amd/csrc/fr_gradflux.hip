@@ -64,19 +64,6 @@ __device__ __forceinline__ void interp3_products(GatherWalk<T, AD> &w, const T *
 template <typename T, int ET>
 constexpr int tile_elems() { return (ET == 2 ? 16 : 32) * 4 / int(sizeof(T)); }
 
-// Column block n of a tile, lane c16, is field v of element e: with at least
-// 16 elements, block NH i + h is field i of elements 16 h .. 16 h + 15.
-template <int NE>
-struct TileColumn {
-    int v, e;
-    __device__ __forceinline__ TileColumn(int n, int c16) {
-        constexpr int NH = NE >= 16 ? NE / 16 : 1;
-        const int flat = 16 * n + c16;
-        v = NE >= 16 ? n / NH : flat / NE;
-        e = NE >= 16 ? 16 * (n % NH) + c16 : flat - v * NE;
-    }
-};
-
 // One workgroup of NW wavefronts per tile.  MG: row blocks of the gradient
 // operator per wavefront (>= nmg / NW); their accumulators stay in registers
 // until every wavefront has finished reading B, so that Qt takes B's place in

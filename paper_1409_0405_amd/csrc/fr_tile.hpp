@@ -51,7 +51,7 @@ struct GatherStep {
     int row;
 };
 
-// Walk of a gathered operator over one row block.  The first AD steps are
+// Walk of a gathered operator over one row block (with two parts: list 2 g + part).  The first AD steps are
 // loaded when the walk is made (before a barrier or a wait that comes
 // anyway), later ones AD steps ahead of their use; the B values (LDS) one
 // step ahead.  The loop has no exit between its steps, so the compiler counts
@@ -139,7 +139,7 @@ __device__ __forceinline__ void block_rows(const Op<T> &A, int g, int krow, int 
 // Whether op is a gathered operator of M rows.
 template <typename T>
 bool gathered(const Op<T> &op, int M) {
-    return op.stage == 7 && op.mbw == 1 && op.M == M && op.nmg > 0 && op.frag && op.koff && op.rowmap;
+    return op.stage == 7 && op.mbw == 1 && op.M == M && op.nmg > 0 && op.parts > 0 && op.frag && op.koff && op.rowmap;
 }
 
 // Tile of NE elements with all five fields: row r of a tile in LDS holds W5
@@ -149,6 +149,19 @@ template <int NE>
 struct TileShape {
     static constexpr int W5 = (5 * NE + 15) / 16 * 16;
     static constexpr int NB = W5 / 16;
+};
+
+// Column block n of a tile, lane c16, is field v of element e: with at least
+// 16 elements, block NH i + h is field i of elements 16 h .. 16 h + 15.
+template <int NE>
+struct TileColumn {
+    int v, e;
+    __device__ __forceinline__ TileColumn(int n, int c16) {
+        constexpr int NH = NE >= 16 ? NE / 16 : 1;
+        const int flat = 16 * n + c16;
+        v = NE >= 16 ? n / NH : flat / NE;
+        e = NE >= 16 ? 16 * (n % NH) + c16 : flat - v * NE;
+    }
 };
 
 // Row stride of a tile in LDS.  A matrix instruction reads B at four

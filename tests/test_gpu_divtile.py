@@ -3,8 +3,8 @@ equations, divergence product, register update, interpolation of the next
 stage's input) against the separate kernels (FR_SEPARATE_UPDATE): the same
 arithmetic on the same values in the same order, so every result has the same
 bits (raw bits, a zero's sign included).  Orders 1 to 4, every element type,
-element counts below and ragged against the tiles (32 and 16 elements),
-straight and curved elements, walls, FP32 and FP64, several steps of every
+element counts below and ragged against the tiles (32 and 16 elements) and on
+both sides of the small-mesh launches (256 tiles of 16), straight and curved elements, walls, FP32 and FP64, several steps of every
 scheme (between which the stage fills the flux-point states), and the learned
 closure."""
 import math
@@ -30,6 +30,10 @@ def _arrays(kind):
         return inputs.hybrid_box(6, 4, 6, 3, 3, L3, jitter=0.1, seed=5)
     if kind == "curvedwall":
         return inputs.curve(inputs.hybrid_box(6, 4, 6, 3, 3, L3, jitter=0.1, seed=5, y_bc="wall"), 0.03)
+    if kind == "wide":           # 4,800 prisms and 4,800 tets
+        return inputs.small_mixed_box(nxy=20, n_pri_layers=6, n_tet_layers=2, jitter=0.1, seed=5)
+    if kind == "widehex":        # 4,913 hexahedra
+        return inputs.hex_box(17, jitter=0.1, seed=5)
     return inputs.small_mixed_box(nxy=5, n_pri_layers=3, n_tet_layers=3, jitter=0.1, seed=5)   # 150 prisms, 450 tets
 
 
@@ -48,9 +52,11 @@ def _results(arrays, p, system, prec, separate, closure=False):
     ts = [NAMES.index(n) for n in O.types]
     M = frlib.Mesh(arrays, p, system=system, precision=prec, mu=0.02, separate_update=separate, t_wall=P0, p_ref=P0)
     net, out = None, []
-    if system == "ns":
-        for t in ts:
+    for t in ts:
+        if system == "ns":
             M.set_gradient_form(t, 1)
+        if separate:             # the interpolation as a product of its own
+            M.set_blocking(t, 0, 2, 0)
     if closure:
         rng = np.random.default_rng(3)
         net = frlib.MLP(1)
@@ -89,6 +95,9 @@ CASES += [("hybrid", p, s, "fp32") for p in (1, 2, 3, 4) for s in ("euler", "ns"
 CASES += [("hybrid", 4, "ns", "fp64"), ("hybrid", 3, "euler", "fp64"), ("tiny", 2, "euler", "fp32"),
           ("tiny", 4, "ns", "fp32"), ("curvedwall", 3, "euler", "fp32"), ("curvedwall", 3, "ns", "fp32"),
           ("curvedwall", 2, "euler", "fp64")]
+CASES += [(k, p, s, q) for k in ("wide", "widehex")
+          for p, s, q in ((1, "ns", "fp32"), (2, "euler", "fp64"), (2, "ns", "fp32"), (3, "euler", "fp32"),
+                          (3, "ns", "fp64"), (4, "euler", "fp32"), (4, "ns", "fp32"))]
 
 
 @pytest.mark.parametrize("kind,p,system,prec", CASES, ids=[f"{k}-p{p}-{s}-{q}" for k, p, s, q in CASES])
