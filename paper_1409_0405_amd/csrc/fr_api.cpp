@@ -632,11 +632,14 @@ fr_status setup_device(fr_mesh m, hipStream_t s) {
             FR_HIP(m, upload_op(D.Fgrad, f, idx, d.allocs));
             D.Tvol = fragment_gathered<T>(columns(div, nu, 3 * nu + nf, 0, 3 * nu), nu, 3 * nu, f, idx);
             FR_HIP(m, upload_op(D.Tvol, f, idx, d.allocs));
-            // before autotuning: the fused stage where its gradient product
-            // has work for at least half of the workgroup's wavefronts
-            // (measured on the mixed Taylor-Green mesh: it loses for tets at
-            // p <= 2 and prisms at p = 1, wins above)
-            D.grad_form = D.Fgrad.nmg >= 4 ? 1 : 0;
+            // before autotuning: the fused stage.  A right-hand side with it
+            // and the divergence stage on tiles against the separate kernels,
+            // mixed Taylor-Green meshes, FP32: order 1, 384 elements 42
+            // against 54 us, 129,600 elements 140 against 182 us; order 2, 53
+            // against 77 and 300 against 410 us; FP64, order 1, 320 against
+            // 340 us.  Without the divergence stage on tiles it loses where
+            // the gradient operator has fewer than four row blocks.
+            D.grad_form = (D.tile && !(m->flags & FR_SEPARATE_UPDATE)) || D.Fgrad.nmg >= 4 ? 1 : 0;
         }
         if (m->precision == FR_SPLIT_BF16 || m->precision == FR_SPLIT_FP16) {
             const int fmt = m->precision == FR_SPLIT_FP16 ? 2 : 1;

@@ -301,15 +301,6 @@ int divtile_elems(int etype, const DivTileArgs<T> &a, bool euler) {
     return divtile_bytes(etype, a, euler, 16) <= TILE_LDS_MAX ? 16 : 0;
 }
 
-// Small meshes, at most one tile of 16 elements per CU: no second workgroup
-// fills a CU's waits, so the tile's own chain of steps is what counts, and
-// sixteen wavefronts with one column block each shorten it (384 elements,
-// order 2: 54.1 -> 52.6 us for a Navier-Stokes right-hand side; 1,296 tets, FP64, order 2:
-// 51.5 -> 47.8 us for an RK4 step).  With two to four tiles per CU the wider work items win
-// (FP64, order 4: 312 against 323 and 332 us; order 3, FP32: 76 against 92).
-constexpr int64_t NARROW_TILES = 256;
-inline bool narrow(int64_t nelem) { return (nelem + 15) / 16 <= NARROW_TILES; }
-
 template <typename K>
 hipError_t allow_lds(K *kernel, bool &set) {
     if (set) return hipSuccess;
@@ -331,7 +322,7 @@ hipError_t launch_dt(const DivTileArgs<T> &a, hipStream_t s) {
 template <typename T, int ET, bool EULER>
 hipError_t launch_dt_et(const DivTileArgs<T> &a, hipStream_t s) {
     const int nmg = a.A.nmg;
-    if (narrow(a.nelem) && nmg * 5 <= 48) {
+    if (narrow_mesh(a.nelem) && nmg * 5 <= 48) {
         // one column block per item over 16 wavefronts
         if (nmg * 5 <= 16) return launch_dt<T, ET, 16, 1, 16, 1, EULER>(a, s);
         return launch_dt<T, ET, 16, 1, 16, 3, EULER>(a, s);
@@ -389,7 +380,7 @@ hipError_t launch_interptile(const Op<T> &M, const T *U, T *Uf, int64_t ld, int6
     if (M.stage != 7 || M.parts != 1 || !gathered(M, M.M) || ld % 64 || nelem > ld || !U || !Uf || !aligned16(U))
         return hipErrorInvalidValue;
     if (!nelem) return hipSuccess;
-    if (narrow(nelem)) return launch_it<T, 16, 1, 16>(M, U, Uf, ld, nelem, nu, s);
+    if (narrow_mesh(nelem)) return launch_it<T, 16, 1, 16>(M, U, Uf, ld, nelem, nu, s);
     if constexpr (sizeof(T) == 4) {
         if (tile_bytes<T>(nu, 32) <= TILE_LDS_MAX / 2) {
             if (M.nmg <= 2) return launch_it<T, 32, 5, 4>(M, U, Uf, ld, nelem, nu, s);

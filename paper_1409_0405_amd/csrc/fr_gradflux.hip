@@ -74,7 +74,7 @@ constexpr int tile_elems() { return (ET == 2 ? 16 : 32) * 4 / int(sizeof(T)); }
 // What bounds it (p = 4, 307,200-element box): the matrix cores and the waits
 // between the phases; the interpolation's and phase 6's first operator steps
 // and row numbers are loaded one phase ahead (tets 595 -> 571 us).
-template <typename T, int ET, int NE, int NW, int MG, bool VD>
+template <typename T, int ET, int NE, int GH, int NBI, int NW, int MG, bool VD>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(GradFluxArgs<T> a) {
     using v4 = typename Vec4<T>::type;
     constexpr int W5 = TileShape<NE>::W5, NB = TileShape<NE>::NB, WS = tile_stride<NE>();
@@ -111,22 +111,24 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(Grad
         for (int idx = tid; idx < (nu + nf) * (W5 - 5 * NE); idx += 64 * NW)
             Bs[(idx / (W5 - 5 * NE)) * WS + 5 * NE + idx % (W5 - 5 * NE)] = T(0);
 
-    // 2. Qt = [G_k | L_k] B: wavefront w takes row blocks w, w + NW, ..., each
-    // against every column block
-    v4 acc[MG][NB];
+    // 2. Qt = [G_k | L_k] B: wavefront w takes items w, w + NW, ... (row block,
+    // every GH-th column block)
+    constexpr int NBG = NB / GH;
+    static_assert(NB % GH == 0 && NB % NBI == 0, "whole column blocks");
+    v4 acc[MG][NBG];
     int qrow[MG][4];
 #pragma unroll
-    for (int m = 0; m < MG; ++m) block_rows(a.G, w + m * NW, krow, qrow[m]);
+    for (int m = 0; m < MG; ++m) block_rows(a.G, (w + m * NW) / GH, krow, qrow[m]);
     __builtin_amdgcn_s_waitcnt(0);                       // this wavefront's direct loads are in LDS
     __syncthreads();
 #pragma unroll
     for (int m = 0; m < MG; ++m) {
 #pragma unroll
-        for (int n = 0; n < NB; ++n) acc[m][n] = v4{0, 0, 0, 0};
-        const int g = w + m * NW;
+        for (int n = 0; n < NBG; ++n) acc[m][n] = v4{0, 0, 0, 0};
+        const int g = (w + m * NW) / GH, h = (w + m * NW) % GH;
         if (g < a.G.nmg) {
             GatherWalk<T> gwalk(a.G, g, lane);
-            gather_products(gwalk, Bs + c16, WS, acc[m]);
+            gather_products<GH>(gwalk, Bs + 16 * h + c16, WS, acc[m]);
         }
     }
     // the states of this thread's first PI points of the point-wise phase,
@@ -153,7 +155,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(Grad
             const int row = qrow[m][r];
             if (row >= 0) {
 #pragma unroll
-                for (int n = 0; n < NB; ++n) QT[row * WS + 16 * n + c16] = acc[m][n][r];
+                for (int n = 0; n < NBG; ++n)
+                    QT[row * WS + 16 * (GH * n + (w + m * NW) % GH) + c16] = acc[m][n][r];
             }
         }
     }
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(Grad
     // blocks) with the three directions together, so an operator fragment
     // feeds 3 NBI matrix instructions; the first item's operator steps, flux
     // points and faces are on their way during the point-wise phase
-    constexpr int NBI = NB % 5 == 0 ? 5 : NB, NH = NB / NBI;
+    constexpr int NH = NB / NBI;
     const int nit = a.M.nmg * NH;
     int frow[4];
     unsigned fb[4];
@@ -283,7 +286,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(Grad
         for (int r = 0; r < 4; ++r) {
             if (frow[r] < 0) continue;
             T *qf = a.Qf + int64_t(frow[r]) * 15 * ld + e0;
-            if constexpr (NE >= 16) {
+            if constexpr (NE >= 16 && NBI == 5) {
                 const TileColumn<NE> c(h, c16);
                 if (!(qm[h] & fb[r])) continue;
 #pragma unroll
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(Grad
 #pragma unroll
                 for (int i = 0; i < NBI; ++i) {
                     const TileColumn<NE> c(NH * i + h, c16);
-                    if (c.v >= 5 || !(qm[0] & fb[r])) continue;
+                    if (c.v >= 5 || !(qm[(NH * i + h) % NQ] & fb[r])) continue;
 #pragma unroll
                     for (int j = 0; j < 3; ++j) qf[(j * 5 + c.v) * ld + c.e] = acc3[j][i][r];
                 }
@@ -496,34 +499,77 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ET == 0
 }
 
 
-template <typename T, int ET, int NE, int NW, int MG, bool VD>
-hipError_t launch_gf_mg(const GradFluxArgs<T> &a, size_t lds, hipStream_t s) {
+template <typename T, int ET, int NE>
+size_t gradflux_bytes(const GradFluxArgs<T> &a) {
+    return (size_t(std::max(a.nu + a.nf, 3 * a.nu)) * tile_stride<NE>() + size_t(n_geom_coeffs<ET>()) * NE +
+            size_t(3 * a.nu)) * sizeof(T);
+}
+
+template <typename T, int ET, int NE, int GH, int NBI, int NW, int MG, bool VD>
+hipError_t launch_gf_mg(const GradFluxArgs<T> &a, hipStream_t s) {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_kernel<T, ET, NE, NW, MG, VD>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_kernel<T, ET, NE, GH, NBI, NW, MG, VD>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int64_t ntiles = (a.nelem + NE - 1) / NE;
-    gradflux_kernel<T, ET, NE, NW, MG, VD><<<xcd_grid(ntiles), 64 * NW, lds, s>>>(a);
+    gradflux_kernel<T, ET, NE, GH, NBI, NW, MG, VD>
+        <<<xcd_grid(ntiles), 64 * NW, gradflux_bytes<T, ET, NE>(a), s>>>(a);
     return hipGetLastError();
 }
 
-template <typename T, int ET, int NE, int NW, bool VD>
-hipError_t launch_gf_vd(const GradFluxArgs<T> &a, size_t lds, hipStream_t s) {
-    const int mg = (a.G.nmg + NW - 1) / NW;
-    if (mg <= 1) return launch_gf_mg<T, ET, NE, NW, 1, VD>(a, lds, s);
+template <typename T, int ET, bool VD>
+hipError_t launch_gf(const GradFluxArgs<T> &a, hipStream_t s) {
+    const int nmg = a.G.nmg;
+    constexpr int NE = tile_elems<T, ET>(), NB = TileShape<NE>::NB, NBI = NB % 5 == 0 ? 5 : NB;
+    // wavefronts per workgroup (row blocks of the gradient operator at p = 4:
+    // tets 7, prisms 15, hexahedra 25): FP32 8, 16 and 16; FP64, whose
+    // accumulators are twice as large, 4, 8 and 8
+    constexpr int NW = (ET == 0 ? 8 : 16) * 4 / int(sizeof(T));
+    // (next to the divergence stage on tiles only)
+    if constexpr (VD) {
+        if (narrow_mesh(a.nelem) && gradflux_bytes<T, ET, 16>(a) <= TILE_LDS_MAX) {
+            // one column block per item over 16 wavefronts (FP64: 8, whose
+            // point-wise work needs more than 128 registers)
+            constexpr int NN = sizeof(T) == 4 ? 16 : 8, F = 16 / NN;
+            if (nmg * 5 <= 16) return launch_gf_mg<T, ET, 16, 5, 1, NN, F, VD>(a, s);
+            if (nmg * 5 <= 48) return launch_gf_mg<T, ET, 16, 5, 1, NN, 3 * F, VD>(a, s);
+            if (nmg * 5 <= 80) return launch_gf_mg<T, ET, 16, 5, 1, NN, 5 * F, VD>(a, s);
+        }
+        // Low orders: the gradient operator has few row blocks, so they are also
+        // split by column blocks (FP32 in two, FP64 in five), and a workgroup has
+        // only as many wavefronts as that gives work to.  Times of this kernel
+        // before -> after: order 1, FP32, 82,944 tets 52 -> 34 us, 46,656 prisms
+        // 54 -> 29 us; order 2, 79 -> 62 and 85 -> 68 us; 13,824 hexahedra, order
+        // 1, 34 -> 16 us, order 2, 47 -> 30 us; FP64, order 1, prisms 103 -> 70
+        // us, hexahedra 48 -> 29 us, order 2, prisms 168 -> 146 us (but tets 84
+        // -> 88 us and 150 -> 169 us: FP64 tets stay with whole row blocks).
+        if constexpr (sizeof(T) == 4) {
+            if (ET < 2 || gradflux_bytes<T, ET, 32>(a) <= TILE_LDS_MAX / 2) {
+                if (nmg <= 2) return launch_gf_mg<T, ET, 32, 2, 5, 4, 1, VD>(a, s);
+                if (nmg <= 4) return launch_gf_mg<T, ET, 32, 2, 5, 8, 1, VD>(a, s);
+                if constexpr (ET == 2)
+                    if (nmg <= 8) return launch_gf_mg<T, ET, 32, 1, 5, 8, 1, VD>(a, s);
+            }
+        } else if (ET > 0 && gradflux_bytes<T, ET, 16>(a) <= TILE_LDS_MAX / 2) {
+            if (nmg <= 2) return launch_gf_mg<T, ET, 16, 5, 5, 4, 3, VD>(a, s);
+            if (nmg <= 4) return launch_gf_mg<T, ET, 16, 5, 5, 4, 5, VD>(a, s);
+        }
+    }
+    const int mg = (nmg + NW - 1) / NW;
+    if (mg <= 1) return launch_gf_mg<T, ET, NE, 1, NBI, NW, 1, VD>(a, s);
     if constexpr (sizeof(T) == 8 || ET == 2)
-        if (mg <= 2) return launch_gf_mg<T, ET, NE, NW, 2, VD>(a, lds, s);
+        if (mg <= 2) return launch_gf_mg<T, ET, NE, 1, NBI, NW, 2, VD>(a, s);
     if constexpr (sizeof(T) == 8 && ET == 2)
-        if (mg <= 4) return launch_gf_mg<T, ET, NE, NW, 4, VD>(a, lds, s);
+        if (mg <= 4) return launch_gf_mg<T, ET, NE, 1, NBI, NW, 4, VD>(a, s);
     return hipErrorInvalidValue;
 }
 
-template <typename T, int ET, int NE, int NW>
-hipError_t launch_gf(const GradFluxArgs<T> &a, size_t lds, hipStream_t s) {
-    return a.D ? launch_gf_vd<T, ET, NE, NW, true>(a, lds, s) : launch_gf_vd<T, ET, NE, NW, false>(a, lds, s);
+template <typename T, int ET>
+hipError_t launch_gf_et(const GradFluxArgs<T> &a, hipStream_t s) {
+    return a.D ? launch_gf<T, ET, true>(a, s) : launch_gf<T, ET, false>(a, s);
 }
 
 size_t gradflux_stream_lds_bytes(int etype, const GradFluxArgs<float> &a) {
@@ -559,11 +605,7 @@ hipError_t launch_gf_stream(const GradFluxArgs<float> &a, size_t lds, hipStream_
 namespace {
 template <typename T, int ET>
 size_t gradflux_lds_t(const GradFluxArgs<T> &a) {
-    constexpr int NE = tile_elems<T, ET>();
-    constexpr int W5 = tile_stride<NE>();
-    const size_t n = size_t(std::max(a.nu + a.nf, 3 * a.nu)) * W5 + size_t(n_geom_coeffs<ET>()) * NE +
-                     size_t(3 * a.nu);
-    const size_t bytes = n * sizeof(T);
+    const size_t bytes = gradflux_bytes<T, ET, tile_elems<T, ET>()>(a);
     return bytes <= TILE_LDS_MAX ? bytes : 0;
 }
 }  // namespace
@@ -596,12 +638,9 @@ hipError_t launch_gradflux(int etype, const GradFluxArgs<T> &a, hipStream_t s, b
     if constexpr (std::is_same<T, float>::value) {
         if (stream) return etype == 0 ? launch_gf_stream<0, 8>(a, lds, s) : launch_gf_stream<1, 8>(a, lds, s);
     }
-    // wavefronts per workgroup (row blocks of the gradient operator at p = 4:
-    // tets 7, prisms 15, hexahedra 25): FP32 8, 16 and 16; FP64, whose
-    // accumulators are twice as large, 4, 8 and 8
-    if (etype == 0) return launch_gf<T, 0, tile_elems<T, 0>(), sizeof(T) == 4 ? 8 : 4>(a, lds, s);
-    if (etype == 1) return launch_gf<T, 1, tile_elems<T, 1>(), sizeof(T) == 4 ? 16 : 8>(a, lds, s);
-    return launch_gf<T, 2, tile_elems<T, 2>(), sizeof(T) == 4 ? 16 : 8>(a, lds, s);
+    if (etype == 0) return launch_gf_et<T, 0>(a, s);
+    if (etype == 1) return launch_gf_et<T, 1>(a, s);
+    return launch_gf_et<T, 2>(a, s);
 }
 
 template size_t gradflux_lds<float>(int, const GradFluxArgs<float> &);

@@ -192,5 +192,14 @@ __device__ __forceinline__ void tile_to_lds(const T *src, int64_t ld, int64_t e0
 
 constexpr size_t TILE_LDS_MAX = 160 * 1024;   // LDS of a CU
 
+// Small meshes, at most one tile of 16 elements per CU: no second workgroup
+// fills a CU's waits, so the tile's own chain of steps is what counts, and
+// sixteen wavefronts with one column block each shorten it (384 elements,
+// order 2: 54.1 -> 52.6 us for a Navier-Stokes right-hand side; 1,296 tets, FP64, order 2:
+// 51.5 -> 47.8 us for an RK4 step).  With two to four tiles per CU the wider work items win
+// (FP64, order 4: 312 against 323 and 332 us; order 3, FP32: 76 against 92).
+constexpr int64_t NARROW_TILES = 256;
+inline bool narrow_mesh(int64_t nelem) { return (nelem + 15) / 16 <= NARROW_TILES; }
+
 }  // namespace
 }  // namespace frd
