@@ -922,14 +922,35 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     Dev<T> &d = dev_of<T>(m);
     const bool ns = m->system == FR_NAVIER_STOKES;
     const T gamma = T(m->gamma), mu = T(m->mu), pr = T(m->prandtl);
+    // Small meshes: one launch covers a stage's kernel of every type (with
+    // per-kernel timing on, one per type, so that each is timed by itself)
+    const bool merge = !m->prof.on;
+    {
+        frd::InterpTileArgs<T> ia[frh::NTYPE];
+        const frd::InterpTileArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
+        int first = -1;
+        for (int t = 0; t < frh::NTYPE; ++t) {
+            DevType<T> &D = d.t[t];
+            if (!D.nelem || (uf && uf[t]) || !D.Fgint.frag || !D.tile_interp) continue;
+            ia[t].M = D.Fgint;
+            ia[t].U = U[t];
+            ia[t].Uf = D.Uf;
+            ia[t].ld = D.ld;
+            ia[t].nelem = D.nelem;
+            ia[t].nu = D.nu;
+            if (merge && frd::interptile_small<T>(ia[t])) {
+                small[t] = &ia[t];
+                if (first < 0) first = t;
+            } else {
+                FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s, frd::launch_interptile<T>(ia[t], s));
+            }
+        }
+        if (first >= 0)
+            FR_LAUNCH(m, prof_op(first, frd::OP_INTERP), s, frd::launch_interptile_small<T>(small, s));
+    }
     for (int t = 0; t < frh::NTYPE; ++t) {
         DevType<T> &D = d.t[t];
-        if (!D.nelem || (uf && uf[t])) continue;
-        if (D.Fgint.frag && D.tile_interp) {
-            FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
-                      frd::launch_interptile<T>(D.Fgint, U[t], D.Uf, D.ld, D.nelem, D.nu, s));
-            continue;
-        }
+        if (!D.nelem || (uf && uf[t]) || (D.Fgint.frag && D.tile_interp)) continue;
         const int64_t w5 = 5 * D.ld;
         FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
                   opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U[t], w5, D.nu, nullptr, 0, 0, D.Uf, w5, w5, s));
@@ -985,19 +1006,28 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     if (ns) {
         FR_LAUNCH(m, 10, s, frd::launch_common_solution<T>(pa, s));
         if (d.nb) FR_LAUNCH(m, 22, s, frd::launch_boundary_solution<T>(ba, s));
+        frd::GradFluxArgs<T> ga[frh::NTYPE];
+        const frd::GradFluxArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
+        int first = -1;
         for (int t = 0; t < frh::NTYPE; ++t) {
             DevType<T> &D = d.t[t];
             if (!D.nelem) continue;
             if (fused[t]) {
-                frd::GradFluxArgs<T> ga = gradflux_args<T>(m, D, U[t]);
-                if (tile[t]) ga.D = D.Ft;
-                FR_LAUNCH(m, prof_gradflux(t), s, frd::launch_gradflux<T>(t, ga, s, D.grad_form == 2));
+                ga[t] = gradflux_args<T>(m, D, U[t]);
+                if (tile[t]) ga[t].D = D.Ft;
+                if (merge && frd::gradflux_small<T>(t, ga[t])) {
+                    small[t] = &ga[t];
+                    if (first < 0) first = t;
+                } else {
+                    FR_LAUNCH(m, prof_gradflux(t), s, frd::launch_gradflux<T>(t, ga[t], s, D.grad_form == 2));
+                }
                 continue;
             }
             const int64_t w5 = 5 * D.ld;
             FR_LAUNCH(m, prof_op(t, frd::OP_GRAD), s,
                       opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U[t], w5, D.nu, D.Cf, w5, D.nf, D.Qt, w5, w5, s));
         }
+        if (first >= 0) FR_LAUNCH(m, prof_gradflux(first), s, frd::launch_gradflux_small<T>(small, s));
     }
     for (int t = 0; t < frh::NTYPE; ++t) {
         DevType<T> &D = d.t[t];
@@ -1027,6 +1057,9 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
         FR_LAUNCH(m, 15, s, frd::launch_mlp_forward(cl->params, cl->params_bf16, cl->bf16, cl->feat, 1, ntot, ntot,
                                                     cl->stats, false, cl->y, 1, ntot, s));
     }
+    frd::DivTileArgs<T> ta[frh::NTYPE];
+    const frd::DivTileArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
+    int first = -1;
     for (int t = 0; t < frh::NTYPE; ++t) {
         DevType<T> &D = d.t[t];
         if (!D.nelem) continue;
@@ -1045,10 +1078,15 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
         }
         if (uf) uf[t] = tile[t] && D.tile_interp && next;
         if (tile[t]) {
-            frd::DivTileArgs<T> ta = divtile_args<T>(m, D, U[t]);
-            ta.ep = na;
-            if (uf && uf[t]) ta.Uf = D.Uf;
-            FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s, frd::launch_divtile<T>(t, !ns, ta, s));
+            ta[t] = divtile_args<T>(m, D, U[t]);
+            ta[t].ep = na;
+            if (uf && uf[t]) ta[t].Uf = D.Uf;
+            if (merge && frd::divtile_small<T>(ta[t])) {
+                small[t] = &ta[t];
+                if (first < 0) first = t;
+            } else {
+                FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s, frd::launch_divtile<T>(t, !ns, ta[t], s));
+            }
             continue;
         }
         // -R~/J and the register update ride in the divergence product's
@@ -1065,6 +1103,7 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
                   opmul<T>(m, 4 * t + frd::OP_DIV, D.Adiv, D.Sdiv, D.Ft, w5, 3 * D.nu, D.Fn, w5, D.nf, D.Rt, w5, w5, s));
         FR_LAUNCH(m, prof_neg(t), s, frd::launch_negdivconf<T>(t, na, s));
     }
+    if (first >= 0) FR_LAUNCH(m, prof_op(first, frd::OP_DIV), s, frd::launch_divtile_small<T>(!ns, small, s));
     return FR_OK;
 }
 

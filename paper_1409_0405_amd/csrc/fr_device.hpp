@@ -117,12 +117,12 @@ hipError_t launch_upts(int etype, bool ns, const UptsArgs<T> &a, hipStream_t s);
 // point-wise arithmetic).
 template <typename T>
 struct GradFluxArgs {
-    const T *U;          // [nu][5][ld]
-    const T *Cf;         // [nf][5][ld] jump to the common solution
-    T *Ft;               // [3 nu][5][ld] transformed flux, row k nu + i
-    T *Qf;               // [nf][15][ld] physical gradient at the flux points
-    const T *geom;       // [ng][ld] Jacobian coefficients (straight elements)
-    const T *xi;         // [nu][3]
+    const T *U = nullptr;      // [nu][5][ld]
+    const T *Cf = nullptr;     // [nf][5][ld] jump to the common solution
+    T *Ft = nullptr;           // [3 nu][5][ld] transformed flux, row k nu + i
+    T *Qf = nullptr;           // [nf][15][ld] physical gradient at the flux points
+    const T *geom = nullptr;   // [ng][ld] Jacobian coefficients (straight elements)
+    const T *xi = nullptr;     // [nu][3]
     const T *padj = nullptr, *pjinv = nullptr;   // curved: [9][nu][ld], [nu][ld]
     int64_t ld = 0, nelem = 0;
     int nu = 0, nf = 0;
@@ -248,7 +248,29 @@ template <typename T>
 hipError_t launch_divtile(int etype, bool euler, const DivTileArgs<T> &a, hipStream_t s);
 // Uf [nf][5][ld] = M0 U, U [nu][5][ld] (M0 gathered, stage 7).
 template <typename T>
-hipError_t launch_interptile(const Op<T> &M, const T *U, T *Uf, int64_t ld, int64_t nelem, int nu, hipStream_t s);
+struct InterpTileArgs {
+    Op<T> M;
+    const T *U = nullptr;
+    T *Uf = nullptr;
+    int64_t ld = 0, nelem = 0;
+    int nu = 0;
+};
+template <typename T>
+hipError_t launch_interptile(const InterpTileArgs<T> &a, hipStream_t s);
+// Small meshes: one launch for every type given (by type, null: none), each
+// of which has to satisfy the query.
+template <typename T>
+bool divtile_small(const DivTileArgs<T> &a);
+template <typename T>
+hipError_t launch_divtile_small(bool euler, const DivTileArgs<T> *const a[3], hipStream_t s);
+template <typename T>
+bool interptile_small(const InterpTileArgs<T> &a);
+template <typename T>
+hipError_t launch_interptile_small(const InterpTileArgs<T> *const a[3], hipStream_t s);
+template <typename T>
+bool gradflux_small(int etype, const GradFluxArgs<T> &a);
+template <typename T>
+hipError_t launch_gradflux_small(const GradFluxArgs<T> *const a[3], hipStream_t s);
 
 // FP64 reductions: per-block partial sums of nq quantities over one type,
 // written to partial[block][nq]; a second pass sums the blocks in order.

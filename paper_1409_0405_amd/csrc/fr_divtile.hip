@@ -72,27 +72,26 @@ __device__ __forceinline__ void interp_items(const Op<T> &M, const T *Bs, T *Uf,
 // of 16 elements needs 38 KB instead of 61 KB and four workgroups share a CU.
 // Order 3, FP32, 13,824 prisms and 24,576 tets: 92.0 -> 76.2 us for the right-hand side.
 // The register bounds keep two workgroups of eight wavefronts (FP32) on a CU.
+// (a by value: by reference the compiler reads it again around every store,
+// 76.4 -> 82.7 us for the order-3 right-hand side above.)
 template <typename T, int ET, int NE, int NBI, int NW, int MI, bool EULER>
-__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? NW == 4 ? 3 : 4 : 2) void divtile_kernel(DivTileArgs<T> a) {
+__device__ __forceinline__ void divtile(const DivTileArgs<T> a, int64_t e0, unsigned char *lds_raw) {
     using v4 = typename Vec4<T>::type;
     constexpr int W5 = TileShape<NE>::W5, WS = tile_stride<NE>(), NB = W5 / 16, NH = NB / NBI;
     static_assert(W5 == 5 * NE && NB % NBI == 0, "whole column blocks");
     constexpr int NG = n_geom_coeffs<ET>(), V = 16 / int(sizeof(T)), VPR = NE / V;
-    extern __shared__ __align__(16) unsigned char lds_raw[];
     const int nu = a.nu, nf = a.nf;
     T *Bs = reinterpret_cast<T *>(lds_raw);              // [divtile_rows][WS]
     T *Gs = Bs + size_t(EULER ? max(3 * nu, nf) : max(nf, nu)) * WS;   // Euler: [NG][NE] Jacobian coefficients
     T *Xs = Gs + NG * NE;                                // Euler: [nu][3] reference coordinates
 
-    const int64_t e0 = int64_t(xcd_block()) * NE;
-    if (e0 >= a.nelem) return;                           // whole workgroup: padding of the grid
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int krow = lane >> 4, c16 = lane & 15;
     const int64_t ld = a.ld;
 
     // Fn: straight into LDS (Navier-Stokes); the first FR 16-byte pieces per
     // thread into registers (Euler; the piece's row, field and position in it)
-    constexpr int FR = NW == 16 ? 2 : 6;
+    constexpr int FR = NW == 16 ? 2 : NW == 8 ? 5 : 6;
     floatx4 fr[EULER ? FR : 1];
     auto piece = [&](int c, int &dst) -> const T * {
         const int row = c / (5 * VPR), q = c - row * (5 * VPR);
@@ -263,21 +262,45 @@ __global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? NW == 4 ? 3 : 4 : 2) void
 // U_f = M0 U of a tile: the interpolation of a right-hand side's or a step's
 // first stage.
 template <typename T, int NE, int NBI, int NW>
-__global__ __launch_bounds__(64 * NW) void interptile_kernel(Op<T> M, const T *U, T *Uf, int64_t ld, int64_t nelem,
-                                                             int nu) {
+__device__ __forceinline__ void interptile(const InterpTileArgs<T> a, int64_t e0, unsigned char *lds_raw) {
     constexpr int NH = TileShape<NE>::NB / NBI;
-    extern __shared__ __align__(16) unsigned char lds_raw[];
     T *Bs = reinterpret_cast<T *>(lds_raw);              // [nu][tile_stride]
-    const int64_t e0 = int64_t(xcd_block()) * NE;
-    if (e0 >= nelem) return;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    tile_to_lds<T, NE, NW>(U, ld, e0, nu, Bs, w, lane);
+    tile_to_lds<T, NE, NW>(a.U, a.ld, e0, a.nu, Bs, w, lane);
     int frow[4];
-    block_rows(M, w / NH, lane >> 4, frow);
-    GatherWalk<T> walk(M, min(w / NH, M.nmg - 1), lane);
+    block_rows(a.M, w / NH, lane >> 4, frow);
+    GatherWalk<T> walk(a.M, min(w / NH, a.M.nmg - 1), lane);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    interp_items<T, NE, NBI, NW>(M, Bs, Uf, ld, e0, nelem, w, lane, walk, frow);
+    interp_items<T, NE, NBI, NW>(a.M, Bs, a.Uf, a.ld, e0, a.nelem, w, lane, walk, frow);
+}
+
+template <typename T, int ET, int NE, int NBI, int NW, int MI, bool EULER>
+__global__ __launch_bounds__(64 * NW, sizeof(T) == 4 ? NW == 4 ? 3 : 4 : 2) void divtile_kernel(DivTileArgs<T> a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int64_t e0 = int64_t(xcd_block()) * NE;
+    if (e0 < a.nelem)                                    // (whole workgroup: padding of the grid)
+        divtile<T, ET, NE, NBI, NW, MI, EULER>(a, e0, lds_raw);
+}
+template <typename T, int NE, int NBI, int NW>
+__global__ __launch_bounds__(64 * NW) void interptile_kernel(InterpTileArgs<T> a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int64_t e0 = int64_t(xcd_block()) * NE;
+    if (e0 < a.nelem) interptile<T, NE, NBI, NW>(a, e0, lds_raw);
+}
+
+// Small meshes: one launch for the tiles of every type.
+template <typename T, int MI, bool EULER>
+__global__ __launch_bounds__(1024, sizeof(T) == 4 ? 4 : 2) void divtile_small_kernel(PerType<DivTileArgs<T>> a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    small_tile(a, [&](auto et, const DivTileArgs<T> &x, int64_t e0) {
+        divtile<T, decltype(et)::value, 16, 1, 16, MI, EULER>(x, e0, lds_raw);
+    });
+}
+template <typename T>
+__global__ __launch_bounds__(1024) void interptile_small_kernel(PerType<InterpTileArgs<T>> a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    small_tile(a, [&](auto, const InterpTileArgs<T> &x, int64_t e0) { interptile<T, 16, 1, 16>(x, e0, lds_raw); });
 }
 
 template <typename T>
@@ -319,13 +342,22 @@ hipError_t launch_dt(const DivTileArgs<T> &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+}  // namespace
+// (More than six row blocks, hexahedra of order 4, keep eight wavefronts busy
+// without the split by column blocks: 512 of them, 57.3 against 54.9 us for a
+// right-hand side.)
+template <typename T>
+bool divtile_small(const DivTileArgs<T> &a) {
+    return narrow_mesh(a.nelem) && a.A.nmg <= 6;
+}
+namespace {
+
 template <typename T, int ET, bool EULER>
 hipError_t launch_dt_et(const DivTileArgs<T> &a, hipStream_t s) {
     const int nmg = a.A.nmg;
-    if (narrow_mesh(a.nelem) && nmg * 5 <= 48) {
-        // one column block per item over 16 wavefronts
+    if (divtile_small(a)) {
         if (nmg * 5 <= 16) return launch_dt<T, ET, 16, 1, 16, 1, EULER>(a, s);
-        return launch_dt<T, ET, 16, 1, 16, 3, EULER>(a, s);
+        return launch_dt<T, ET, 16, 1, 16, 2, EULER>(a, s);
     }
     // four wavefronts where the divergence product has at most four items
     // (row block, five column blocks), else eight with up to two items each
@@ -346,12 +378,37 @@ hipError_t launch_dt_et(const DivTileArgs<T> &a, hipStream_t s) {
 }
 
 template <typename T, int NE, int NBI, int NW>
-hipError_t launch_it(const Op<T> &M, const T *U, T *Uf, int64_t ld, int64_t nelem, int nu, hipStream_t s) {
+hipError_t launch_it(const InterpTileArgs<T> &a, hipStream_t s) {
     static bool set = false;
     const auto kernel = interptile_kernel<T, NE, NBI, NW>;
     if (hipError_t e = allow_lds(kernel, set); e != hipSuccess) return e;
-    kernel<<<xcd_grid((nelem + NE - 1) / NE), 64 * NW, tile_bytes<T>(nu, NE), s>>>(M, U, Uf, ld, nelem, nu);
+    kernel<<<xcd_grid((a.nelem + NE - 1) / NE), 64 * NW, tile_bytes<T>(a.nu, NE), s>>>(a);
     return hipGetLastError();
+}
+
+// Launch of a small-mesh kernel over the tiles of the types present.
+template <typename K, typename A, typename Bytes>
+hipError_t launch_small(K *kernel, bool &set, const A *const a[3], Bytes bytes, hipStream_t s) {
+    if (hipError_t e = allow_lds(kernel, set); e != hipSuccess) return e;
+    PerType<A> p;
+    size_t lds = 0;
+    int64_t ntiles = 0;
+    for (int t = 0; t < 3; ++t) {
+        if (!a[t]) continue;
+        p.a[t] = *a[t];
+        ntiles += (a[t]->nelem + 15) / 16;
+        lds = std::max(lds, bytes(t));
+    }
+    if (!ntiles) return hipSuccess;
+    kernel<<<unsigned(ntiles), 1024, lds, s>>>(p);
+    return hipGetLastError();
+}
+
+template <typename T, int MI, bool EULER>
+hipError_t launch_dt_small(const DivTileArgs<T> *const a[3], hipStream_t s) {
+    static bool set = false;
+    return launch_small(divtile_small_kernel<T, MI, EULER>, set, a,
+                        [&](int t) { return divtile_bytes(t, *a[t], EULER, 16); }, s);
 }
 
 bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
@@ -363,12 +420,41 @@ bool divtile_supported(int etype, const DivTileArgs<T> &a, bool euler) {
     return divtile_elems<T>(etype, a, euler) > 0;
 }
 
+namespace {
+template <typename T>
+bool valid_args(const DivTileArgs<T> &a, bool euler) {
+    return gathered(a.A, a.nu) && a.A.parts == (euler ? 2 : 1) && gathered(a.M, a.nf) && a.M.parts == 1 &&
+           a.ld % 64 == 0 && a.nelem <= a.ld && a.ep.ld == a.ld && a.ep.nelem == a.nelem && a.ep.nu == a.nu &&
+           a.ep.jinv && a.Fn && (euler ? a.U != nullptr : a.D != nullptr) && aligned16(a.Fn) && aligned16(a.geom);
+}
+template <typename T>
+bool valid_args(const InterpTileArgs<T> &a) {
+    return gathered(a.M, a.M.M) && a.M.parts == 1 && a.ld % 64 == 0 && a.nelem <= a.ld && a.U && a.Uf &&
+           aligned16(a.U);
+}
+}  // namespace
+
+template <typename T>
+hipError_t launch_divtile_small(bool euler, const DivTileArgs<T> *const a[3], hipStream_t s) {
+    int nmg = 1, ntypes = 0, et = 0;
+    for (int t = 0; t < 3; ++t) {
+        if (!a[t]) continue;
+        if (!valid_args(*a[t], euler) || !divtile_small(*a[t]) || divtile_bytes(t, *a[t], euler, 16) > TILE_LDS_MAX)
+            return hipErrorInvalidValue;
+        nmg = std::max(nmg, a[t]->A.nmg);
+        ++ntypes;
+        et = t;
+    }
+    // (one type alone: without the choice of the type, ten RK4 steps of 1,296
+    // tets, FP64, took 477 instead of 496 us)
+    if (ntypes == 1) return launch_divtile(et, euler, *a[et], s);
+    if (nmg * 5 <= 16) return euler ? launch_dt_small<T, 1, true>(a, s) : launch_dt_small<T, 1, false>(a, s);
+    return euler ? launch_dt_small<T, 2, true>(a, s) : launch_dt_small<T, 2, false>(a, s);
+}
+
 template <typename T>
 hipError_t launch_divtile(int etype, bool euler, const DivTileArgs<T> &a, hipStream_t s) {
-    if (!gathered(a.A, a.nu) || a.A.parts != (euler ? 2 : 1) || !gathered(a.M, a.nf) || a.M.parts != 1 ||
-        a.ld % 64 || a.nelem > a.ld || a.ep.ld != a.ld || a.ep.nelem != a.nelem || a.ep.nu != a.nu || !a.ep.jinv ||
-        !a.Fn || (euler ? !a.U : !a.D) || !aligned16(a.Fn) || !aligned16(a.geom))
-        return hipErrorInvalidValue;
+    if (!valid_args(a, euler)) return hipErrorInvalidValue;
     if (!a.nelem) return hipSuccess;
     if (etype == 0) return euler ? launch_dt_et<T, 0, true>(a, s) : launch_dt_et<T, 0, false>(a, s);
     if (etype == 1) return euler ? launch_dt_et<T, 1, true>(a, s) : launch_dt_et<T, 1, false>(a, s);
@@ -376,29 +462,46 @@ hipError_t launch_divtile(int etype, bool euler, const DivTileArgs<T> &a, hipStr
 }
 
 template <typename T>
-hipError_t launch_interptile(const Op<T> &M, const T *U, T *Uf, int64_t ld, int64_t nelem, int nu, hipStream_t s) {
-    if (M.stage != 7 || M.parts != 1 || !gathered(M, M.M) || ld % 64 || nelem > ld || !U || !Uf || !aligned16(U))
-        return hipErrorInvalidValue;
-    if (!nelem) return hipSuccess;
-    if (narrow_mesh(nelem)) return launch_it<T, 16, 1, 16>(M, U, Uf, ld, nelem, nu, s);
-    if constexpr (sizeof(T) == 4) {
-        if (tile_bytes<T>(nu, 32) <= TILE_LDS_MAX / 2) {
-            if (M.nmg <= 2) return launch_it<T, 32, 5, 4>(M, U, Uf, ld, nelem, nu, s);
-            return launch_it<T, 32, 5, 8>(M, U, Uf, ld, nelem, nu, s);
-        }
-    }
-    if (tile_bytes<T>(nu, 16) > TILE_LDS_MAX) return hipErrorInvalidValue;
-    if (M.nmg <= 4) return launch_it<T, 16, 5, 4>(M, U, Uf, ld, nelem, nu, s);
-    return launch_it<T, 16, 5, 8>(M, U, Uf, ld, nelem, nu, s);
+bool interptile_small(const InterpTileArgs<T> &a) {
+    return narrow_mesh(a.nelem);
 }
 
-template bool divtile_supported<float>(int, const DivTileArgs<float> &, bool);
-template bool divtile_supported<double>(int, const DivTileArgs<double> &, bool);
-template hipError_t launch_divtile<float>(int, bool, const DivTileArgs<float> &, hipStream_t);
-template hipError_t launch_divtile<double>(int, bool, const DivTileArgs<double> &, hipStream_t);
-template hipError_t launch_interptile<float>(const Op<float> &, const float *, float *, int64_t, int64_t, int,
-                                             hipStream_t);
-template hipError_t launch_interptile<double>(const Op<double> &, const double *, double *, int64_t, int64_t, int,
-                                              hipStream_t);
+template <typename T>
+hipError_t launch_interptile_small(const InterpTileArgs<T> *const a[3], hipStream_t s) {
+    static bool set = false;
+    for (int t = 0; t < 3; ++t)
+        if (a[t] && (!valid_args(*a[t]) || !interptile_small(*a[t]) || tile_bytes<T>(a[t]->nu, 16) > TILE_LDS_MAX))
+            return hipErrorInvalidValue;
+    return launch_small(interptile_small_kernel<T>, set, a, [&](int t) { return tile_bytes<T>(a[t]->nu, 16); }, s);
+}
+
+template <typename T>
+hipError_t launch_interptile(const InterpTileArgs<T> &a, hipStream_t s) {
+    if (interptile_small(a)) {
+        const InterpTileArgs<T> *p[3] = {&a, nullptr, nullptr};   // (the type plays no part)
+        return launch_interptile_small(p, s);
+    }
+    if (!valid_args(a)) return hipErrorInvalidValue;
+    if constexpr (sizeof(T) == 4) {
+        if (tile_bytes<T>(a.nu, 32) <= TILE_LDS_MAX / 2) {
+            if (a.M.nmg <= 2) return launch_it<T, 32, 5, 4>(a, s);
+            return launch_it<T, 32, 5, 8>(a, s);
+        }
+    }
+    if (tile_bytes<T>(a.nu, 16) > TILE_LDS_MAX) return hipErrorInvalidValue;
+    if (a.M.nmg <= 4) return launch_it<T, 16, 5, 4>(a, s);
+    return launch_it<T, 16, 5, 8>(a, s);
+}
+
+#define FR_DIVTILE_INSTANCES(T)                                                                              \
+    template bool divtile_supported<T>(int, const DivTileArgs<T> &, bool);                                   \
+    template bool divtile_small<T>(const DivTileArgs<T> &);                                                  \
+    template hipError_t launch_divtile<T>(int, bool, const DivTileArgs<T> &, hipStream_t);                   \
+    template hipError_t launch_divtile_small<T>(bool, const DivTileArgs<T> *const[3], hipStream_t);          \
+    template bool interptile_small<T>(const InterpTileArgs<T> &);                                            \
+    template hipError_t launch_interptile<T>(const InterpTileArgs<T> &, hipStream_t);                        \
+    template hipError_t launch_interptile_small<T>(const InterpTileArgs<T> *const[3], hipStream_t);
+FR_DIVTILE_INSTANCES(float)
+FR_DIVTILE_INSTANCES(double)
 
 }  // namespace frd

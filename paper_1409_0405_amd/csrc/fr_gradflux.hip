@@ -75,12 +75,11 @@ constexpr int tile_elems() { return (ET == 2 ? 16 : 32) * 4 / int(sizeof(T)); }
 // between the phases; the interpolation's and phase 6's first operator steps
 // and row numbers are loaded one phase ahead (tets 595 -> 571 us).
 template <typename T, int ET, int NE, int GH, int NBI, int NW, int MG, bool VD>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(GradFluxArgs<T> a) {
+__device__ __forceinline__ void gradflux(const GradFluxArgs<T> a, int64_t e0, unsigned char *lds_raw) {
     using v4 = typename Vec4<T>::type;
     constexpr int W5 = TileShape<NE>::W5, NB = TileShape<NE>::NB, WS = tile_stride<NE>();
     constexpr int NG = n_geom_coeffs<ET>();
     constexpr int V = 16 / int(sizeof(T)), VPR = NE / V;   // values per 16 bytes, 16-byte pieces per (row, field)
-    extern __shared__ __align__(16) unsigned char lds_raw[];
     const int nu = a.nu, nf = a.nf;
     // one region: B = [U; Cf] ([nu + nf][WS]) for the gradient product, then Qt
     // and, in place, Q and Ft ([3 nu][WS], row k nu + i)
@@ -89,8 +88,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(Grad
     T *Gs = Bs + size_t(max(nu + nf, 3 * nu)) * WS;      // [NG][NE] Jacobian coefficients
     T *Xs = Gs + NG * NE;                                // [nu][3] reference coordinates
 
-    const int64_t e0 = int64_t(xcd_block()) * NE;
-    if (e0 >= a.nelem) return;                           // whole workgroup: padding of the grid
     // the wavefront index is uniform in the wavefront: say so, so that the
     // loops branch on scalars
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -365,6 +362,27 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(Grad
     }
 }
 
+template <typename T, int ET, int NE, int GH, int NBI, int NW, int MG, bool VD>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void gradflux_kernel(GradFluxArgs<T> a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int64_t e0 = int64_t(xcd_block()) * NE;
+    if (e0 < a.nelem)                                    // (whole workgroup: padding of the grid)
+        gradflux<T, ET, NE, GH, NBI, NW, MG, VD>(a, e0, lds_raw);
+}
+
+// Small meshes: one launch for the tiles of every type, one column block per
+// item over 16 wavefronts (FP64: 8, whose point-wise work needs more than 128
+// registers).
+template <typename T>
+constexpr int small_waves() { return sizeof(T) == 4 ? 16 : 8; }
+template <typename T, int MG>
+__global__ __launch_bounds__(64 * small_waves<T>()) void gradflux_small_kernel(PerType<GradFluxArgs<T>> a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    small_tile(a, [&](auto et, const GradFluxArgs<T> &x, int64_t e0) {
+        gradflux<T, decltype(et)::value, 16, 5, 1, small_waves<T>(), MG, true>(x, e0, lds_raw);
+    });
+}
+
 // Streaming form (FP32): a workgroup takes a contiguous run of tiles and,
 // while it works on one, the next tile's B = [U; Cf] and Jacobian
 // coefficients travel straight from memory into a second LDS buffer
@@ -530,14 +548,6 @@ hipError_t launch_gf(const GradFluxArgs<T> &a, hipStream_t s) {
     constexpr int NW = (ET == 0 ? 8 : 16) * 4 / int(sizeof(T));
     // (next to the divergence stage on tiles only)
     if constexpr (VD) {
-        if (narrow_mesh(a.nelem) && gradflux_bytes<T, ET, 16>(a) <= TILE_LDS_MAX) {
-            // one column block per item over 16 wavefronts (FP64: 8, whose
-            // point-wise work needs more than 128 registers)
-            constexpr int NN = sizeof(T) == 4 ? 16 : 8, F = 16 / NN;
-            if (nmg * 5 <= 16) return launch_gf_mg<T, ET, 16, 5, 1, NN, F, VD>(a, s);
-            if (nmg * 5 <= 48) return launch_gf_mg<T, ET, 16, 5, 1, NN, 3 * F, VD>(a, s);
-            if (nmg * 5 <= 80) return launch_gf_mg<T, ET, 16, 5, 1, NN, 5 * F, VD>(a, s);
-        }
         // Low orders: the gradient operator has few row blocks, so they are also
         // split by column blocks (FP32 in two, FP64 in five), and a workgroup has
         // only as many wavefronts as that gives work to.  Times of this kernel
@@ -616,6 +626,68 @@ size_t gradflux_lds(int etype, const GradFluxArgs<T> &a) {
                                                 : etype == 2 ? gradflux_lds_t<T, 2>(a) : 0;
 }
 
+namespace {
+template <typename T>
+bool valid_args(const GradFluxArgs<T> &a) {
+    return gathered(a.G, 3 * a.nu) && gathered(a.M, a.nf) && (!a.D || gathered(a.V, a.nu)) && a.ld % 64 == 0 &&
+           a.nelem <= a.ld &&
+           (reinterpret_cast<uintptr_t>(a.U) | reinterpret_cast<uintptr_t>(a.Cf) |
+            reinterpret_cast<uintptr_t>(a.geom)) % 16 == 0 &&
+           reinterpret_cast<uintptr_t>(a.xi) % 4 == 0;   // 16- and 4-byte direct loads into LDS
+}
+
+template <typename T>
+size_t gradflux_small_bytes(int etype, const GradFluxArgs<T> &a) {
+    return etype == 0 ? gradflux_bytes<T, 0, 16>(a) : etype == 1 ? gradflux_bytes<T, 1, 16>(a)
+                                                                 : gradflux_bytes<T, 2, 16>(a);
+}
+
+template <typename T, int MG>
+hipError_t launch_gf_small(const PerType<GradFluxArgs<T>> &p, int64_t ntiles, size_t lds, hipStream_t s) {
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_small_kernel<T, MG>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    gradflux_small_kernel<T, MG><<<unsigned(ntiles), 64 * small_waves<T>(), lds, s>>>(p);
+    return hipGetLastError();
+}
+}  // namespace
+
+// Next to the divergence stage on tiles only.  A right-hand side of 2,058
+// tets and 1,176 prisms at order 4: 87 -> 54 us.  Hexahedra with more than
+// eight row blocks (orders 3 and 4) keep the tiles of 16 elements and 16
+// wavefronts of larger meshes, whose items are full (order 3, 256 tiles: 25
+// against 31 us).
+template <typename T>
+bool gradflux_small(int etype, const GradFluxArgs<T> &a) {
+    return a.D && narrow_mesh(a.nelem) && a.G.nmg <= (etype == 2 ? 8 : 16) &&
+           gradflux_small_bytes(etype, a) <= TILE_LDS_MAX;
+}
+
+template <typename T>
+hipError_t launch_gradflux_small(const GradFluxArgs<T> *const a[3], hipStream_t s) {
+    PerType<GradFluxArgs<T>> p;
+    size_t lds = 0;
+    int64_t ntiles = 0;
+    int nmg = 1;
+    for (int t = 0; t < 3; ++t) {
+        if (!a[t]) continue;
+        if (!valid_args(*a[t]) || !gradflux_small(t, *a[t])) return hipErrorInvalidValue;
+        p.a[t] = *a[t];
+        ntiles += (a[t]->nelem + 15) / 16;
+        lds = std::max(lds, gradflux_small_bytes(t, *a[t]));
+        nmg = std::max(nmg, a[t]->G.nmg);
+    }
+    if (!ntiles) return hipSuccess;
+    constexpr int F = 16 / small_waves<T>();             // five items per row block
+    if (nmg <= 3) return launch_gf_small<T, F>(p, ntiles, lds, s);
+    if (nmg <= 9) return launch_gf_small<T, 3 * F>(p, ntiles, lds, s);
+    return launch_gf_small<T, 5 * F>(p, ntiles, lds, s);
+}
+
 template <typename T>
 hipError_t launch_gradflux(int etype, const GradFluxArgs<T> &a, hipStream_t s, bool stream) {
     size_t lds = gradflux_lds<T>(etype, a);
@@ -628,13 +700,13 @@ hipError_t launch_gradflux(int etype, const GradFluxArgs<T> &a, hipStream_t s, b
     } else {
         if (stream) return hipErrorInvalidValue;
     }
-    if (!lds || !gathered(a.G, 3 * a.nu) || !gathered(a.M, a.nf) || (a.D && (stream || !gathered(a.V, a.nu))) ||
-        a.ld % 64 || a.nelem > a.ld ||
-        (reinterpret_cast<uintptr_t>(a.U) | reinterpret_cast<uintptr_t>(a.Cf) |
-         reinterpret_cast<uintptr_t>(a.geom)) % 16 ||
-        reinterpret_cast<uintptr_t>(a.xi) % 4)   // 16- and 4-byte direct loads into LDS
-        return hipErrorInvalidValue;
+    if (!lds || !valid_args(a) || (a.D && stream)) return hipErrorInvalidValue;
     if (!a.nelem) return hipSuccess;
+    if (gradflux_small(etype, a) && !stream) {
+        const GradFluxArgs<T> *p[3] = {nullptr, nullptr, nullptr};
+        p[etype] = &a;
+        return launch_gradflux_small(p, s);
+    }
     if constexpr (std::is_same<T, float>::value) {
         if (stream) return etype == 0 ? launch_gf_stream<0, 8>(a, lds, s) : launch_gf_stream<1, 8>(a, lds, s);
     }
@@ -645,6 +717,10 @@ hipError_t launch_gradflux(int etype, const GradFluxArgs<T> &a, hipStream_t s, b
 
 template size_t gradflux_lds<float>(int, const GradFluxArgs<float> &);
 template size_t gradflux_lds<double>(int, const GradFluxArgs<double> &);
+template bool gradflux_small<float>(int, const GradFluxArgs<float> &);
+template bool gradflux_small<double>(int, const GradFluxArgs<double> &);
+template hipError_t launch_gradflux_small<float>(const GradFluxArgs<float> *const[3], hipStream_t);
+template hipError_t launch_gradflux_small<double>(const GradFluxArgs<double> *const[3], hipStream_t);
 template hipError_t launch_gradflux<float>(int, const GradFluxArgs<float> &, hipStream_t, bool);
 template hipError_t launch_gradflux<double>(int, const GradFluxArgs<double> &, hipStream_t, bool);
 

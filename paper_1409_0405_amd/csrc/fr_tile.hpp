@@ -201,5 +201,26 @@ constexpr size_t TILE_LDS_MAX = 160 * 1024;   // LDS of a CU
 constexpr int64_t NARROW_TILES = 256;
 inline bool narrow_mesh(int64_t nelem) { return (nelem + 15) / 16 <= NARROW_TILES; }
 
+// Their kernels take the tiles of every element type in one launch (the
+// types' own launches would run one after the other, each with the chip
+// mostly idle and a launch's cost of its own): arguments by type, nelem 0
+// where a type is absent.
+template <typename A>
+struct PerType {
+    A a[3];
+};
+// f(type, its arguments, first element) for this workgroup's tile of 16:
+// prisms and hexahedra, whose tiles take longer, come first.
+template <typename A, typename F>
+__device__ __forceinline__ void small_tile(const PerType<A> &p, F &&f) {
+    int64_t b = blockIdx.x;
+    const int64_t n1 = (p.a[1].nelem + 15) / 16, n2 = (p.a[2].nelem + 15) / 16;
+    if (b < n1) return f(std::integral_constant<int, 1>{}, p.a[1], 16 * b);
+    b -= n1;
+    if (b < n2) return f(std::integral_constant<int, 2>{}, p.a[2], 16 * b);
+    b -= n2;
+    if (16 * b < p.a[0].nelem) f(std::integral_constant<int, 0>{}, p.a[0], 16 * b);
+}
+
 }  // namespace
 }  // namespace frd
