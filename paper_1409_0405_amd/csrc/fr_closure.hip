@@ -62,6 +62,10 @@ __global__ __launch_bounds__(256) void moments_kernel(const T *__restrict__ U, c
 // inputs x[g][0..119]: own moments, then the neighbours' across faces 0..4
 // (zeros where there is no such face), normalised (x - mu) / s if stats.
 // Moments at mom[g * rs + q * cs], inputs at feat[g * frs + k * fcs].
+// A thread takes one element and one of the six sources, blockIdx.y, with its
+// twenty loads in flight together: a thread that walked all 120 inputs waited
+// for a gather and a division each time (129,600 elements, 62 MB written:
+// 45 -> 25 us).
 __global__ __launch_bounds__(256) void features_kernel(const float *__restrict__ mom, int64_t rs, int64_t cs,
                                                        const int32_t *__restrict__ nb,
                                                        int64_t ntot,
@@ -69,14 +73,18 @@ __global__ __launch_bounds__(256) void features_kernel(const float *__restrict__
                                                        float *__restrict__ feat, int64_t frs, int64_t fcs) {
     const int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (g >= ntot) return;
-    float *out = feat + g * frs;
-    for (int b = 0; b < 6; ++b) {
-        const int64_t src = b == 0 ? g : nb[g * 5 + b - 1];
-        for (int q = 0; q < 20; ++q) {
-            float v = src >= 0 ? mom[src * rs + q * cs] : 0.0f;
-            if (stats) v = (v - stats[b * 20 + q]) / stats[MLP_IN + b * 20 + q];
-            out[(b * 20 + q) * fcs] = v;
-        }
+    const int b = blockIdx.y;
+    const int64_t src = b == 0 ? g : nb[g * 5 + b - 1];
+    float *out = feat + g * frs + b * 20 * fcs;
+    const float *in = mom + (src >= 0 ? src : g) * rs;
+    float v[20];
+#pragma unroll
+    for (int q = 0; q < 20; ++q) v[q] = in[q * cs];
+#pragma unroll
+    for (int q = 0; q < 20; ++q) {
+        float x = src >= 0 ? v[q] : 0.0f;
+        if (stats) x = (x - stats[b * 20 + q]) / stats[MLP_IN + b * 20 + q];
+        out[q * fcs] = x;
     }
 }
 
@@ -503,7 +511,7 @@ hipError_t launch_moments(const T *U, const T *B, int64_t ld, int64_t nelem, int
 hipError_t launch_features(const float *mom, int64_t rs, int64_t cs, const int32_t *nb, int64_t ntot,
                            const float *stats, float *feat, int64_t frs, int64_t fcs, hipStream_t s) {
     if (!ntot) return hipSuccess;
-    features_kernel<<<unsigned((ntot + 255) / 256), 256, 0, s>>>(mom, rs, cs, nb, ntot, stats, feat, frs, fcs);
+    features_kernel<<<dim3(unsigned((ntot + 255) / 256), 6), 256, 0, s>>>(mom, rs, cs, nb, ntot, stats, feat, frs, fcs);
     return hipGetLastError();
 }
 
