@@ -40,12 +40,16 @@ RIDGE = PEAK_FP32_MFMA / PEAK_HBM
 # (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000, the factors read off the state
 # copies of known size), keyed (kernel class, 16-row blocks per wavefront,
 # stage) for the products and (class, 0, 0) for the point-wise kernels and the
-# fused gradient stage; the file below holds the commands and counts.  A
+# kernels on element tiles (the divergence stage per stage of a step); the file below holds the commands and counts.  A
 # variant not listed reports traffic null.
 TRAFFIC_SOURCE = "profiles/rhs_ns_p4_tgv_mixed_hbm_counters.md"
 MEASURED_TRAFFIC = {
-    ('gradflux_tet', 0, 0): 1164.4e6,
-    ('gradflux_pri', 0, 0): 1257.8e6,
+    ('gradflux_tet', 0, 0): 1018.2e6,
+    ('gradflux_pri', 0, 0): 1049.1e6,
+    ('div_tet', 0, 0): 976.4e6,
+    ('div_pri', 0, 0): 1082.4e6,
+    ('interp_tet', 0, 0): 374.0e6,
+    ('interp_pri', 0, 0): 400.4e6,
     ('interp_tet', 2, 1): 373.8e6,
     ('interp_pri', 2, 1): 398.8e6,
     ('interp_pri', 1, 1): 398.5e6,
@@ -161,8 +165,20 @@ def variant_of(mesh, k, report):
     m_ = re.search(rf"{TYPE_SHORT[t]} op{op} cap (\d+) stage (\d+)", report or "")
     if not m_:
         return None
+    # the kernels on element tiles, where the autotuner kept them
+    if op == 0 and re.search(rf"{TYPE_SHORT[t]} interp: [^;]*, tile;", report or ""):
+        return 0, 0
+    if op == 3 and stage_form(report, t) == "tiles":
+        return 0, 0
     nmg = -(-Mb // int(m_.group(1)))
     return -(-Mb // nmg), int(m_.group(2))
+
+
+def stage_form(report, t):
+    """The form of type t's whole stage the autotuner kept ("separate",
+    "fused", "tiles" or "streaming"; None where it had no choice)."""
+    m_ = re.search(rf"{TYPE_SHORT[t]} stage: [^;]*, (\w+);", report or "")
+    return m_.group(1) if m_ else None
 
 
 def operator_nnz(mesh, t):
@@ -178,11 +194,18 @@ def operator_nnz(mesh, t):
     grad = np.concatenate([np.concatenate([G[k], L * nref[:, k][None, :]], axis=1) for k in range(3)])
     div = np.concatenate([G[k] - (L * nref[:, k][None, :]) @ M0 for k in range(3)] + [L], axis=1)
     nz = lambda A: int(np.count_nonzero(np.abs(A) > 1e-10 * np.abs(A).max()))
-    return {"interp": nz(M0), "gradinterp": nz(M0), "grad": nz(grad), "div": nz(div)}
+    return {"interp": nz(M0), "gradinterp": nz(M0), "grad": nz(grad), "div": nz(div),
+            "div_volume": nz(div[:, :3 * M0.shape[1]])}
 
 
-def kernel_model(mesh, system):
+def kernel_model(mesh, system, report=None, stages=5):
     """Algorithmic FLOPs and bytes per launch of each kernel class (FP32).
+
+    With the autotuner's report, types whose stage runs on element tiles are
+    counted as these kernels divide the work: the gradient stage also forms
+    the volume part D of the divergence (written instead of Ft), the
+    divergence class adds L Fn and the update and, in all but the last of a
+    step's stages, interpolates the next stage's input to the flux points.
 
     Operator products C = A B: the paper's dense-operator count 2 M K n flops
     ("flops") and 4 (K + M) n bytes over the n = fields x elements real
@@ -225,6 +248,18 @@ def kernel_model(mesh, system):
         # the divergence product applies -R~/J and the register update in
         # its store: R~ is neither written nor read back
         out[f"div_{name}"]["bytes"] += neg - 2 * 5 * nu * E * s
+        if ns and stage_form(report, t) == "tiles":
+            g, gi = ops["grad"], ops["gradinterp"]
+            vol, again = nnz["div_volume"], (stages - 1) / stages
+            out[f"gradflux_{name}"] = {
+                "flops": 2.0 * (g[0] * g[1] * g[2] + gi[0] * gi[1] * gi[2] + nu * 3 * nu * cols5),
+                "nnz_flops": 2.0 * (nnz["grad"] * g[2] + nnz["gradinterp"] * gi[2] + vol * cols5),
+                "bytes": float(s * (5 * nu + 5 * nf + 5 * nu + 15 * nf) * E + s * ng * E)}
+            out[f"div_{name}"] = {
+                "flops": 2.0 * (nu * nf + again * nf * nu) * cols5,
+                "nnz_flops": 2.0 * (nnz["div"] - vol + again * nnz["interp"]) * cols5,
+                # D, Fn, 1/J, the accumulator in and out, the output
+                "bytes": float(s * (5 * nu + 5 * nf + nu + 15 * nu + again * 5 * nf) * E)}
     npairs //= 2
     # with the LDG beta = 1/2 (the default) only side L's gradient enters the
     # common viscous flux
@@ -604,10 +639,10 @@ def structural(model, avg_s, k):
 
 def walks_nonzeros(k, variant):
     """Whether kernel class k walks only its operators' structural nonzeros
-    (step-list products, stages 5 and 6, and the fused gradient stage): such
+    (step-list products, stages 5 and 6, and the kernels on element tiles): such
     a kernel is priced on its structural work, since the paper's dense count
     would credit it with work it skips (a fraction above 1 of the roof)."""
-    return k.startswith("gradflux_") or bool(variant and variant[1] in (5, 6))
+    return k.startswith("gradflux_") or bool(variant and (variant[1] in (5, 6) or variant[0] == 0))
 
 
 def workload_form(name, arrays, h_ref, steps, warmup, mach, mu, pr, stream, cfl=0.3, p=4, **mesh_kw):
@@ -660,7 +695,7 @@ def workload_form(name, arrays, h_ref, steps, warmup, mach, mu, pr, stream, cfl=
         m.rk_step(frlib.FR_RK45_2RP, dt, 1, stream)
     prof = m.profile_read()
     m.profile(False)
-    model = kernel_model(m, "ns")
+    model = kernel_model(m, "ns", report)
     nbp = boundary_points(arrays, p)
     if nbp:
         # boundary points: state and gradient traces in, the jump and the flux out
@@ -916,7 +951,7 @@ def main():
             mesh.rk_step(frlib.FR_RK45_2RP, dt, 1, stream)
         prof = mesh.profile_read()
         mesh.profile(False)
-        model = kernel_model(mesh, "ns")
+        model = kernel_model(mesh, "ns", tuned.get("fp32", ""))
         rows = sorted(((ms, k, cnt) for k, (ms, cnt) in prof.items() if cnt), reverse=True)
         tot = sum(r[0] for r in rows)
         for ms, k, cnt in rows:
@@ -928,8 +963,12 @@ def main():
         # the HBM bytes one RHS moves, from the measured per-launch traffic of
         # each kernel variant the timed steps ran (null if one is not in the
         # table)
-        per_rhs = [MEASURED_TRAFFIC.get((kk,) + (variant_of(mesh, kk, tuned.get("fp32", "")) or (0, 0)))
-                   for _, kk, cc in rows]
+        # (weighted with the launches per stage: on tiles only a step's first
+        # stage has an interpolation kernel)
+        nst = max(cc for _, _, cc in rows)
+        per_rhs = [None if x is None else x * cc / nst for x, cc in
+                   ((MEASURED_TRAFFIC.get((kk,) + (variant_of(mesh, kk, tuned.get("fp32", "")) or (0, 0))), cc)
+                    for _, kk, cc in rows)]
         rhs_traffic = float(sum(per_rhs)) if all(x is not None for x in per_rhs) else None
         ms, k, cnt = rows[0]
         avg = ms / cnt * 1e-3
@@ -944,10 +983,10 @@ def main():
         roof["structural"] = structural(model, avg, k)
         roof["hbm"] = {"achieved": model[k]["bytes"] / avg / 1e9, "unit": "GB/s",
                        "frac": model[k]["bytes"] / avg / PEAK_HBM, "algorithmic_bytes": model[k]["bytes"]}
-        if vt:
+        if vt and vt[0]:
             roof["variant"] = {"rows_blocks_per_wave": vt[0], "stage": vt[1]}
         roof["traffic"] = MEASURED_TRAFFIC.get((k,) + (vt or (0, 0)))
-        roof["traffic_source"] = (f"{TRAFFIC_SOURCE}: {k}" + (f" (row blocks {vt[0]}, stage {vt[1]})" if vt else "")
+        roof["traffic_source"] = (f"{TRAFFIC_SOURCE}: {k}" + (f" (row blocks {vt[0]}, stage {vt[1]})" if vt and vt[0] else "")
                                   if roof["traffic"] else None)
         roof["kernel"] = k
         roof["avg_launch_us"] = avg * 1e6

@@ -87,11 +87,11 @@ typedef enum { FR_RK4 = 0, FR_RK45_2RP = 1, FR_FWD_EULER = 2 } fr_scheme;
  * product, the solution-point work (physical gradient, transformed flux) and
  * the gradient interpolation as three kernels that pass the reference and
  * physical gradients through memory.  By default one kernel does all three
- * per tile of elements with those gradients in LDS wherever the gradient
- * operator has at least four 16-row blocks (tets from p = 3, prisms and
- * hexahedra from p = 2), the three kernels below that; fr_autotune then
- * keeps whichever form is fastest per element type.  All give the same
- * bits. */
+ * per tile of elements with those gradients in LDS, and the divergence
+ * stage runs on tiles behind it (without that, under FR_SEPARATE_UPDATE,
+ * only where the gradient operator has at least four 16-row blocks);
+ * fr_autotune then keeps whichever form is fastest per element type.  All
+ * give the same bits. */
 #define FR_SEPARATE_GRADIENT 0x8u
 
 typedef struct fr_mesh_s *fr_mesh;   /* opaque, library-owned */

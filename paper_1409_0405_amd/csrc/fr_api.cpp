@@ -17,6 +17,11 @@
 // operator, so F~ is read once.  Step 3 takes the jump D, which the interface
 // kernel forms directly (no cancellation between L C and L M0 U); a side whose
 // LDG weight is zero (beta = +-1/2) has D = 0 and is never written.
+//
+// In FP32 and FP64 these steps run on tiles of elements in LDS: steps 3 to 5
+// and the volume part of step 7 in one kernel (Navier-Stokes), the rest of
+// step 7 (Euler: steps 4 and 7), step 8 and, inside a time step, step 1 of
+// the next stage in another.  Small meshes launch each once for all types.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -47,13 +52,15 @@ struct DevType {
     int nu = 0, nf = 0;
     int64_t nelem = 0, ld = 0;
     frd::Op<T> Aint, Agint, Agrad, Adiv;          // Agint: M0 for the gradients
-    // operators of the kernels on element tiles (gathered): gradient stage [G_k | L_k] and M0, its volume part of the
-    // divergence [G'_0 G'_1 G'_2], and the divergence stage's operator (Euler
+    // operators of the kernels on element tiles (gathered): gradient stage
+    // [G_k | L_k] and M0, its volume part of the divergence
+    // [G'_0 G'_1 G'_2], and the divergence stage's operator (Euler
     // [G'_k | L], Navier-Stokes L)
     frd::Op<T> Fgrad, Fgint, Tvol, Tdiv;
     // divergence stage on tiles (it fits a CU, and no product variant was
-    // forced); tile_interp: it also interpolates the next stage's input
-    bool tile = false, tile_interp = true;
+    // forced); tile_interp: it also interpolates the next stage's input;
+    // interp_tile: a first stage's interpolation runs on tiles too
+    bool tile = false, tile_interp = true, interp_tile = true;
     // fused gradient stage: bit f of qmask[e] is set when an interface or
     // boundary kernel reads the gradient on face f of element e (the other
     // flux points are not written); fbit[s] = 1 << face of the flux point in
@@ -63,6 +70,7 @@ struct DevType {
     // streaming (FP32); set from the operator's size at setup, the autotuner
     // keeps the fastest
     int grad_form = 1;
+    bool form_chosen = false;     // by the autotuner or the caller
     frd::OpSplit Sint, Sgint, Sgrad, Sdiv;        // split-precision forms only
     T *geom = nullptr, *xi = nullptr;
     T *jinv = nullptr;        // [nu][ld] 1 / J at the solution points (host FP64, rounded)
@@ -634,8 +642,8 @@ fr_status setup_device(fr_mesh m, hipStream_t s) {
             FR_HIP(m, upload_op(D.Tvol, f, idx, d.allocs));
             // before autotuning: the fused stage.  A right-hand side with it
             // and the divergence stage on tiles against the separate kernels,
-            // mixed Taylor-Green meshes, FP32: order 1, 384 elements 42
-            // against 54 us, 129,600 elements 140 against 182 us; order 2, 53
+            // mixed Taylor-Green meshes, FP32: order 1, 608 elements 42
+            // against 54 us, 129,024 elements 140 against 182 us; order 2, 53
             // against 77 and 300 against 410 us; FP64, order 1, 320 against
             // 340 us.  Without the divergence stage on tiles it loses where
             // the gradient operator has fewer than four row blocks.
@@ -902,6 +910,19 @@ frd::DivTileArgs<T> divtile_args(fr_mesh m, const DevType<T> &D, const T *U) {
     return ta;
 }
 
+// Arguments of the interpolation on tiles, U_f = M0 U.
+template <typename T>
+frd::InterpTileArgs<T> interptile_args(const DevType<T> &D, const T *U) {
+    frd::InterpTileArgs<T> ia;
+    ia.M = D.Fgint;
+    ia.U = U;
+    ia.Uf = D.Uf;
+    ia.ld = D.ld;
+    ia.nelem = D.nelem;
+    ia.nu = D.nu;
+    return ia;
+}
+
 // Solution-point kernel arguments of one element type on state U.
 template <typename T>
 frd::UptsArgs<T> upts_args(fr_mesh m, const DevType<T> &D, const T *U) {
@@ -931,13 +952,8 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
         int first = -1;
         for (int t = 0; t < frh::NTYPE; ++t) {
             DevType<T> &D = d.t[t];
-            if (!D.nelem || (uf && uf[t]) || !D.Fgint.frag || !D.tile_interp) continue;
-            ia[t].M = D.Fgint;
-            ia[t].U = U[t];
-            ia[t].Uf = D.Uf;
-            ia[t].ld = D.ld;
-            ia[t].nelem = D.nelem;
-            ia[t].nu = D.nu;
+            if (!D.nelem || (uf && uf[t]) || !D.Fgint.frag || !D.interp_tile) continue;
+            ia[t] = interptile_args<T>(D, U[t]);
             if (merge && frd::interptile_small<T>(ia[t])) {
                 small[t] = &ia[t];
                 if (first < 0) first = t;
@@ -950,7 +966,7 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     }
     for (int t = 0; t < frh::NTYPE; ++t) {
         DevType<T> &D = d.t[t];
-        if (!D.nelem || (uf && uf[t]) || (D.Fgint.frag && D.tile_interp)) continue;
+        if (!D.nelem || (uf && uf[t]) || (D.Fgint.frag && D.interp_tile)) continue;
         const int64_t w5 = 5 * D.ld;
         FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
                   opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U[t], w5, D.nu, nullptr, 0, 0, D.Uf, w5, w5, s));
@@ -1524,8 +1540,28 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         if (fused_ok && !tile_ok) forms.push_back({1, false, "fused"});
         if (tile_ok) forms.push_back({ns ? 1 : 0, true, "tiles"});
         if (fused_ok && sizeof(T) == 4 && t < 2) forms.push_back({2, false, "streaming"});
-        if (forms.size() == 1) continue;
+        // (a forced interpolation product stays)
         const T *U = D.reg[0];
+        auto timed = [&](auto &&go, float &ms) -> hipError_t {
+            hipError_t e = go();
+            if (e == hipSuccess) e = hipEventRecord(e0, s);
+            for (int r = 0; r < 3 && e == hipSuccess; ++r) e = go();
+            if (e == hipSuccess) e = hipEventRecord(e1, s);
+            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            return e == hipSuccess ? hipEventElapsedTime(&ms, e0, e1) : e;
+        };
+        static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
+        if (D.tile_interp) {
+            float product = 0, onto = 0;
+            FR_HIP(m, timed([&] {
+                return opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U, w5, nu, nullptr, 0, 0, D.Uf, w5, w5, s);
+            }, product));
+            FR_HIP(m, timed([&] { return frd::launch_interptile<T>(interptile_args<T>(D, U), s); }, onto));
+            D.interp_tile = onto <= product;
+            report += sn[t] + std::string(" interp: product ") + std::to_string(product / 3 * 1e3) + " us tile " +
+                      std::to_string(onto / 3 * 1e3) + " us, " + (D.interp_tile ? "tile" : "product") + "; ";
+        }
+        if (forms.size() == 1) continue;
         frd::NegArgs<T> na{};
         na.Rt = D.Rt;
         na.out = D.R;
@@ -1568,16 +1604,10 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         };
         size_t best = 0;
         float best_ms = 1e30f;
-        static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
         report += sn[t] + std::string(" stage:");
         for (size_t i = 0; i < forms.size(); ++i) {
             float ms = 0;
-            FR_HIP(m, run(forms[i]));
-            FR_HIP(m, hipEventRecord(e0, s));
-            for (int r = 0; r < 3; ++r) FR_HIP(m, run(forms[i]));
-            FR_HIP(m, hipEventRecord(e1, s));
-            FR_HIP(m, hipEventSynchronize(e1));
-            FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
+            FR_HIP(m, timed([&] { return run(forms[i]); }, ms));
             if (ms < best_ms) {
                 best_ms = ms;
                 best = i;
@@ -1585,6 +1615,7 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
             report += std::string(" ") + forms[i].name + " " + std::to_string(ms / 3 * 1e3) + " us";
         }
         if (ns) D.grad_form = forms[best].grad;
+        D.form_chosen = true;
         D.tile = forms[best].tile;
         report += std::string(", ") + forms[best].name + "; ";
     }
@@ -2003,7 +2034,10 @@ fr_status set_blocking_impl(fr_mesh m, int t, int op, int cap, int stage) {
     *dst[op] = o;
     // a forced product variant runs as a product of its own
     if (op == frd::OP_DIV) D.tile = false;
-    if (op == frd::OP_INTERP) D.tile_interp = false;
+    if (op == frd::OP_INTERP) D.tile_interp = D.interp_tile = false;
+    // (below four row blocks the fused gradient stage is the default only
+    // next to the divergence stage on tiles)
+    if (op != frd::OP_INTERP && D.Fgrad.frag && D.Fgrad.nmg < 4 && !D.form_chosen) D.grad_form = 0;
     return FR_OK;
 }
 }  // namespace
@@ -2021,10 +2055,14 @@ fr_status fr_set_blocking(fr_mesh m, int32_t etype, int32_t op, int32_t cap, int
         if (stage > 0 && !have) return fail(m, FR_ERR_UNSUPPORTED, "no fused gradient stage for this type or form");
         if (stage == 2 && (m->precision != FR_FP32 || etype == 2))
             return fail(m, FR_ERR_UNSUPPORTED, "the streaming gradient stage is FP32 tets and prisms only");
+        auto choose = [&](auto &D) {
+            D.grad_form = stage;
+            D.form_chosen = true;
+        };
         if (m->precision == FR_FP64)
-            dev_of<double>(m).t[etype].grad_form = stage;
+            choose(dev_of<double>(m).t[etype]);
         else
-            dev_of<float>(m).t[etype].grad_form = stage;
+            choose(dev_of<float>(m).t[etype]);
         return FR_OK;
     }
     if (op < 0 || op > 3 || cap < 1 || stage < 0 || stage > 6)

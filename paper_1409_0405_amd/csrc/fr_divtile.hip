@@ -19,6 +19,11 @@
 // The operators are walked in the K order of the product kernels (gathered
 // layout), and the update is the shared one, so every value has the bits of
 // the separate kernels.
+//
+// What bounds it: memory.  At p = 4, FP32, Navier-Stokes inside a step, 196,608
+// tets take 264 us and 110,592 prisms 294 us, about 4 TB/s of the arrays named
+// above (the card copies at 4.9); the separate divergence and interpolation
+// products took 231 + 85 and 342 + 131 us and had Ft, three times D, to read.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -9,12 +9,17 @@
 // NE elements with all five fields and keeps Qt and Q in LDS:
 //   1. B = [U; Cf] of the tile -> LDS;
 //   2. Qt = [G_k | L_k] B on the matrix cores -> LDS;
-//   3. per (solution point, element): Q = adj^T Qt / J (in place), and
-//      Ft = adj (F_inv(U) - F_vis(U, Q)) -> memory;
-//   4. Qf = M0 Q on the matrix cores -> memory.
-// Only U and Cf are read and only Ft and Qf are written, Qf only on the
-// faces whose gradient the interface and boundary kernels read (with the
-// usual LDG weights one side of each interface).  The operators are walked
+//   3. per (solution point, element): Q = adj^T Qt / J (in place);
+//   4. Qf = M0 Q on the matrix cores -> memory, only on the faces whose
+//      gradient the interface and boundary kernels read (with the usual LDG
+//      weights one side of each interface);
+//   5. Ft = adj (F_inv(U) - F_vis(U, Q)) in Q's place;
+//   6. the volume part of the divergence, D = [G'_0 G'_1 G'_2] Ft, on the
+//      matrix cores -> memory: five values per point for the divergence
+//      stage to read instead of the fifteen of Ft.
+// Without the divergence stage on tiles (FR_SEPARATE_UPDATE, a forced
+// divergence product, the streaming form) Ft goes to memory in step 3 and the
+// kernel ends with step 4.  The operators are walked
 // in the K order of the product kernels (gathered layout, below), and the
 // point-wise arithmetic is the shared one, so every value has the bits of the
 // separate kernels.
@@ -64,15 +69,19 @@ __device__ __forceinline__ void interp3_products(GatherWalk<T, AD> &w, const T *
 template <typename T, int ET>
 constexpr int tile_elems() { return (ET == 2 ? 16 : 32) * 4 / int(sizeof(T)); }
 
-// One workgroup of NW wavefronts per tile.  MG: row blocks of the gradient
-// operator per wavefront (>= nmg / NW); their accumulators stay in registers
-// until every wavefront has finished reading B, so that Qt takes B's place in
-// LDS and a tile needs max(B, Qt) of it.
+// One workgroup of NW wavefronts per tile.  Work items of the gradient
+// product: (row block, every GH-th column block), MG per wavefront; their
+// accumulators stay in registers until every wavefront has finished reading
+// B, so that Qt takes B's place in LDS and a tile needs max(B, Qt) of it.
+// NBI: column blocks per item of the other two products.
 // VD: the volume part D = [G'_0 G'_1 G'_2] Ft of the divergence is written
 // instead of Ft: Q stays in LDS until it is interpolated, then Ft takes its
 // place (phase 5) and is multiplied there (phase 6).
-// What bounds it (p = 4, 307,200-element box): the matrix cores and the waits
-// between the phases; the interpolation's and phase 6's first operator steps
+// What bounds it (p = 4, FP32, 196,608 tets and 110,592 prisms: 571 and 492
+// us with the volume part, 571 + 264 and 492 + 294 us with the divergence
+// stage, against 467 + 231 + 85 and 518 + 342 + 131 us with Ft in memory and
+// separate divergence and interpolation products): the matrix cores, busy 44
+// per cent of the time for tets, and the waits between the phases; the interpolation's and phase 6's first operator steps
 // and row numbers are loaded one phase ahead (tets 595 -> 571 us).
 template <typename T, int ET, int NE, int GH, int NBI, int NW, int MG, bool VD>
 __device__ __forceinline__ void gradflux(const GradFluxArgs<T> a, int64_t e0, unsigned char *lds_raw) {
@@ -551,7 +560,7 @@ hipError_t launch_gf(const GradFluxArgs<T> &a, hipStream_t s) {
         // Low orders: the gradient operator has few row blocks, so they are also
         // split by column blocks (FP32 in two, FP64 in five), and a workgroup has
         // only as many wavefronts as that gives work to.  Times of this kernel
-        // before -> after: order 1, FP32, 82,944 tets 52 -> 34 us, 46,656 prisms
+        // before -> after: order 1, FP32, 82,944 tets 52 -> 34 us, 46,080 prisms
         // 54 -> 29 us; order 2, 79 -> 62 and 85 -> 68 us; 13,824 hexahedra, order
         // 1, 34 -> 16 us, order 2, 47 -> 30 us; FP64, order 1, prisms 103 -> 70
         // us, hexahedra 48 -> 29 us, order 2, prisms 168 -> 146 us (but tets 84

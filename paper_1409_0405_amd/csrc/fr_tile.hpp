@@ -194,17 +194,19 @@ constexpr size_t TILE_LDS_MAX = 160 * 1024;   // LDS of a CU
 
 // Small meshes, at most one tile of 16 elements per CU: no second workgroup
 // fills a CU's waits, so the tile's own chain of steps is what counts, and
-// sixteen wavefronts with one column block each shorten it (384 elements,
-// order 2: 54.1 -> 52.6 us for a Navier-Stokes right-hand side; 1,296 tets, FP64, order 2:
-// 51.5 -> 47.8 us for an RK4 step).  With two to four tiles per CU the wider work items win
-// (FP64, order 4: 312 against 323 and 332 us; order 3, FP32: 76 against 92).
+// sixteen wavefronts with one column block each shorten it (608 elements,
+// order 2: 54.1 -> 52.6 us for a Navier-Stokes right-hand side with this in
+// the divergence stage and the interpolation; 1,296 tets, FP64, order 2: 51.5
+// -> 47.8 us for an RK4 step).  With two to four tiles per CU the wider work
+// items win (FP64, order 4: 312 against 323 and 332 us; order 3, FP32: 76
+// against 92).
 constexpr int64_t NARROW_TILES = 256;
 inline bool narrow_mesh(int64_t nelem) { return (nelem + 15) / 16 <= NARROW_TILES; }
 
-// Their kernels take the tiles of every element type in one launch (the
-// types' own launches would run one after the other, each with the chip
-// mostly idle and a launch's cost of its own): arguments by type, nelem 0
-// where a type is absent.
+// Their kernels take the tiles of every element type in one launch: the
+// types' own launches run one after the other, each with the chip mostly
+// idle and a launch's cost of its own (the 608 elements: 40.6 -> 26.0 us).
+// Arguments by type, nelem 0 where a type is absent.
 template <typename A>
 struct PerType {
     A a[3];
