@@ -175,14 +175,43 @@ __device__ __forceinline__ void store_c(T *C, int64_t ldc, int row, int64_t col,
     if constexpr (TAG % 4 == 3) {
         if (ep.fuse) {
             const int v = int(col / ep.ld);
-            const int64_t e0 = col - int64_t(v) * ep.ld, o0 = int64_t(row) * ldc + col;
-            if (update4_whole(ep, e0)) {
-                UpdateIn<T, V4> x;
-                update4_load(ep, row, e0, o0, x);
-                update4(ep, e0, o0, val, x);
-            } else {
-                update4_tail(ep, row, v, e0, o0, val);
+            const int64_t e0 = col - int64_t(v) * ep.ld;
+            const int64_t o0 = int64_t(row) * ldc + col;
+            if (e0 + 3 < ep.nelem && !ep.cy) {
+                // four whole elements: the same arithmetic as neg_update on
+                // 16-byte (FP32) / 32-byte (FP64) loads and stores
+                const V4 J = *reinterpret_cast<const V4 *>(ep.jinv + int64_t(row) * ep.ld + e0);
+                const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
+                V4 k;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    k[j] = -T(val[j]) * J[j];
+                    k[j] *= S[j];
+                }
+                if (ep.err) {
+                    V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) er[j] = er[j] + ep.c * k[j];
+                    *reinterpret_cast<V4 *>(ep.err + o0) = er;
+                }
+                V4 accv = V4{0, 0, 0, 0};
+                if (ep.acc) {
+                    accv = *reinterpret_cast<const V4 *>(ep.acc + o0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) accv[j] = accv[j] + ep.a * k[j];
+                    *reinterpret_cast<V4 *>(ep.acc + o0) = accv;
+                }
+                if (ep.out) {
+                    V4 o = ep.base ? *reinterpret_cast<const V4 *>(ep.base + o0) : accv;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o[j] = o[j] + ep.b * k[j];
+                    *reinterpret_cast<V4 *>(ep.out + o0) = o;
+                }
+                return;
             }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (e0 + j < ep.nelem) neg_update(ep, row, v, e0 + j, o0 + j, T(val[j]));
             return;
         }
     }
