@@ -1640,6 +1640,10 @@ struct fr_batch_s {
     std::vector<Prob> prob;
     hipStream_t stream = nullptr;             // stream the step graph replays on
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
+    // branches of the step graph: the groups' steps are independent (each
+    // group has its own buffers), and only capture uses these streams
+    hipStream_t branch[4] = {nullptr, nullptr, nullptr, nullptr};
+    hipEvent_t ev_fork = nullptr, ev_join[4] = {nullptr, nullptr, nullptr, nullptr};
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     // register pointers (group, type, register) the graph was captured with:
@@ -1653,6 +1657,11 @@ struct fr_batch_s {
         if (graph) (void)hipGraphDestroy(graph);
         if (ev_in) (void)hipEventDestroy(ev_in);
         if (ev_out) (void)hipEventDestroy(ev_out);
+        if (ev_fork) (void)hipEventDestroy(ev_fork);
+        for (int g = 0; g < 4; ++g) {
+            if (ev_join[g]) (void)hipEventDestroy(ev_join[g]);
+            if (branch[g]) (void)hipStreamDestroy(branch[g]);
+        }
         if (stream) (void)hipStreamDestroy(stream);
     }
 };
@@ -2163,6 +2172,12 @@ fr_status fr_batch_create(int32_t n, const fr_mesh_desc *descs, void *stream, fr
     FR_BHIP(nullptr, hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking));
     FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming));
     FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming));
+    FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
+    for (int g = 0; g < 4; ++g) {
+        if (!b->group[g]) continue;
+        FR_BHIP(nullptr, hipStreamCreateWithFlags(&b->branch[g], hipStreamNonBlocking));
+        FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_join[g], hipEventDisableTiming));
+    }
     *out = b.release();
     return FR_OK;
 }
@@ -2276,15 +2291,33 @@ fr_status fr_batch_rk_step(fr_batch b, int32_t scheme, int32_t n_steps, void *st
     if (scheme != FR_RK4 && scheme != FR_RK45_2RP && scheme != FR_FWD_EULER)
         return bfail(b, FR_ERR_INVALID_ARG, "unknown scheme");
     hipStream_t s = static_cast<hipStream_t>(stream);
+    auto step_group = [&](int g, hipStream_t st, int steps) -> fr_status {
+        fr_mesh m = b->group[g].get();
+        if (!m) return FR_OK;
+        fr_status r = m->precision != FR_FP64 ? rk_impl<float>(m, scheme, 1.0, steps, st, true, false)
+                                              : rk_impl<double>(m, scheme, 1.0, steps, st, true, false);
+        return r ? bfail(b, r, m->err) : FR_OK;
+    };
     auto step_all = [&](hipStream_t st, int steps) -> fr_status {
-        for (int g = 0; g < 4; ++g) {
-            fr_mesh m = b->group[g].get();
-            if (!m) continue;
-            fr_status r = m->precision != FR_FP64 ? rk_impl<float>(m, scheme, 1.0, steps, st, true, false)
-                                                  : rk_impl<double>(m, scheme, 1.0, steps, st, true, false);
-            if (r) return bfail(b, r, m->err);
-        }
+        for (int g = 0; g < 4; ++g)
+            if (fr_status r = step_group(g, st, steps)) return r;
         return FR_OK;
+    };
+    // In the graph the groups are parallel branches: one after the other, a
+    // sixth of a step was gaps between launches, and the ends of kernels no
+    // longer fill the chip (48 problems of 150 to 6,000 elements, orders 1 to
+    // 4, ten steps: 11.40 -> 8.54 ms).
+    auto capture_step = [&]() -> fr_status {
+        FR_BHIP(b, hipEventRecord(b->ev_fork, b->stream));
+        fr_status r = FR_OK;
+        for (int g = 0; g < 4; ++g) {
+            if (!b->group[g]) continue;
+            FR_BHIP(b, hipStreamWaitEvent(b->branch[g], b->ev_fork, 0));
+            if (!r) r = step_group(g, b->branch[g], 1);
+            FR_BHIP(b, hipEventRecord(b->ev_join[g], b->branch[g]));
+            FR_BHIP(b, hipStreamWaitEvent(b->stream, b->ev_join[g], 0));
+        }
+        return r;
     };
     // RK4 swaps its registers every step and cannot be replayed as one graph
     if (!b->use_graph || scheme != FR_RK45_2RP) return step_all(s, n_steps);
@@ -2308,7 +2341,7 @@ fr_status fr_batch_rk_step(fr_batch b, int32_t scheme, int32_t n_steps, void *st
     }
     if (!b->exec) {
         FR_BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-        fr_status r = step_all(b->stream, 1);
+        fr_status r = capture_step();
         hipGraph_t gph = nullptr;
         hipError_t e = hipStreamEndCapture(b->stream, &gph);
         if (r) {
