@@ -78,9 +78,9 @@ typedef enum { FR_RK4 = 0, FR_RK45_2RP = 1, FR_FWD_EULER = 2 } fr_scheme;
 #define FR_VALIDATE_ONLY 0x1u  /* build host-side tables only; no device work */
 #define FR_CHECK_FINITE 0x2u   /* fr_rk_step ends with a finiteness check */
 /* Run -R~/J and the RK register update as a kernel of their own after the
- * divergence product.  By default (every precision, no closure) they are
- * applied in the divergence product's store, so R~ is never written; both
- * orders of work give the same bits.  The autotuner times the divergence
+ * divergence product.  By default R~ is never written: in FP32 and FP64 the
+ * divergence stage on tiles of elements applies them, elsewhere (no closure)
+ * the divergence product's store; all orders of work give the same bits.  The autotuner times the divergence
  * products the way the right-hand side runs them. */
 #define FR_SEPARATE_UPDATE 0x4u
 /* Navier-Stokes in FP32 / FP64: run the corrected gradient
@@ -321,8 +321,10 @@ fr_status fr_profile_read(fr_mesh mesh, double *total_ms, int64_t *count);
 
 /* Operator-product autotuner: for every operator of every element type,
  * time the row-blocking candidates (16-row blocks per wavefront) on this
- * mesh's buffers and keep the fastest.  Results are bitwise unchanged (the
- * blocking does not change any output's accumulation order).  Synchronises
+ * mesh's buffers and keep the fastest; then, in FP32 and FP64, the kernels on
+ * tiles of elements against them (the interpolation, and a type's whole
+ * stage).  Results are bitwise unchanged (none changes any output's
+ * accumulation order).  Synchronises
  * the stream; the choice is reported by fr_last_error(mesh) on success. */
 fr_status fr_autotune(fr_mesh mesh, void *stream);
 
@@ -342,8 +344,9 @@ fr_status fr_autotune(fr_mesh mesh, void *stream);
  * gradient stage (FP32 and FP64; cap ignored): stage 0 the three separate
  * kernels, 1 one fused kernel per tile of elements, 2 (FP32 tets and
  * prisms) the fused kernel streaming runs of tiles with the next tile's
- * input loaded into LDS during the current one.  Results are bitwise the same for every
- * variant (for finite states).  Synchronous
+ * input loaded into LDS during the current one.  A forced op 0 or 3 takes
+ * that type's interpolation or divergence off the tile kernels.  Results are
+ * bitwise the same for every variant (for finite states).  Synchronous
  * (uploads the operator); FR_ERR_UNSUPPORTED for a combination the form
  * does not have. */
 fr_status fr_set_blocking(fr_mesh mesh, int32_t etype, int32_t op, int32_t cap, int32_t stage);
