@@ -296,7 +296,11 @@ fr_status fr_reduce_noalloc(fr_mesh mesh, int32_t what, double *out_host, void *
  *            it only on the faces whose gradient the common flux reads:
  *            boundary faces, and the sides of an interface whose LDG weight
  *            1/2 +- beta is not zero (with beta = 1/2 side L only); the
- *            other points keep what they held before. */
+ *            other points keep what they held before.  Where the gradient
+ *            operator has fewer than four 16-row blocks (tets up to order 2,
+ *            prisms and hexahedra of order 1) every point is written, unless
+ *            the form of the stage was chosen by fr_autotune or
+ *            fr_set_blocking. */
 fr_status fr_intermediate(fr_mesh mesh, int32_t etype, int32_t which, void *dst_dev,
                           void *stream);
 

@@ -66,6 +66,8 @@ struct DevType {
     // flux points are not written); fbit[s] = 1 << face of the flux point in
     // row slot s of Fgint (0 for padding slots)
     uint8_t *qmask = nullptr, *fbit = nullptr;
+    // every flux point is written until a form of the gradient stage is chosen
+    bool qf_all = false;
     // gradient stage form: 0 three kernels, 1 fused per tile, 2 fused and
     // streaming (FP32); set from the operator's size at setup, the autotuner
     // keeps the fastest
@@ -648,6 +650,13 @@ fr_status setup_device(fr_mesh m, hipStream_t s) {
             // 340 us.  Without the divergence stage on tiles it loses where
             // the gradient operator has fewer than four row blocks.
             D.grad_form = (D.tile && !(m->flags & FR_SEPARATE_UPDATE)) || D.Fgrad.nmg >= 4 ? 1 : 0;
+            // fewer than four row blocks (tets of orders 1 and 2, prisms and
+            // hexahedra of order 1): fr_intermediate promises the gradient at
+            // every flux point there, as the separate kernels leave it.  The
+            // stores that no kernel reads cost 55 MB of a right-hand side at
+            // order 1 with 129,024 elements, 130.5 -> 141.1 us (608 elements,
+            // order 2: 26.2 -> 26.3 us); a tuned mesh does without them.
+            D.qf_all = 3 * nu <= 48;
         }
         if (m->precision == FR_SPLIT_BF16 || m->precision == FR_SPLIT_FP16) {
             const int fmt = m->precision == FR_SPLIT_FP16 ? 2 : 1;
@@ -884,7 +893,7 @@ frd::GradFluxArgs<T> gradflux_args(fr_mesh m, const DevType<T> &D, const T *U) {
     ga.G = D.Fgrad;
     ga.M = D.Fgint;
     ga.V = D.Tvol;
-    ga.qmask = D.qmask;
+    ga.qmask = D.qf_all && !D.form_chosen ? nullptr : D.qmask;
     ga.fbit = D.fbit;
     return ga;
 }
@@ -1541,6 +1550,7 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         if (tile_ok) forms.push_back({ns ? 1 : 0, true, "tiles"});
         if (fused_ok && sizeof(T) == 4 && t < 2) forms.push_back({2, false, "streaming"});
         // (a forced interpolation product stays)
+        D.form_chosen = true;
         const T *U = D.reg[0];
         auto timed = [&](auto &&go, float &ms) -> hipError_t {
             hipError_t e = go();
@@ -1615,7 +1625,6 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
             report += std::string(" ") + forms[i].name + " " + std::to_string(ms / 3 * 1e3) + " us";
         }
         if (ns) D.grad_form = forms[best].grad;
-        D.form_chosen = true;
         D.tile = forms[best].tile;
         report += std::string(", ") + forms[best].name + "; ";
     }
