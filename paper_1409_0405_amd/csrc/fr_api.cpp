@@ -1046,7 +1046,17 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
                 } else {
                     FR_LAUNCH(m, prof_gradflux(t), s, frd::launch_gradflux<T>(t, ga[t], s, D.grad_form == 2));
                 }
+                continue;
             }
+            // (every type's gradient product comes before the first point-wise
+            // kernel: three kernels of one type in a row leave less of what
+            // the next type's product and the common flux read in the caches:
+            // 38,400 and 86,436 elements, order 4, BF16 parts, two RK45 steps:
+            // 4925 against 4915 us and 10,673 against 10,547 us, order 3, FP16
+            // parts: 6125 against 6058 us)
+            const int64_t w5 = 5 * D.ld;
+            FR_LAUNCH(m, prof_op(t, frd::OP_GRAD), s,
+                      opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U[t], w5, D.nu, D.Cf, w5, D.nf, D.Qt, w5, w5, s));
         }
         if (first >= 0) FR_LAUNCH(m, prof_gradflux(first), s, frd::launch_gradflux_small<T>(small, s));
     }
@@ -1054,17 +1064,13 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
         DevType<T> &D = d.t[t];
         if (!D.nelem) continue;
         if (fused[t] || tile[t]) continue;
-        // (a type's three kernels in a row: what one writes is in cache for
-        // the next)
-        const int64_t w5 = 5 * D.ld, w15 = 15 * D.ld;
-        if (ns)
-            FR_LAUNCH(m, prof_op(t, frd::OP_GRAD), s,
-                      opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U[t], w5, D.nu, D.Cf, w5, D.nf, D.Qt, w5, w5, s));
         const frd::UptsArgs<T> ua = upts_args<T>(m, D, U[t]);
         FR_LAUNCH(m, prof_upts(t), s, frd::launch_upts<T>(t, ns, ua, s));
-        if (ns)
+        if (ns) {
+            const int64_t w15 = 15 * D.ld;
             FR_LAUNCH(m, prof_op(t, frd::OP_GRADINTERP), s,
                       opmul<T>(m, 4 * t + frd::OP_GRADINTERP, D.Agint, D.Sgint, D.Q, w15, D.nu, nullptr, 0, 0, D.Qf, w15, w15, s));
+        }
     }
     FR_LAUNCH(m, 11, s, frd::launch_common_flux<T>(ns, pa, s));
     if (d.nb) FR_LAUNCH(m, 23, s, frd::launch_boundary_flux<T>(ns, ba, s));

@@ -1,0 +1,88 @@
+"""What the library's host code launches, on a machine without a GPU: libfr.so
+runs against a stand-in for the HIP runtime (hip_stand_in.cpp) that logs the
+kernels and gives each a time by its name.  Each scenario is a program of its
+own, so that the stand-in never meets a real runtime."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = textwrap.dedent("""
+    import ctypes, os, re, sys
+    import numpy as np
+    S = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+    S.stand_in_log.restype = ctypes.c_char_p
+    S.stand_in_cost.argtypes = [ctypes.c_char_p, ctypes.c_double]
+    from paper_1409_0405_amd import frlib, inputs
+
+    def costs(**us):
+        S.stand_in_clear()
+        for part, t in us.items():
+            S.stand_in_cost(part.encode(), t)
+
+    def log():
+        # [(device, blocks, kernel)] since the last costs()
+        rows = [l.split(" ", 2) for l in S.stand_in_log().decode().splitlines()]
+        return [(int(a), int(b), c) for a, b, c in rows]
+
+    def mixed(n=3):
+        return inputs.small_mixed_box(nxy=n, n_pri_layers=3, n_tet_layers=3, jitter=0.1, seed=2)
+
+    def buffers(m):
+        # 64-byte aligned host arrays as the states of every type
+        keep, out = [], []
+        for t in range(3):
+            q = m.query(t)
+            n = q["nupts"] * 5 * q["ld"] if q["nelem"] else 0
+            a = np.zeros(n + 16)
+            keep.append(a)
+            out.append((a.ctypes.data + 63) // 64 * 64 if n else 0)
+        return keep, out
+
+    def rhs(m):
+        (k1, u), (k2, r) = buffers(m), buffers(m)
+        m.rhs(u, r)
+""")
+
+
+@pytest.fixture(scope="session")
+def stand_in(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if not cxx:
+        pytest.skip("no host C++ compiler")
+    out = str(tmp_path_factory.mktemp("hip") / "hip_stand_in.so")
+    subprocess.run([cxx, "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "hip_stand_in.cpp"), "-o", out],
+                   check=True)
+    return out
+
+
+def _run(stand_in, body):
+    env = dict(os.environ, PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), stand_in], env=env,
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+@pytest.mark.parametrize("prec", ("split_bf16", "split_fp16"))
+def test_separate_gradient_kernels_run_stage_by_stage(stand_in, prec):
+    """The gradient products of every type come before the first point-wise
+    kernel: they share what the common solution just wrote in the caches."""
+    _run(stand_in, f"""
+        m = frlib.Mesh(mixed(), 4, system="ns", precision="{prec}", mu=0.02)
+        costs()
+        rhs(m)
+        kinds = []
+        for _, _, k in log():
+            tag = re.search(r"opmul_split\\w*kernelILi\\d+ELb[01]ELi(\\d+)E", k)
+            if tag and int(tag[1]) % 4 == 1:
+                kinds.append("gradient")
+            elif "upts_kernel" in k:
+                kinds.append("upts")
+        assert kinds == ["gradient", "gradient", "upts", "upts"], kinds
+    """)
