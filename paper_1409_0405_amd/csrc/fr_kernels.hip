@@ -163,20 +163,25 @@ __global__ __launch_bounds__(256) void common_flux_kernel(PairArgs<T> a) {
     }
     // gradients of the sides whose LDG weight is not zero, loaded together
     // with the states (beta = +-1/2, the usual choice, needs one side only:
-    // the other term would be an exact zero)
+    // the other term would be an exact zero).  One address per side: formed
+    // anew for each of the fifteen loads, a wide multiply shared a register
+    // pair with the load before it and waited for every load in flight
+    // (order 4, 9,261 hexahedra, FP32 state: 35.9 us, without that wait 33.0)
     const T wl = T(0.5) + a.beta, wr = T(0.5) - a.beta;
     T qL[3][5], qR[3][5];
     if (NS && wl != T(0)) {
+        const T *__restrict__ q = pick(a.Qf, tL) + (int64_t(fL) * 15 * ldL + eL);
 #pragma unroll
         for (int j = 0; j < 3; ++j)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) qL[j][v] = pick(a.Qf, tL)[(int64_t(fL) * 15 + j * 5 + v) * ldL + eL];
+            for (int v = 0; v < 5; ++v) qL[j][v] = q[(j * 5 + v) * ldL];
     }
     if (NS && wr != T(0)) {
+        const T *__restrict__ q = pick(a.Qf, tR) + (int64_t(fR) * 15 * ldR + eR);
 #pragma unroll
         for (int j = 0; j < 3; ++j)
 #pragma unroll
-            for (int v = 0; v < 5; ++v) qR[j][v] = pick(a.Qf, tR)[(int64_t(fR) * 15 + j * 5 + v) * ldR + eR];
+            for (int v = 0; v < 5; ++v) qR[j][v] = q[(j * 5 + v) * ldR];
     }
     T FL[3][5], FR[3][5], pL, pR;
     euler_flux(uL, a.gamma, a.pref, FL, pL);
