@@ -40,12 +40,14 @@ RIDGE = PEAK_FP32_MFMA / PEAK_HBM
 # (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000, the factors read off the state
 # copies of known size), keyed (kernel class, 16-row blocks per wavefront,
 # stage) for the products and (class, 0, 0) for the point-wise kernels and the
-# kernels on element tiles (the divergence stage per stage of a step); the file below holds the commands and counts.  A
-# variant not listed reports traffic null.
+# kernels on element tiles (the divergence stage per stage of a step; the
+# gradient stage that also forms the divergence's volume part is (class, 0, 1));
+# the file below holds the commands and counts.  A variant not listed reports
+# traffic null.
 TRAFFIC_SOURCE = "profiles/rhs_ns_p4_tgv_mixed_hbm_counters.md"
 MEASURED_TRAFFIC = {
-    ('gradflux_tet', 0, 0): 1018.2e6,
-    ('gradflux_pri', 0, 0): 1049.1e6,
+    ('gradflux_tet', 0, 1): 1018.2e6,
+    ('gradflux_pri', 0, 1): 1049.1e6,
     ('div_tet', 0, 0): 976.4e6,
     ('div_pri', 0, 0): 1082.4e6,
     ('interp_tet', 0, 0): 374.0e6,
@@ -158,6 +160,9 @@ def product_row_blocks(mesh, k):
 
 def variant_of(mesh, k, report):
     """(rows blocks per wavefront, stage) the autotuner chose for product k."""
+    op, _, name = k.partition("_")
+    if op == "gradflux" and name in TYPE_SHORT:
+        return 0, int(stage_form(report, TYPE_SHORT.index(name)) == "tiles")
     rb = product_row_blocks(mesh, k)
     if rb is None:
         return None

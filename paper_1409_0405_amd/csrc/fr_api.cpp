@@ -647,8 +647,11 @@ fr_status setup_device(fr_mesh m, hipStream_t s) {
             // mixed Taylor-Green meshes, FP32: order 1, 608 elements 42
             // against 54 us, 129,024 elements 140 against 182 us; order 2, 53
             // against 77 and 300 against 410 us; FP64, order 1, 320 against
-            // 340 us.  Without the divergence stage on tiles it loses where
-            // the gradient operator has fewer than four row blocks.
+            // 340 us; order 4, FP32, against the fused stage with the
+            // divergence product, 196,608 tets 845 against 877 us per stage
+            // of a step, 110,592 prisms 789 against 1,012 us.  Without the
+            // divergence stage on tiles it loses where the gradient operator
+            // has fewer than four row blocks.
             D.grad_form = (D.tile && !(m->flags & FR_SEPARATE_UPDATE)) || D.Fgrad.nmg >= 4 ? 1 : 0;
             // fewer than four row blocks (tets of orders 1 and 2, prisms and
             // hexahedra of order 1): fr_intermediate promises the gradient at
@@ -1539,9 +1542,13 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
                       std::to_string(best / 3 * 1e3) + " us; ";
         }
         // the whole stage of this type inside a time step, with the variants
-        // just chosen: separate kernels against the kernels on tiles (the
-        // fused gradient stage, Navier-Stokes, with the divergence stage;
-        // form 2: the streaming gradient stage, FP32 tets and prisms)
+        // just chosen: separate kernels, the fused gradient stage with the
+        // divergence product, both stages on tiles, and the streaming
+        // gradient stage (FP32 tets and prisms).  With tuned products the
+        // tets of large meshes are fastest with the divergence product at
+        // order 4 in FP32, whose dense operators gain least from the volume
+        // part (196,608 of them: 823 against 842 us); prisms and hexahedra
+        // are fastest on tiles
         if (!D.Fgint.frag) continue;
         const bool sep_update = (m->flags & FR_SEPARATE_UPDATE) != 0;
         const bool fused_ok = ns && D.Fgrad.frag && !(m->flags & FR_SEPARATE_GRADIENT);
@@ -1552,7 +1559,7 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
             const char *name;
         };
         std::vector<Form> forms = {{0, false, "separate"}};
-        if (fused_ok && !tile_ok) forms.push_back({1, false, "fused"});
+        if (fused_ok) forms.push_back({1, false, "fused"});
         if (tile_ok) forms.push_back({ns ? 1 : 0, true, "tiles"});
         if (fused_ok && sizeof(T) == 4 && t < 2) forms.push_back({2, false, "streaming"});
         // (a forced interpolation product stays)

@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <regex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -29,7 +30,7 @@ struct State {
     std::vector<Config> configs;
     std::map<const void *, std::string> names;           // host function -> kernel
     std::map<std::pair<int, const void *>, int> lds_limit;
-    std::vector<std::pair<std::string, double>> costs;   // part of a name, microseconds
+    std::vector<std::pair<std::regex, double>> costs;    // of the names that match, microseconds
     std::string log;                                     // "device grid name" per launch
     std::map<const void *, void *> symbols;
 };
@@ -43,7 +44,7 @@ constexpr int INVALID_VALUE = 1;
 extern "C" {
 // ---- control ----
 void stand_in_device(int d) { S().device = d; }
-void stand_in_cost(const char *part, double us) { S().costs.emplace_back(part, us); }
+void stand_in_cost(const char *name, double us) { S().costs.emplace_back(std::regex(name), us); }
 void stand_in_clear() {
     S().costs.clear();
     S().log.clear();
@@ -83,7 +84,7 @@ int hipLaunchKernel(const void *f, Dim3 grid, Dim3, void **, size_t lds, void *)
     s.log += std::to_string(s.device) + " " + std::to_string(grid.x) + " " + name + "\n";
     double us = 1;
     for (const auto &c : s.costs)
-        if (name.find(c.first) != std::string::npos) us += c.second;
+        if (std::regex_search(name, c.first)) us += c.second;
     s.clock += us;
     return 0;
 }

@@ -13,7 +13,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
-PRELUDE = textwrap.dedent("""
+PRELUDE = textwrap.dedent(r"""
     import ctypes, os, re, sys
     import numpy as np
     S = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
@@ -21,10 +21,14 @@ PRELUDE = textwrap.dedent("""
     S.stand_in_cost.argtypes = [ctypes.c_char_p, ctypes.c_double]
     from paper_1409_0405_amd import frlib, inputs
 
-    def costs(**us):
+    INTERP = r"opmul\w*kernelIf?Li[0-9]+ELi(0|4|8)E"    # products of tag 4 * type + operator
+    DIV = r"opmul\w*kernelIf?Li[0-9]+ELi(3|7|11)E"
+
+    def costs(us={}, **more):
+        # one microsecond per launch and these on top, by a part of the name
         S.stand_in_clear()
-        for part, t in us.items():
-            S.stand_in_cost(part.encode(), t)
+        for name, t in dict(us, **more).items():
+            S.stand_in_cost(name.encode(), t)
 
     def log():
         # [(device, blocks, kernel)] since the last costs()
@@ -86,3 +90,32 @@ def test_separate_gradient_kernels_run_stage_by_stage(stand_in, prec):
                 kinds.append("upts")
         assert kinds == ["gradient", "gradient", "upts", "upts"], kinds
     """)
+
+
+TUNED = """
+    def chosen(report, kind):
+        return re.search(kind + r" stage: [^;]*, (\\w+);", report)[1]
+
+    def step(m):
+        # the kernels of one step, after the first stage's interpolation
+        (k, u) = buffers(m)
+        for t in range(3):
+            if m.query(t)["nelem"]:
+                m.set_solution(t, u[t])
+        S.stand_in_clear()
+        m.rk_step(frlib.FR_RK45_2RP, 1e-3, 1)
+        return [k for _, _, k in log()]
+"""
+
+
+def test_autotuner_times_the_fused_gradient_stage_with_the_divergence_product(stand_in):
+    """Fused gradient stage without the volume part, divergence as a product:
+    the fastest form of large tetrahedral meshes at order 4."""
+    _run(stand_in, textwrap.dedent(TUNED) + textwrap.dedent("""
+        m = frlib.Mesh(mixed(), 4, system="ns", precision="fp32", mu=0.02)
+        costs(gradflux_small=50.0, gradflux_stream=50.0)
+        report = m.autotune()
+        assert chosen(report, "tet") == chosen(report, "pri") == "fused", report
+        ks = step(m)
+        assert any("gradflux_kernel" in k for k in ks) and not any("divtile" in k for k in ks), ks
+    """))
