@@ -349,7 +349,8 @@ fr_status fr_autotune(fr_mesh mesh, void *stream);
  * kernels, 1 one fused kernel per tile of elements, 2 (FP32 tets and
  * prisms) the fused kernel streaming runs of tiles with the next tile's
  * input loaded into LDS during the current one.  A forced op 0 or 3 takes
- * that type's interpolation or divergence off the tile kernels.  Results are
+ * that type's interpolation or divergence off the tile kernels; what is
+ * forced holds until the next fr_autotune, which compares everything again.  Results are
  * bitwise the same for every variant (for finite states).  Synchronous
  * (uploads the operator); FR_ERR_UNSUPPORTED for a combination the form
  * does not have. */

@@ -57,10 +57,11 @@ struct DevType {
     // [G'_0 G'_1 G'_2], and the divergence stage's operator (Euler
     // [G'_k | L], Navier-Stokes L)
     frd::Op<T> Fgrad, Fgint, Tvol, Tdiv;
-    // divergence stage on tiles (it fits a CU, and no product variant was
-    // forced); tile_interp: it also interpolates the next stage's input;
-    // interp_tile: a first stage's interpolation runs on tiles too
-    bool tile = false, tile_interp = true, interp_tile = true;
+    // divergence stage on tiles: it fits a CU (tile_fits); it is in use
+    // (tile: until the autotuner finds another form faster or a product
+    // variant is forced); tile_interp: it also interpolates the next stage's
+    // input; interp_tile: a first stage's interpolation runs on tiles too
+    bool tile_fits = false, tile = false, tile_interp = true, interp_tile = true;
     // fused gradient stage: bit f of qmask[e] is set when an interface or
     // boundary kernel reads the gradient on face f of element e (the other
     // flux points are not written); fbit[s] = 1 << face of the flux point in
@@ -634,7 +635,7 @@ fr_status setup_device(fr_mesh m, hipStream_t s) {
             ta.A = D.Tdiv;
             ta.nu = nu;
             ta.nf = nf;
-            D.tile = frd::divtile_supported<T>(t, ta, !ns);
+            D.tile = D.tile_fits = frd::divtile_supported<T>(t, ta, !ns);
         }
         if (ns && (m->precision == FR_FP32 || m->precision == FR_FP64)) {
             std::vector<int32_t> idx;
@@ -1552,7 +1553,7 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         if (!D.Fgint.frag) continue;
         const bool sep_update = (m->flags & FR_SEPARATE_UPDATE) != 0;
         const bool fused_ok = ns && D.Fgrad.frag && !(m->flags & FR_SEPARATE_GRADIENT);
-        const bool tile_ok = D.tile && !sep_update && (!ns || fused_ok);
+        const bool tile_ok = D.tile_fits && !sep_update && (!ns || fused_ok);
         struct Form {
             int grad;
             bool tile;
@@ -1562,8 +1563,10 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         if (fused_ok) forms.push_back({1, false, "fused"});
         if (tile_ok) forms.push_back({ns ? 1 : 0, true, "tiles"});
         if (fused_ok && sizeof(T) == 4 && t < 2) forms.push_back({2, false, "streaming"});
-        // (a forced interpolation product stays)
+        // (every form is compared again, whatever an earlier run chose or a
+        // caller forced: the products have been chosen anew as well)
         D.form_chosen = true;
+        D.tile_interp = true;
         const T *U = D.reg[0];
         auto timed = [&](auto &&go, float &ms) -> hipError_t {
             hipError_t e = go();
@@ -1574,7 +1577,7 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
             return e == hipSuccess ? hipEventElapsedTime(&ms, e0, e1) : e;
         };
         static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
-        if (D.tile_interp) {
+        {
             float product = 0, onto = 0;
             FR_HIP(m, timed([&] {
                 return opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U, w5, nu, nullptr, 0, 0, D.Uf, w5, w5, s);

@@ -119,3 +119,31 @@ def test_autotuner_times_the_fused_gradient_stage_with_the_divergence_product(st
         ks = step(m)
         assert any("gradflux_kernel" in k for k in ks) and not any("divtile" in k for k in ks), ks
     """))
+
+
+@pytest.mark.parametrize("system", ("ns", "euler"))
+def test_tuning_again_compares_everything_again(stand_in, system):
+    """A form that lost, or was switched off by a forced product, is back in
+    the next comparison."""
+    _run(stand_in, textwrap.dedent(TUNED) + textwrap.dedent(f"""
+        m = frlib.Mesh(mixed(), 3, system="{system}", precision="fp32", mu=0.02)
+
+        def tiles():
+            ks = step(m)
+            return [any("divtile" in k for k in ks), sum("interptile" in k or bool(re.search(INTERP, k)) for k in ks)]
+
+        costs(divtile=50.0)
+        assert chosen(m.autotune(), "tet") != "tiles" and not tiles()[0]
+        costs()
+        report = m.autotune()
+        assert chosen(report, "tet") == chosen(report, "pri") == "tiles", report
+        want = tiles()
+        assert want[0]
+        for op in (0, 3):
+            for t in (0, 1):
+                m.set_blocking(t, op, 2, 0)
+        assert not tiles()[0]
+        report = m.autotune()
+        assert chosen(report, "tet") == chosen(report, "pri") == "tiles", report
+        assert tiles() == want, (tiles(), want)
+    """))
