@@ -947,6 +947,176 @@ frd::UptsArgs<T> upts_args(fr_mesh m, const DevType<T> &D, const T *U) {
     return ua;
 }
 
+const Closure *attached_closure(fr_mesh m) {
+    return m->closure && m->closure->params ? m->closure.get() : nullptr;
+}
+
+// A right-hand side's kernels that work on one element type each, in three
+// parts for the types of the bit set `types` (the autotuner times them as a
+// step runs them).  Small meshes: one launch covers a part's kernel of every
+// type (with per-kernel timing on, one per type, so that each is timed by
+// itself).
+constexpr unsigned ALL_TYPES = (1u << frh::NTYPE) - 1;
+
+template <typename T>
+bool has_type(const DevType<T> &D, int t, unsigned types) {
+    return D.nelem && (types >> t & 1);
+}
+
+// Corrected gradient, point-wise work and gradient interpolation in one
+// kernel (FR_SEPARATE_GRADIENT: three).
+template <typename T>
+bool runs_fused(fr_mesh m, const DevType<T> &D) {
+    return m->system == FR_NAVIER_STOKES && D.nelem && D.Fgrad.frag && D.grad_form > 0 &&
+           !(m->flags & FR_SEPARATE_GRADIENT);
+}
+
+// The divergence stage on tiles: for Navier-Stokes it takes the volume part
+// from the fused gradient stage.
+template <typename T>
+bool runs_tiles(fr_mesh m, const DevType<T> &D) {
+    return D.nelem && D.tile && !(m->flags & FR_SEPARATE_UPDATE) &&
+           (m->system != FR_NAVIER_STOKES || (runs_fused(m, D) && D.grad_form == 1));
+}
+
+// U_f = M0 U.  uf[t] set: Uf of that type holds it already.
+template <typename T>
+fr_status interp_part(fr_mesh m, const T *const U[frh::NTYPE], unsigned types, hipStream_t s, const bool *uf) {
+    Dev<T> &d = dev_of<T>(m);
+    frd::InterpTileArgs<T> ia[frh::NTYPE];
+    const frd::InterpTileArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
+    int first = -1;
+    for (int t = 0; t < frh::NTYPE; ++t) {
+        DevType<T> &D = d.t[t];
+        if (!has_type(D, t, types) || (uf && uf[t]) || !D.Fgint.frag || !D.interp_tile) continue;
+        ia[t] = interptile_args<T>(D, U[t]);
+        if (!m->prof.on && frd::interptile_small<T>(ia[t])) {
+            small[t] = &ia[t];
+            if (first < 0) first = t;
+        } else {
+            FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s, frd::launch_interptile<T>(ia[t], s));
+        }
+    }
+    if (first >= 0) FR_LAUNCH(m, prof_op(first, frd::OP_INTERP), s, frd::launch_interptile_small<T>(small, s));
+    for (int t = 0; t < frh::NTYPE; ++t) {
+        DevType<T> &D = d.t[t];
+        if (!has_type(D, t, types) || (uf && uf[t]) || (D.Fgint.frag && D.interp_tile)) continue;
+        const int64_t w5 = 5 * D.ld;
+        FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
+                  opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U[t], w5, D.nu, nullptr, 0, 0, D.Uf, w5, w5, s));
+    }
+    return FR_OK;
+}
+
+// Gradient stage: the work between the common solution and the common flux.
+template <typename T>
+fr_status gradient_part(fr_mesh m, const T *const U[frh::NTYPE], unsigned types, hipStream_t s) {
+    Dev<T> &d = dev_of<T>(m);
+    const bool ns = m->system == FR_NAVIER_STOKES;
+    if (ns) {
+        frd::GradFluxArgs<T> ga[frh::NTYPE];
+        const frd::GradFluxArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
+        int first = -1;
+        for (int t = 0; t < frh::NTYPE; ++t) {
+            DevType<T> &D = d.t[t];
+            if (!has_type(D, t, types)) continue;
+            if (runs_fused(m, D)) {
+                ga[t] = gradflux_args<T>(m, D, U[t]);
+                if (runs_tiles(m, D)) ga[t].D = D.Ft;
+                if (!m->prof.on && frd::gradflux_small<T>(t, ga[t])) {
+                    small[t] = &ga[t];
+                    if (first < 0) first = t;
+                } else {
+                    FR_LAUNCH(m, prof_gradflux(t), s, frd::launch_gradflux<T>(t, ga[t], s, D.grad_form == 2));
+                }
+                continue;
+            }
+            // (every type's gradient product comes before the first point-wise
+            // kernel: three kernels of one type in a row leave less of what
+            // the next type's product and the common flux read in the caches:
+            // 38,400 and 86,436 elements, order 4, BF16 parts, two RK45 steps:
+            // 4925 against 4915 us and 10,673 against 10,547 us, order 3, FP16
+            // parts: 6125 against 6058 us)
+            const int64_t w5 = 5 * D.ld;
+            FR_LAUNCH(m, prof_op(t, frd::OP_GRAD), s,
+                      opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U[t], w5, D.nu, D.Cf, w5, D.nf, D.Qt, w5, w5, s));
+        }
+        if (first >= 0) FR_LAUNCH(m, prof_gradflux(first), s, frd::launch_gradflux_small<T>(small, s));
+    }
+    for (int t = 0; t < frh::NTYPE; ++t) {
+        DevType<T> &D = d.t[t];
+        if (!has_type(D, t, types) || runs_fused(m, D) || runs_tiles(m, D)) continue;
+        const frd::UptsArgs<T> ua = upts_args<T>(m, D, U[t]);
+        FR_LAUNCH(m, prof_upts(t), s, frd::launch_upts<T>(t, ns, ua, s));
+        if (ns) {
+            const int64_t w15 = 15 * D.ld;
+            FR_LAUNCH(m, prof_op(t, frd::OP_GRADINTERP), s,
+                      opmul<T>(m, 4 * t + frd::OP_GRADINTERP, D.Agint, D.Sgint, D.Q, w15, D.nu, nullptr, 0, 0, D.Qf, w15, w15, s));
+        }
+    }
+    return FR_OK;
+}
+
+// Divergence, -R~ / J and the register update.  next: another stage follows
+// on the state written; uf[t] (if given) is set where Uf then holds its
+// interpolation.
+template <typename T>
+fr_status divergence_part(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T> so[frh::NTYPE], unsigned types,
+                          hipStream_t s, bool *uf, bool next) {
+    Dev<T> &d = dev_of<T>(m);
+    const bool ns = m->system == FR_NAVIER_STOKES;
+    const Closure *cl = attached_closure(m);
+    frd::DivTileArgs<T> ta[frh::NTYPE];
+    const frd::DivTileArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
+    int first = -1;
+    for (int t = 0; t < frh::NTYPE; ++t) {
+        DevType<T> &D = d.t[t];
+        if (!has_type(D, t, types)) continue;
+        const bool tile = runs_tiles(m, D);
+        const int64_t w5 = 5 * D.ld;
+        frd::NegArgs<T> na{D.Rt, so[t].out, so[t].acc, so[t].base, so[t].a, so[t].b,
+                           D.jinv, D.ld, D.nelem, D.nu,
+                           so[t].per_elem_dt ? D.dte : nullptr};
+        na.err = so[t].err;
+        na.c = so[t].c;
+        na.err_set = so[t].err_set;
+        if (cl && t < 2) {
+            na.cy = cl->y;
+            na.cys = d.t[0].nelem + d.t[1].nelem;
+            na.clift = cl->lift[t];
+            na.goff = t ? d.t[0].nelem : 0;
+        }
+        if (uf) uf[t] = tile && D.tile_interp && next;
+        if (tile) {
+            ta[t] = divtile_args<T>(m, D, U[t]);
+            ta[t].ep = na;
+            if (uf && uf[t]) ta[t].Uf = D.Uf;
+            if (!m->prof.on && frd::divtile_small<T>(ta[t])) {
+                small[t] = &ta[t];
+                if (first < 0) first = t;
+            } else {
+                FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s, frd::launch_divtile<T>(t, !ns, ta[t], s));
+            }
+            continue;
+        }
+        // -R~/J and the register update ride in the divergence product's
+        // store (R~ never reaches memory) unless the closure or
+        // FR_SEPARATE_UPDATE asks for the separate kernel
+        if (!na.cy && !(m->flags & FR_SEPARATE_UPDATE)) {
+            na.fuse = true;
+            FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s,
+                      opmul<T>(m, 4 * t + frd::OP_DIV, D.Adiv, D.Sdiv, D.Ft, w5, 3 * D.nu, D.Fn, w5, D.nf, D.Rt, w5,
+                               w5, s, &na));
+            continue;
+        }
+        FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s,
+                  opmul<T>(m, 4 * t + frd::OP_DIV, D.Adiv, D.Sdiv, D.Ft, w5, 3 * D.nu, D.Fn, w5, D.nf, D.Rt, w5, w5, s));
+        FR_LAUNCH(m, prof_neg(t), s, frd::launch_negdivconf<T>(t, na, s));
+    }
+    if (first >= 0) FR_LAUNCH(m, prof_op(first, frd::OP_DIV), s, frd::launch_divtile_small<T>(!ns, small, s));
+    return FR_OK;
+}
+
 // uf: for a run of stages inside one call, per type whether Uf already holds
 // the interpolation of U[t] (in) and that of the state this stage writes
 // (out); next: whether another stage follows on that state.
@@ -956,34 +1126,7 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     Dev<T> &d = dev_of<T>(m);
     const bool ns = m->system == FR_NAVIER_STOKES;
     const T gamma = T(m->gamma), mu = T(m->mu), pr = T(m->prandtl);
-    // Small meshes: one launch covers a stage's kernel of every type (with
-    // per-kernel timing on, one per type, so that each is timed by itself)
-    const bool merge = !m->prof.on;
-    {
-        frd::InterpTileArgs<T> ia[frh::NTYPE];
-        const frd::InterpTileArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
-        int first = -1;
-        for (int t = 0; t < frh::NTYPE; ++t) {
-            DevType<T> &D = d.t[t];
-            if (!D.nelem || (uf && uf[t]) || !D.Fgint.frag || !D.interp_tile) continue;
-            ia[t] = interptile_args<T>(D, U[t]);
-            if (merge && frd::interptile_small<T>(ia[t])) {
-                small[t] = &ia[t];
-                if (first < 0) first = t;
-            } else {
-                FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s, frd::launch_interptile<T>(ia[t], s));
-            }
-        }
-        if (first >= 0)
-            FR_LAUNCH(m, prof_op(first, frd::OP_INTERP), s, frd::launch_interptile_small<T>(small, s));
-    }
-    for (int t = 0; t < frh::NTYPE; ++t) {
-        DevType<T> &D = d.t[t];
-        if (!D.nelem || (uf && uf[t]) || (D.Fgint.frag && D.interp_tile)) continue;
-        const int64_t w5 = 5 * D.ld;
-        FR_LAUNCH(m, prof_op(t, frd::OP_INTERP), s,
-                  opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U[t], w5, D.nu, nullptr, 0, 0, D.Uf, w5, w5, s));
-    }
+    if (fr_status st = interp_part<T>(m, U, ALL_TYPES, s, uf)) return st;
     frd::PairArgs<T> pa{};
     pa.sideL = d.sideL;
     pa.sideR = d.sideR;
@@ -1021,65 +1164,14 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
     ba.t_wall = T(m->t_wall);
     for (int k = 0; k < 5; ++k) ba.free[k] = T(m->farfield[k]);
     ba.pref = T(m->pref);
-    // Navier-Stokes tets and prisms: corrected gradient, point-wise work and
-    // gradient interpolation in one kernel (FR_SEPARATE_GRADIENT: three)
-    bool fused[frh::NTYPE] = {false, false, false}, tile[frh::NTYPE];
-    for (int t = 0; t < frh::NTYPE; ++t) {
-        fused[t] = ns && d.t[t].nelem && d.t[t].Fgrad.frag && d.t[t].grad_form > 0 &&
-                   !(m->flags & FR_SEPARATE_GRADIENT);
-        // the divergence stage on tiles: for Navier-Stokes it takes the
-        // volume part from the fused gradient stage
-        tile[t] = d.t[t].nelem && d.t[t].tile && !(m->flags & FR_SEPARATE_UPDATE) &&
-                  (!ns || (fused[t] && d.t[t].grad_form == 1));
-    }
     if (ns) {
         FR_LAUNCH(m, 10, s, frd::launch_common_solution<T>(pa, s));
         if (d.nb) FR_LAUNCH(m, 22, s, frd::launch_boundary_solution<T>(ba, s));
-        frd::GradFluxArgs<T> ga[frh::NTYPE];
-        const frd::GradFluxArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
-        int first = -1;
-        for (int t = 0; t < frh::NTYPE; ++t) {
-            DevType<T> &D = d.t[t];
-            if (!D.nelem) continue;
-            if (fused[t]) {
-                ga[t] = gradflux_args<T>(m, D, U[t]);
-                if (tile[t]) ga[t].D = D.Ft;
-                if (merge && frd::gradflux_small<T>(t, ga[t])) {
-                    small[t] = &ga[t];
-                    if (first < 0) first = t;
-                } else {
-                    FR_LAUNCH(m, prof_gradflux(t), s, frd::launch_gradflux<T>(t, ga[t], s, D.grad_form == 2));
-                }
-                continue;
-            }
-            // (every type's gradient product comes before the first point-wise
-            // kernel: three kernels of one type in a row leave less of what
-            // the next type's product and the common flux read in the caches:
-            // 38,400 and 86,436 elements, order 4, BF16 parts, two RK45 steps:
-            // 4925 against 4915 us and 10,673 against 10,547 us, order 3, FP16
-            // parts: 6125 against 6058 us)
-            const int64_t w5 = 5 * D.ld;
-            FR_LAUNCH(m, prof_op(t, frd::OP_GRAD), s,
-                      opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U[t], w5, D.nu, D.Cf, w5, D.nf, D.Qt, w5, w5, s));
-        }
-        if (first >= 0) FR_LAUNCH(m, prof_gradflux(first), s, frd::launch_gradflux_small<T>(small, s));
     }
-    for (int t = 0; t < frh::NTYPE; ++t) {
-        DevType<T> &D = d.t[t];
-        if (!D.nelem) continue;
-        if (fused[t] || tile[t]) continue;
-        const frd::UptsArgs<T> ua = upts_args<T>(m, D, U[t]);
-        FR_LAUNCH(m, prof_upts(t), s, frd::launch_upts<T>(t, ns, ua, s));
-        if (ns) {
-            const int64_t w15 = 15 * D.ld;
-            FR_LAUNCH(m, prof_op(t, frd::OP_GRADINTERP), s,
-                      opmul<T>(m, 4 * t + frd::OP_GRADINTERP, D.Agint, D.Sgint, D.Q, w15, D.nu, nullptr, 0, 0, D.Qf, w15, w15, s));
-        }
-    }
+    if (fr_status st = gradient_part<T>(m, U, ALL_TYPES, s)) return st;
     FR_LAUNCH(m, 11, s, frd::launch_common_flux<T>(ns, pa, s));
     if (d.nb) FR_LAUNCH(m, 23, s, frd::launch_boundary_flux<T>(ns, ba, s));
-    const Closure *cl = (m->closure && m->closure->params) ? m->closure.get() : nullptr;
-    if (cl) {
+    if (const Closure *cl = attached_closure(m)) {
         const int64_t ntot = d.t[0].nelem + d.t[1].nelem;
         for (int t = 0; t < 2; ++t) {   // the closure covers tets and prisms only
             DevType<T> &D = d.t[t];
@@ -1092,54 +1184,7 @@ fr_status rhs_pipeline(fr_mesh m, const T *const U[frh::NTYPE], const StageOut<T
         FR_LAUNCH(m, 15, s, frd::launch_mlp_forward(cl->params, cl->params_bf16, cl->bf16, cl->feat, 1, ntot, ntot,
                                                     cl->stats, false, cl->y, 1, ntot, s));
     }
-    frd::DivTileArgs<T> ta[frh::NTYPE];
-    const frd::DivTileArgs<T> *small[frh::NTYPE] = {nullptr, nullptr, nullptr};
-    int first = -1;
-    for (int t = 0; t < frh::NTYPE; ++t) {
-        DevType<T> &D = d.t[t];
-        if (!D.nelem) continue;
-        const int64_t w5 = 5 * D.ld;
-        frd::NegArgs<T> na{D.Rt, so[t].out, so[t].acc, so[t].base, so[t].a, so[t].b,
-                           D.jinv, D.ld, D.nelem, D.nu,
-                           so[t].per_elem_dt ? D.dte : nullptr};
-        na.err = so[t].err;
-        na.c = so[t].c;
-        na.err_set = so[t].err_set;
-        if (cl && t < 2) {
-            na.cy = cl->y;
-            na.cys = d.t[0].nelem + d.t[1].nelem;
-            na.clift = cl->lift[t];
-            na.goff = t ? d.t[0].nelem : 0;
-        }
-        if (uf) uf[t] = tile[t] && D.tile_interp && next;
-        if (tile[t]) {
-            ta[t] = divtile_args<T>(m, D, U[t]);
-            ta[t].ep = na;
-            if (uf && uf[t]) ta[t].Uf = D.Uf;
-            if (merge && frd::divtile_small<T>(ta[t])) {
-                small[t] = &ta[t];
-                if (first < 0) first = t;
-            } else {
-                FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s, frd::launch_divtile<T>(t, !ns, ta[t], s));
-            }
-            continue;
-        }
-        // -R~/J and the register update ride in the divergence product's
-        // store (R~ never reaches memory) unless the closure or
-        // FR_SEPARATE_UPDATE asks for the separate kernel
-        if (!na.cy && !(m->flags & FR_SEPARATE_UPDATE)) {
-            na.fuse = true;
-            FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s,
-                      opmul<T>(m, 4 * t + frd::OP_DIV, D.Adiv, D.Sdiv, D.Ft, w5, 3 * D.nu, D.Fn, w5, D.nf, D.Rt, w5,
-                               w5, s, &na));
-            continue;
-        }
-        FR_LAUNCH(m, prof_op(t, frd::OP_DIV), s,
-                  opmul<T>(m, 4 * t + frd::OP_DIV, D.Adiv, D.Sdiv, D.Ft, w5, 3 * D.nu, D.Fn, w5, D.nf, D.Rt, w5, w5, s));
-        FR_LAUNCH(m, prof_neg(t), s, frd::launch_negdivconf<T>(t, na, s));
-    }
-    if (first >= 0) FR_LAUNCH(m, prof_op(first, frd::OP_DIV), s, frd::launch_divtile_small<T>(!ns, small, s));
-    return FR_OK;
+    return divergence_part<T>(m, U, so, ALL_TYPES, s, uf, next);
 }
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -1413,6 +1458,13 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
     if (split) caps = fmt == 2 ? std::vector<int>{1, 2} : std::vector<int>{1, 2, 4};
     else caps = sizeof(T) == 4 ? std::vector<int>{1, 2, 4, 8} : std::vector<int>{1, 2, 4};
     fr_status st = FR_OK;
+    const T *const U[frh::NTYPE] = {d.t[0].reg[0], d.t[1].reg[0], d.t[2].reg[0]};
+    // what is timed here stays out of the caller's per-kernel timing
+    struct ProfilerOff {
+        bool &on, was;
+        explicit ProfilerOff(bool &x) : on(x), was(x) { x = false; }
+        ~ProfilerOff() { on = was; }
+    } profiler_off(m->prof.on);
     for (int t = 0; t < frh::NTYPE && !st; ++t) {
         DevType<T> &D = d.t[t];
         if (!D.nelem) continue;
@@ -1567,81 +1619,63 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         // caller forced: the products have been chosen anew as well)
         D.form_chosen = true;
         D.tile_interp = true;
-        const T *U = D.reg[0];
-        auto timed = [&](auto &&go, float &ms) -> hipError_t {
-            hipError_t e = go();
-            if (e == hipSuccess) e = hipEventRecord(e0, s);
-            for (int r = 0; r < 3 && e == hipSuccess; ++r) e = go();
-            if (e == hipSuccess) e = hipEventRecord(e1, s);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            return e == hipSuccess ? hipEventElapsedTime(&ms, e0, e1) : e;
+        auto timed = [&](auto &&go, float &ms) -> fr_status {
+            if (fr_status r = go()) return r;
+            FR_HIP(m, hipEventRecord(e0, s));
+            for (int r = 0; r < 3; ++r)
+                if (fr_status r2 = go()) return r2;
+            FR_HIP(m, hipEventRecord(e1, s));
+            FR_HIP(m, hipEventSynchronize(e1));
+            FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
+            return FR_OK;
         };
         static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
+        const unsigned self = 1u << t;
         {
-            float product = 0, onto = 0;
-            FR_HIP(m, timed([&] {
-                return opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U, w5, nu, nullptr, 0, 0, D.Uf, w5, w5, s);
-            }, product));
-            FR_HIP(m, timed([&] { return frd::launch_interptile<T>(interptile_args<T>(D, U), s); }, onto));
-            D.interp_tile = onto <= product;
-            report += sn[t] + std::string(" interp: product ") + std::to_string(product / 3 * 1e3) + " us tile " +
-                      std::to_string(onto / 3 * 1e3) + " us, " + (D.interp_tile ? "tile" : "product") + "; ";
+            float ms[2] = {0, 0};
+            for (int onto = 0; onto < 2; ++onto) {
+                D.interp_tile = onto;
+                if ((st = timed([&] { return interp_part<T>(m, U, self, s, nullptr); }, ms[onto]))) return st;
+            }
+            D.interp_tile = ms[1] <= ms[0];
+            report += sn[t] + std::string(" interp: product ") + std::to_string(ms[0] / 3 * 1e3) + " us tile " +
+                      std::to_string(ms[1] / 3 * 1e3) + " us, " + (D.interp_tile ? "tile" : "product") + "; ";
         }
         if (forms.size() == 1) continue;
-        frd::NegArgs<T> na{};
-        na.Rt = D.Rt;
-        na.out = D.R;
-        na.acc = D.Rt;
-        na.b = T(1);
-        na.jinv = D.jinv;
-        na.ld = D.ld;
-        na.nelem = D.nelem;
-        na.nu = nu;
-        auto run = [&](const Form &fm) -> hipError_t {
-            hipError_t e = hipSuccess;
-            const bool interp = !(fm.tile && D.tile_interp);
-            if (interp)
-                e = opmul<T>(m, 4 * t + frd::OP_INTERP, D.Aint, D.Sint, U, w5, nu, nullptr, 0, 0, D.Uf, w5, w5, s);
-            if (ns && fm.grad > 0) {
-                frd::GradFluxArgs<T> ga = gradflux_args<T>(m, D, U);
-                if (fm.tile) ga.D = D.Ft;
-                if (e == hipSuccess) e = frd::launch_gradflux<T>(t, ga, s, fm.grad == 2);
-            } else if (!fm.tile) {
-                if (ns && e == hipSuccess)
-                    e = opmul<T>(m, 4 * t + frd::OP_GRAD, D.Agrad, D.Sgrad, U, w5, nu, D.Cf, w5, nf, D.Qt, w5, w5, s);
-                if (e == hipSuccess) e = frd::launch_upts<T>(t, ns, upts_args<T>(m, D, U), s);
-                if (ns && e == hipSuccess)
-                    e = opmul<T>(m, 4 * t + frd::OP_GRADINTERP, D.Agint, D.Sgint, D.Q, w15, nu, nullptr, 0, 0, D.Qf,
-                                 w15, w15, s);
-            }
-            if (e != hipSuccess) return e;
-            if (fm.tile) {
-                frd::DivTileArgs<T> ta = divtile_args<T>(m, D, U);
-                ta.ep = na;
-                ta.Uf = D.tile_interp ? D.Uf : nullptr;
-                return frd::launch_divtile<T>(t, !ns, ta, s);
-            }
-            frd::NegArgs<T> nf_ = na;
-            nf_.fuse = !sep_update;
-            e = opmul<T>(m, 4 * t + frd::OP_DIV, D.Adiv, D.Sdiv, D.Ft, w5, 3 * nu, D.Fn, w5, nf, D.Rt, w5, w5, s,
-                         sep_update ? nullptr : &nf_);
-            if (e == hipSuccess && sep_update) e = frd::launch_negdivconf<T>(t, na, s);
-            return e;
+        // a stage in the middle of a step, as the pipeline runs it with the
+        // form in force (and the closure attached, if one is)
+        auto use = [&](const Form &fm) {
+            if (ns) D.grad_form = fm.grad;
+            D.tile = fm.tile;
+        };
+        const Form was = {D.grad_form, D.tile, ""};
+        auto stage = [&]() -> fr_status {
+            StageOut<T> so[frh::NTYPE];
+            so[t].out = D.R;
+            so[t].acc = D.Rt;
+            bool uf[frh::NTYPE] = {};
+            uf[t] = runs_tiles(m, D) && D.tile_interp;
+            if (fr_status r = interp_part<T>(m, U, self, s, uf)) return r;
+            if (fr_status r = gradient_part<T>(m, U, self, s)) return r;
+            return divergence_part<T>(m, U, so, self, s, uf, true);
         };
         size_t best = 0;
         float best_ms = 1e30f;
         report += sn[t] + std::string(" stage:");
         for (size_t i = 0; i < forms.size(); ++i) {
             float ms = 0;
-            FR_HIP(m, timed([&] { return run(forms[i]); }, ms));
+            use(forms[i]);
+            if ((st = timed(stage, ms))) {
+                use(was);
+                return st;
+            }
             if (ms < best_ms) {
                 best_ms = ms;
                 best = i;
             }
             report += std::string(" ") + forms[i].name + " " + std::to_string(ms / 3 * 1e3) + " us";
         }
-        if (ns) D.grad_form = forms[best].grad;
-        D.tile = forms[best].tile;
+        use(forms[best]);
         report += std::string(", ") + forms[best].name + "; ";
     }
     (void)hipEventDestroy(e0);

@@ -147,3 +147,45 @@ def test_tuning_again_compares_everything_again(stand_in, system):
         assert chosen(report, "tet") == chosen(report, "pri") == "tiles", report
         assert tiles() == want, (tiles(), want)
     """))
+
+
+def test_forms_are_timed_with_the_interpolation_that_runs(stand_in):
+    """The forms without the divergence stage on tiles interpolate every
+    stage's input: on tiles where that was found faster."""
+    _run(stand_in, textwrap.dedent(TUNED) + textwrap.dedent("""
+        m = frlib.Mesh(mixed(), 3, system="ns", precision="fp32", mu=0.02)
+        costs({INTERP: 100.0}, divtile=20.0)
+        report = m.autotune()
+        for kind in ("tet", "pri"):
+            assert re.search(kind + r" interp: [^;]*, tile;", report), report
+            assert chosen(report, kind) == "fused", report
+        assert not any(re.search(INTERP, k) for k in step(m))
+    """))
+
+
+def test_forms_are_timed_with_the_attached_closure(stand_in):
+    """With the closure the divergence product is followed by the update
+    kernel; the divergence stage on tiles applies the correction itself."""
+    _run(stand_in, textwrap.dedent(TUNED) + textwrap.dedent("""
+        m = frlib.Mesh(mixed(), 1, system="ns", precision="fp32", mu=0.02)
+        net = frlib.MLP(0)
+        stats = np.ones(280, np.float32)
+        m.closure_attach(net, stats.ctypes.data)
+        costs(negdivconf=100.0, divtile=20.0)
+        report = m.autotune()
+        assert chosen(report, "tet") == chosen(report, "pri") == "tiles", report
+        m.closure_attach(None)
+        report = m.autotune()
+        assert chosen(report, "tet") == chosen(report, "pri") == "fused", report
+    """))
+
+
+def test_tuning_stays_out_of_the_per_kernel_timing(stand_in):
+    _run(stand_in, """
+        m = frlib.Mesh(mixed(), 2, system="ns", precision="fp32", mu=0.02)
+        m.profile(True)
+        rhs(m)
+        m.autotune()
+        counts = {k: n for k, (_, n) in m.profile_read().items() if n}
+        assert counts["common_flux"] == counts["gradflux_tet"] == counts["div_pri"] == 1, counts
+    """)
