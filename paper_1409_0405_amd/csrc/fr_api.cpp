@@ -1465,6 +1465,44 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         explicit ProfilerOff(bool &x) : on(x), was(x) { x = false; }
         ~ProfilerOff() { on = was; }
     } profiler_off(m->prof.on);
+    static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
+    auto timed = [&](auto &&go, float &ms) -> fr_status {
+        if (fr_status r = go()) return r;
+        FR_HIP(m, hipEventRecord(e0, s));
+        for (int r = 0; r < 3; ++r)
+            if (fr_status r2 = go()) return r2;
+        FR_HIP(m, hipEventRecord(e1, s));
+        FR_HIP(m, hipEventSynchronize(e1));
+        FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
+        return FR_OK;
+    };
+    // the stage of some types in the middle of a step, as the pipeline runs it
+    // with the forms in force (and the closure attached, if one is)
+    auto stage = [&](unsigned types) -> fr_status {
+        StageOut<T> so[frh::NTYPE];
+        bool uf[frh::NTYPE] = {};
+        for (int t = 0; t < frh::NTYPE; ++t) {
+            so[t].out = d.t[t].R;
+            so[t].acc = d.t[t].Rt;
+            uf[t] = runs_tiles(m, d.t[t]) && d.t[t].tile_interp;
+        }
+        if (fr_status r = interp_part<T>(m, U, types, s, uf)) return r;
+        if (fr_status r = gradient_part<T>(m, U, types, s)) return r;
+        return divergence_part<T>(m, U, so, types, s, uf, true);
+    };
+    struct Form {
+        int grad;
+        bool tile;
+        const char *name;
+    };
+    auto use = [&](int t, const Form &fm) {
+        if (ns) d.t[t].grad_form = fm.grad;
+        d.t[t].tile = fm.tile;
+    };
+    const Form tiles = {ns ? 1 : 0, true, "tiles"};
+    std::string interp_text[frh::NTYPE], stage_text[frh::NTYPE];
+    Form kept[frh::NTYPE] = {};
+    unsigned small = 0;                   // types whose tiles share a launch
     for (int t = 0; t < frh::NTYPE && !st; ++t) {
         DevType<T> &D = d.t[t];
         if (!D.nelem) continue;
@@ -1606,30 +1644,14 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         const bool sep_update = (m->flags & FR_SEPARATE_UPDATE) != 0;
         const bool fused_ok = ns && D.Fgrad.frag && !(m->flags & FR_SEPARATE_GRADIENT);
         const bool tile_ok = D.tile_fits && !sep_update && (!ns || fused_ok);
-        struct Form {
-            int grad;
-            bool tile;
-            const char *name;
-        };
         std::vector<Form> forms = {{0, false, "separate"}};
         if (fused_ok) forms.push_back({1, false, "fused"});
-        if (tile_ok) forms.push_back({ns ? 1 : 0, true, "tiles"});
+        if (tile_ok) forms.push_back(tiles);
         if (fused_ok && sizeof(T) == 4 && t < 2) forms.push_back({2, false, "streaming"});
         // (every form is compared again, whatever an earlier run chose or a
         // caller forced: the products have been chosen anew as well)
         D.form_chosen = true;
         D.tile_interp = true;
-        auto timed = [&](auto &&go, float &ms) -> fr_status {
-            if (fr_status r = go()) return r;
-            FR_HIP(m, hipEventRecord(e0, s));
-            for (int r = 0; r < 3; ++r)
-                if (fr_status r2 = go()) return r2;
-            FR_HIP(m, hipEventRecord(e1, s));
-            FR_HIP(m, hipEventSynchronize(e1));
-            FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
-            return FR_OK;
-        };
-        static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
         const unsigned self = 1u << t;
         {
             float ms[2] = {0, 0};
@@ -1638,45 +1660,81 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
                 if ((st = timed([&] { return interp_part<T>(m, U, self, s, nullptr); }, ms[onto]))) return st;
             }
             D.interp_tile = ms[1] <= ms[0];
-            report += sn[t] + std::string(" interp: product ") + std::to_string(ms[0] / 3 * 1e3) + " us tile " +
-                      std::to_string(ms[1] / 3 * 1e3) + " us, " + (D.interp_tile ? "tile" : "product") + "; ";
+            interp_text[t] = sn[t] + std::string(" interp: product ") + std::to_string(ms[0] / 3 * 1e3) +
+                             " us tile " + std::to_string(ms[1] / 3 * 1e3) + " us";
         }
         if (forms.size() == 1) continue;
-        // a stage in the middle of a step, as the pipeline runs it with the
-        // form in force (and the closure attached, if one is)
-        auto use = [&](const Form &fm) {
-            if (ns) D.grad_form = fm.grad;
-            D.tile = fm.tile;
-        };
         const Form was = {D.grad_form, D.tile, ""};
-        auto stage = [&]() -> fr_status {
-            StageOut<T> so[frh::NTYPE];
-            so[t].out = D.R;
-            so[t].acc = D.Rt;
-            bool uf[frh::NTYPE] = {};
-            uf[t] = runs_tiles(m, D) && D.tile_interp;
-            if (fr_status r = interp_part<T>(m, U, self, s, uf)) return r;
-            if (fr_status r = gradient_part<T>(m, U, self, s)) return r;
-            return divergence_part<T>(m, U, so, self, s, uf, true);
-        };
         size_t best = 0;
         float best_ms = 1e30f;
-        report += sn[t] + std::string(" stage:");
+        stage_text[t] = sn[t] + std::string(" stage:");
         for (size_t i = 0; i < forms.size(); ++i) {
             float ms = 0;
-            use(forms[i]);
-            if ((st = timed(stage, ms))) {
-                use(was);
+            use(t, forms[i]);
+            if ((st = timed([&] { return stage(self); }, ms))) {
+                use(t, was);
                 return st;
             }
             if (ms < best_ms) {
                 best_ms = ms;
                 best = i;
             }
-            report += std::string(" ") + forms[i].name + " " + std::to_string(ms / 3 * 1e3) + " us";
+            stage_text[t] += std::string(" ") + forms[i].name + " " + std::to_string(ms / 3 * 1e3) + " us";
         }
-        use(forms[best]);
-        report += std::string(", ") + forms[best].name + "; ";
+        kept[t] = forms[best];
+        use(t, kept[t]);
+        if (tile_ok) {
+            frd::GradFluxArgs<T> ga = gradflux_args<T>(m, D, U[t]);
+            ga.D = D.Ft;
+            if (frd::interptile_small<T>(interptile_args<T>(D, U[t])) &&
+                frd::divtile_small<T>(divtile_args<T>(m, D, U[t])) && (!ns || frd::gradflux_small<T>(t, ga)))
+                small |= 1u << t;
+        }
+    }
+    // Small meshes run the tiles of every type in one launch, which no type
+    // alone shows: the choices made type by type against tiles for all
+    if (!st && (small & (small - 1))) {
+        bool changed = false, product = false;
+        for (int t = 0; t < frh::NTYPE; ++t) {
+            if (!(small >> t & 1)) continue;
+            changed = changed || !kept[t].tile;
+            product = product || !d.t[t].interp_tile;
+        }
+        auto together = [&](bool wanted, auto &&part, auto &&all, auto &&back) -> fr_status {
+            if (!wanted) return FR_OK;
+            float ms[2] = {0, 0};
+            fr_status r = timed(part, ms[0]);
+            all();
+            if (!r) r = timed(part, ms[1]);
+            if (r || ms[1] > ms[0]) back();
+            return r;
+        };
+        bool was[frh::NTYPE];
+        for (int t = 0; t < frh::NTYPE; ++t) was[t] = d.t[t].interp_tile;
+        st = together(product, [&] { return interp_part<T>(m, U, small, s, nullptr); },
+                      [&] {
+                          for (int t = 0; t < frh::NTYPE; ++t)
+                              if (small >> t & 1) d.t[t].interp_tile = true;
+                      },
+                      [&] {
+                          for (int t = 0; t < frh::NTYPE; ++t) d.t[t].interp_tile = was[t];
+                      });
+        Form chosen[frh::NTYPE] = {kept[0], kept[1], kept[2]};
+        if (!st)
+            st = together(changed, [&] { return stage(small); },
+                          [&] {
+                              for (int t = 0; t < frh::NTYPE; ++t)
+                                  if (small >> t & 1) use(t, kept[t] = tiles);
+                          },
+                          [&] {
+                              for (int t = 0; t < frh::NTYPE; ++t)
+                                  if (small >> t & 1) use(t, kept[t] = chosen[t]);
+                          });
+        if (st) return st;
+    }
+    for (int t = 0; t < frh::NTYPE; ++t) {
+        if (!interp_text[t].empty()) report += interp_text[t] + ", " + (d.t[t].interp_tile ? "tile" : "product") + "; ";
+        if (!stage_text[t].empty()) report += stage_text[t] + ", " + kept[t].name + "; ";
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -189,3 +189,22 @@ def test_tuning_stays_out_of_the_per_kernel_timing(stand_in):
         counts = {k: n for k, (_, n) in m.profile_read().items() if n}
         assert counts["common_flux"] == counts["gradflux_tet"] == counts["div_pri"] == 1, counts
     """)
+
+
+def test_small_meshes_are_tuned_as_they_run(stand_in):
+    """The tiles of every type share a launch on a small mesh: cheaper than
+    the sum of the types alone, and than their fastest forms alone."""
+    _run(stand_in, textwrap.dedent(TUNED) + textwrap.dedent("""
+        m = frlib.Mesh(mixed(), 3, system="ns", precision="fp32", mu=0.02)
+        # a type alone: tiles 6 + 2, fused 1 + 1 + 3 (+ the interpolation's 1);
+        # both types: tiles 6 + 2 in all, fused twice 6
+        costs({DIV: 2.0}, gradflux_small=5.0, gradflux_stream=50.0, divtile=1.0)
+        report = m.autotune()
+        assert chosen(report, "tet") == chosen(report, "pri") == "tiles", report
+        ks = step(m)
+        assert any("divtile_small" in k for k in ks) and not any(re.search(DIV, k) for k in ks), ks
+        # and not where it costs more
+        costs({DIV: 2.0}, gradflux_small=20.0, gradflux_stream=50.0, divtile=1.0)
+        report = m.autotune()
+        assert chosen(report, "tet") == chosen(report, "pri") == "fused", report
+    """))
