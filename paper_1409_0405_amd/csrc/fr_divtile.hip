@@ -329,20 +329,11 @@ int divtile_elems(int etype, const DivTileArgs<T> &a, bool euler) {
     return divtile_bytes(etype, a, euler, 16) <= TILE_LDS_MAX ? 16 : 0;
 }
 
-template <typename K>
-hipError_t allow_lds(K *kernel, bool &set) {
-    if (set) return hipSuccess;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
-    set = e == hipSuccess;
-    return e;
-}
-
 template <typename T, int ET, int NE, int NBI, int NW, int MI, bool EULER>
 hipError_t launch_dt(const DivTileArgs<T> &a, hipStream_t s) {
-    static bool set = false;
+    static LdsLimit limit;
     const auto kernel = divtile_kernel<T, ET, NE, NBI, NW, MI, EULER>;
-    if (hipError_t e = allow_lds(kernel, set); e != hipSuccess) return e;
+    if (hipError_t e = limit.raise(kernel); e != hipSuccess) return e;
     kernel<<<xcd_grid((a.nelem + NE - 1) / NE), 64 * NW, divtile_bytes(ET, a, EULER, NE), s>>>(a);
     return hipGetLastError();
 }
@@ -384,17 +375,17 @@ hipError_t launch_dt_et(const DivTileArgs<T> &a, hipStream_t s) {
 
 template <typename T, int NE, int NBI, int NW>
 hipError_t launch_it(const InterpTileArgs<T> &a, hipStream_t s) {
-    static bool set = false;
+    static LdsLimit limit;
     const auto kernel = interptile_kernel<T, NE, NBI, NW>;
-    if (hipError_t e = allow_lds(kernel, set); e != hipSuccess) return e;
+    if (hipError_t e = limit.raise(kernel); e != hipSuccess) return e;
     kernel<<<xcd_grid((a.nelem + NE - 1) / NE), 64 * NW, tile_bytes<T>(a.nu, NE), s>>>(a);
     return hipGetLastError();
 }
 
 // Launch of a small-mesh kernel over the tiles of the types present.
 template <typename K, typename A, typename Bytes>
-hipError_t launch_small(K *kernel, bool &set, const A *const a[3], Bytes bytes, hipStream_t s) {
-    if (hipError_t e = allow_lds(kernel, set); e != hipSuccess) return e;
+hipError_t launch_small(K *kernel, LdsLimit &limit, const A *const a[3], Bytes bytes, hipStream_t s) {
+    if (hipError_t e = limit.raise(kernel); e != hipSuccess) return e;
     PerType<A> p;
     size_t lds = 0;
     int64_t ntiles = 0;
@@ -411,8 +402,8 @@ hipError_t launch_small(K *kernel, bool &set, const A *const a[3], Bytes bytes, 
 
 template <typename T, int MI, bool EULER>
 hipError_t launch_dt_small(const DivTileArgs<T> *const a[3], hipStream_t s) {
-    static bool set = false;
-    return launch_small(divtile_small_kernel<T, MI, EULER>, set, a,
+    static LdsLimit limit;
+    return launch_small(divtile_small_kernel<T, MI, EULER>, limit, a,
                         [&](int t) { return divtile_bytes(t, *a[t], EULER, 16); }, s);
 }
 
@@ -473,11 +464,11 @@ bool interptile_small(const InterpTileArgs<T> &a) {
 
 template <typename T>
 hipError_t launch_interptile_small(const InterpTileArgs<T> *const a[3], hipStream_t s) {
-    static bool set = false;
+    static LdsLimit limit;
     for (int t = 0; t < 3; ++t)
         if (a[t] && (!valid_args(*a[t]) || !interptile_small(*a[t]) || tile_bytes<T>(a[t]->nu, 16) > TILE_LDS_MAX))
             return hipErrorInvalidValue;
-    return launch_small(interptile_small_kernel<T>, set, a, [&](int t) { return tile_bytes<T>(a[t]->nu, 16); }, s);
+    return launch_small(interptile_small_kernel<T>, limit, a, [&](int t) { return tile_bytes<T>(a[t]->nu, 16); }, s);
 }
 
 template <typename T>

@@ -534,16 +534,11 @@ size_t gradflux_bytes(const GradFluxArgs<T> &a) {
 
 template <typename T, int ET, int NE, int GH, int NBI, int NW, int MG, bool VD>
 hipError_t launch_gf_mg(const GradFluxArgs<T> &a, hipStream_t s) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_kernel<T, ET, NE, GH, NBI, NW, MG, VD>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    const auto kernel = gradflux_kernel<T, ET, NE, GH, NBI, NW, MG, VD>;
+    if (hipError_t e = limit.raise(kernel); e != hipSuccess) return e;
     const int64_t ntiles = (a.nelem + NE - 1) / NE;
-    gradflux_kernel<T, ET, NE, GH, NBI, NW, MG, VD>
-        <<<xcd_grid(ntiles), 64 * NW, gradflux_bytes<T, ET, NE>(a), s>>>(a);
+    kernel<<<xcd_grid(ntiles), 64 * NW, gradflux_bytes<T, ET, NE>(a), s>>>(a);
     return hipGetLastError();
 }
 
@@ -598,17 +593,12 @@ size_t gradflux_stream_lds_bytes(int etype, const GradFluxArgs<float> &a) {
 
 template <int ET, int NW>
 hipError_t launch_gf_stream(const GradFluxArgs<float> &a, size_t lds, hipStream_t s) {
-    static bool attr_set = false;
-    static int ncu = 0;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_stream_kernel<ET, NW>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
-        if (e != hipSuccess) return e;
-        int dev = 0;
-        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-        if ((e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    hipError_t e = limit.raise(gradflux_stream_kernel<ET, NW>);
+    int dev = 0, ncu = 0;
+    if (e == hipSuccess) e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
     // as many workgroups as fit at once (LDS-bound), each a contiguous run of tiles
     const int per_cu = std::max(1, int(TILE_LDS_MAX / lds));
     const int64_t ntiles = (a.nelem + 15) / 16;
@@ -653,13 +643,8 @@ size_t gradflux_small_bytes(int etype, const GradFluxArgs<T> &a) {
 
 template <typename T, int MG>
 hipError_t launch_gf_small(const PerType<GradFluxArgs<T>> &p, int64_t ntiles, size_t lds, hipStream_t s) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(gradflux_small_kernel<T, MG>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    if (hipError_t e = limit.raise(gradflux_small_kernel<T, MG>); e != hipSuccess) return e;
     gradflux_small_kernel<T, MG><<<unsigned(ntiles), 64 * small_waves<T>(), lds, s>>>(p);
     return hipGetLastError();
 }

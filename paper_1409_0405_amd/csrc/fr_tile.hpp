@@ -5,6 +5,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "fr_device.hpp"
@@ -191,6 +192,25 @@ __device__ __forceinline__ void tile_to_lds(const T *src, int64_t ld, int64_t e0
 }
 
 constexpr size_t TILE_LDS_MAX = 160 * 1024;   // LDS of a CU
+
+// Raises a kernel's limit on dynamic LDS to a CU's on its first use on each
+// device (the limit belongs to the device; threads that meet here raise it
+// twice, which changes nothing).  One static object per kernel.
+class LdsLimit {
+    std::atomic<uint64_t> raised{0};          // by device, the first 64
+public:
+    template <typename K>
+    hipError_t raise(K *kernel) {
+        int dev = 0;
+        if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+        const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
+        if (raised.load(std::memory_order_relaxed) & bit) return hipSuccess;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(TILE_LDS_MAX));
+        if (e == hipSuccess) raised.fetch_or(bit, std::memory_order_relaxed);
+        return e;
+    }
+};
 
 // Small meshes, at most one tile of 16 elements per CU: no second workgroup
 // fills a CU's waits, so the tile's own chain of steps is what counts, and

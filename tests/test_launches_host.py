@@ -208,3 +208,27 @@ def test_small_meshes_are_tuned_as_they_run(stand_in):
         report = m.autotune()
         assert chosen(report, "tet") == chosen(report, "pri") == "fused", report
     """))
+
+
+@pytest.mark.parametrize("box,order,system,prec", [("mixed(3)", 4, "ns", "fp32"), ("mixed(3)", 4, "ns", "fp64"),
+                                                   ("mixed(16)", 4, "ns", "fp32"), ("inputs.hex_box(4)", 4, "euler", "fp32"),
+                                                   ("inputs.hex_box(4)", 4, "ns", "fp64"),
+                                                   ("inputs.hex_box(17)", 4, "ns", "fp32"),
+                                                   ("inputs.hex_box(17)", 3, "euler", "fp64")])
+def test_every_device_of_a_process_gets_the_lds_limit(stand_in, box, order, system, prec):
+    """A kernel's limit on dynamic LDS belongs to the device that it was
+    raised on: meshes on two devices, in turn."""
+    _run(stand_in, f"""
+        box = {box}
+        for device in (0, 1, 0, 2):
+            S.stand_in_device(device)
+            m = frlib.Mesh(box, {order}, system="{system}", precision="{prec}", mu=0.02)
+            costs()
+            rhs(m)
+            assert {{d for d, _, _ in log()}} == {{device}}
+            if "{system}" == "ns" and "{prec}" == "fp32" and m.query(0)["nelem"]:
+                for t in (0, 1):
+                    m.set_gradient_form(t, 2)
+                rhs(m)
+            m.close()
+    """)
