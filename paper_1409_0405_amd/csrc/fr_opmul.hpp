@@ -70,13 +70,19 @@ __device__ __forceinline__ unsigned xcd_block() {
 }
 inline unsigned xcd_grid(int64_t nblocks) { return unsigned((nblocks + 7) / 8 * 8); }
 
+// a b + c, rounded once.  The last pipeline step writes its multiply-adds out
+// (where the compiler may choose, it can choose differently in two kernels).
+template <typename T>
+__device__ __forceinline__ T muladd(T a, T b, T c) { return __builtin_elementwise_fma(a, b, c); }
+
 // The last pipeline step at one (solution point i, field v, element e), with
 // o = (5 i + v) ld + e: k = -r / J (plus the learned closure's lifted
 // correction), times the element's step size, into the error, accumulator
-// and output registers (frd::NegArgs).  negdivconf_kernel, the fused store
-// of the divergence products and the divergence stage on tiles all go through
-// it, so they give the same bits.  Returns the value left in the output
-// register (the accumulator's where there is no output).
+// and output registers (frd::NegArgs).  negdivconf_kernel and the ragged ends
+// of the other kernels go through it, whole groups of four elements through
+// update4_apply below; both are the same operations, so every kernel gives
+// the same bits.  Returns the value left in the output register (the
+// accumulator's where there is no output).
 template <typename T>
 __device__ __forceinline__ T neg_update(const NegArgs<T> &a, int i, int v, int64_t e, int64_t o,
                                         T r) {
@@ -86,35 +92,71 @@ __device__ __forceinline__ T neg_update(const NegArgs<T> &a, int i, int v, int64
     if (a.cy) {
         const float *y = a.cy + (a.goff + e) + int64_t(v) * 4 * a.cys;
         const float *l = a.clift + i * 4;
-        k += T(l[0] * y[0] + l[1] * y[a.cys] + l[2] * y[2 * a.cys] + l[3] * y[3 * a.cys]);
+        const float c = muladd(l[3], y[3 * a.cys], muladd(l[2], y[2 * a.cys], muladd(l[1], y[a.cys], l[0] * y[0])));
+        k = muladd(-r, Jinv, T(c));
     }
     k *= sc;
-    if (a.err) a.err[o] = (a.err_set ? T(0) : a.err[o]) + a.c * k;
+    if (a.err) a.err[o] = muladd(a.c, k, a.err_set ? T(0) : a.err[o]);
     T accv = 0;
     if (a.acc) {
-        accv = a.acc[o] + a.a * k;
+        accv = muladd(a.a, k, a.acc[o]);
         a.acc[o] = accv;
     }
     if (!a.out) return accv;
-    const T outv = (a.base ? a.base[o] : accv) + a.b * k;
+    const T outv = muladd(a.b, k, a.base ? a.base[o] : accv);
     a.out[o] = outv;
     return outv;
 }
 
-// What neg_update reads for the four consecutive elements e0 .. e0 + 3 of
-// solution point i and field v (o0 = (5 i + v) ld + e0), on 16-byte (FP32) /
-// 32-byte (FP64) loads, so that a kernel can issue them long before the
-// product they are combined with is there.  The register pointers are
-// 4-element aligned (checked at entry).
-template <typename T, typename V4>
-struct UpdateIn {
-    V4 J, acc, base;
-};
-// Whether the four elements go through update4 (else element by element).
+// Whether the four consecutive elements e0 .. e0 + 3 go through update4 (else
+// element by element).
 template <typename T>
 __device__ __forceinline__ bool update4_whole(const NegArgs<T> &ep, int64_t e0) {
     return e0 + 3 < ep.nelem && !ep.cy;
 }
+// The operations of neg_update on four consecutive elements of solution point
+// i and field v (o0 = (5 i + v) ld + e0), with 16-byte (FP32) / 32-byte (FP64)
+// accesses: J = 1 / J there, acc() and base() the values of those registers
+// (called only where they are set).  The register pointers are 4-element
+// aligned (checked at entry).  Returns the values left in the output register
+// (the accumulator where there is no output).
+template <typename T, typename V4, typename Acc, typename Base>
+__device__ __forceinline__ V4 update4_apply(const NegArgs<T> &ep, int64_t e0, int64_t o0, const V4 &val, const V4 &J,
+                                            Acc acc, Base base) {
+    V4 res = V4{0, 0, 0, 0}, k;
+    const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        k[j] = -T(val[j]) * J[j];
+        k[j] *= S[j];
+    }
+    if (ep.err) {
+        V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) er[j] = muladd(ep.c, T(k[j]), T(er[j]));
+        *reinterpret_cast<V4 *>(ep.err + o0) = er;
+    }
+    if (ep.acc) {
+        res = acc();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) res[j] = muladd(ep.a, T(k[j]), T(res[j]));
+        *reinterpret_cast<V4 *>(ep.acc + o0) = res;
+    }
+    if (ep.out) {
+        if (ep.base) res = base();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) res[j] = muladd(ep.b, T(k[j]), T(res[j]));
+        *reinterpret_cast<V4 *>(ep.out + o0) = res;
+    }
+    return res;
+}
+
+// With what it reads loaded ahead, long before the product it is combined
+// with is there.
+template <typename T, typename V4>
+struct UpdateIn {
+    V4 J, acc, base;
+};
 template <typename T, typename V4>
 __device__ __forceinline__ void update4_load(const NegArgs<T> &ep, int i, int64_t e0, int64_t o0,
                                              UpdateIn<T, V4> &x) {
@@ -122,37 +164,10 @@ __device__ __forceinline__ void update4_load(const NegArgs<T> &ep, int i, int64_
     if (ep.acc) x.acc = *reinterpret_cast<const V4 *>(ep.acc + o0);
     if (ep.out && ep.base) x.base = *reinterpret_cast<const V4 *>(ep.base + o0);
 }
-// The arithmetic of neg_update on them (the step sizes of a batch and the
-// error register of the adaptive scheme are read here).  Returns the values
-// left in the output register (the accumulator where there is no output).
 template <typename T, typename V4>
 __device__ __forceinline__ V4 update4(const NegArgs<T> &ep, int64_t e0, int64_t o0, const V4 &val,
                                       const UpdateIn<T, V4> &x) {
-    V4 res = V4{0, 0, 0, 0}, k;
-    const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        k[j] = -T(val[j]) * x.J[j];
-        k[j] *= S[j];
-    }
-    if (ep.err) {
-        V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) er[j] = er[j] + ep.c * k[j];
-        *reinterpret_cast<V4 *>(ep.err + o0) = er;
-    }
-    if (ep.acc) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) res[j] = x.acc[j] + ep.a * k[j];
-        *reinterpret_cast<V4 *>(ep.acc + o0) = res;
-    }
-    if (ep.out) {
-        if (ep.base) res = x.base;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) res[j] = res[j] + ep.b * k[j];
-        *reinterpret_cast<V4 *>(ep.out + o0) = res;
-    }
-    return res;
+    return update4_apply(ep, e0, o0, val, x.J, [&] { return x.acc; }, [&] { return x.base; });
 }
 // The same element by element; elements past nelem are skipped.
 template <typename T, typename V4>
@@ -177,36 +192,14 @@ __device__ __forceinline__ void store_c(T *C, int64_t ldc, int row, int64_t col,
             const int v = int(col / ep.ld);
             const int64_t e0 = col - int64_t(v) * ep.ld;
             const int64_t o0 = int64_t(row) * ldc + col;
-            if (e0 + 3 < ep.nelem && !ep.cy) {
-                // four whole elements: the same arithmetic as neg_update on
-                // 16-byte (FP32) / 32-byte (FP64) loads and stores
+            if (update4_whole(ep, e0)) {
+                // (each register is read where it is needed: loaded ahead they
+                // cost the products registers, 281 -> 285 us for a right-hand
+                // side of 26,586 elements in FP16 parts)
                 const V4 J = *reinterpret_cast<const V4 *>(ep.jinv + int64_t(row) * ep.ld + e0);
-                const V4 S = ep.dte ? *reinterpret_cast<const V4 *>(ep.dte + e0) : V4{1, 1, 1, 1};
-                V4 k;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    k[j] = -T(val[j]) * J[j];
-                    k[j] *= S[j];
-                }
-                if (ep.err) {
-                    V4 er = ep.err_set ? V4{0, 0, 0, 0} : *reinterpret_cast<const V4 *>(ep.err + o0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) er[j] = er[j] + ep.c * k[j];
-                    *reinterpret_cast<V4 *>(ep.err + o0) = er;
-                }
-                V4 accv = V4{0, 0, 0, 0};
-                if (ep.acc) {
-                    accv = *reinterpret_cast<const V4 *>(ep.acc + o0);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) accv[j] = accv[j] + ep.a * k[j];
-                    *reinterpret_cast<V4 *>(ep.acc + o0) = accv;
-                }
-                if (ep.out) {
-                    V4 o = ep.base ? *reinterpret_cast<const V4 *>(ep.base + o0) : accv;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) o[j] = o[j] + ep.b * k[j];
-                    *reinterpret_cast<V4 *>(ep.out + o0) = o;
-                }
+                update4_apply(
+                    ep, e0, o0, val, J, [&] { return *reinterpret_cast<const V4 *>(ep.acc + o0); },
+                    [&] { return *reinterpret_cast<const V4 *>(ep.base + o0); });
                 return;
             }
 #pragma unroll
