@@ -80,8 +80,8 @@ typedef enum { FR_RK4 = 0, FR_RK45_2RP = 1, FR_FWD_EULER = 2 } fr_scheme;
 /* Run -R~/J and the RK register update as a kernel of their own after the
  * divergence product.  By default R~ is never written: in FP32 and FP64 the
  * divergence stage on tiles of elements applies them, elsewhere (no closure)
- * the divergence product's store; all orders of work give the same bits.  The autotuner times the divergence
- * products the way the right-hand side runs them. */
+ * the divergence product's store; all orders of work give the same bits.  The
+ * autotuner times every form the way the right-hand side runs it. */
 #define FR_SEPARATE_UPDATE 0x4u
 /* Navier-Stokes in FP32 / FP64: run the corrected gradient
  * product, the solution-point work (physical gradient, transformed flux) and
@@ -318,16 +318,25 @@ fr_status fr_intermediate(fr_mesh mesh, int32_t etype, int32_t which, void *dst_
  * network forward; hexahedra: 16 + op the products, 20 the solution-point
  * kernel, 21 negdivconf; 22 boundary states, 23 boundary flux; 24 + etype
  * the fused gradient stage of tets, prisms and hexahedra (corrected
- * gradient, point-wise work and gradient interpolation in one kernel). */
+ * gradient, point-wise work and gradient interpolation in one kernel).  The
+ * kernels on tiles of elements count under the class of the work they are
+ * named after: the fused gradient stage may form the volume part of the
+ * divergence, the divergence class then adds the correction, the update and,
+ * inside a step, the next stage's interpolation.  While timing is on, small
+ * meshes run one launch per type instead of one for all. */
 #define FR_PROF_NCLASS 27
 fr_status fr_profile(fr_mesh mesh, int32_t enable);
 fr_status fr_profile_read(fr_mesh mesh, double *total_ms, int64_t *count);
 
 /* Operator-product autotuner: for every operator of every element type,
  * time the row-blocking candidates (16-row blocks per wavefront) on this
- * mesh's buffers and keep the fastest; then, in FP32 and FP64, the kernels on
- * tiles of elements against them (the interpolation, and a type's whole
- * stage).  Results are bitwise unchanged (none changes any output's
+ * mesh's buffers and keep the fastest; then, in FP32 and FP64, the
+ * interpolation on tiles of elements against its product, and the forms of a
+ * type's whole stage inside a step: separate kernels, the fused gradient stage
+ * with the divergence product, both stages on tiles, and the streaming
+ * gradient stage.  Small meshes, which run the tiles of all types in one
+ * launch, are then compared as a whole.  A later call compares everything
+ * again.  Results are bitwise unchanged (none changes any output's
  * accumulation order).  Synchronises
  * the stream; the choice is reported by fr_last_error(mesh) on success. */
 fr_status fr_autotune(fr_mesh mesh, void *stream);
@@ -349,9 +358,11 @@ fr_status fr_autotune(fr_mesh mesh, void *stream);
  * kernels, 1 one fused kernel per tile of elements, 2 (FP32 tets and
  * prisms) the fused kernel streaming runs of tiles with the next tile's
  * input loaded into LDS during the current one.  A forced op 0 or 3 takes
- * that type's interpolation or divergence off the tile kernels; what is
- * forced holds until the next fr_autotune, which compares everything again.  Results are
- * bitwise the same for every variant (for finite states).  Synchronous
+ * that type's interpolation or divergence off the tile kernels.  Where the
+ * gradient operator has fewer than four 16-row blocks, a forced op 1, 2 or 3
+ * also returns a type whose form was not chosen to the three separate
+ * gradient kernels.  What is forced holds until the next fr_autotune.  Results
+ * are bitwise the same for every variant (for finite states).  Synchronous
  * (uploads the operator); FR_ERR_UNSUPPORTED for a combination the form
  * does not have. */
 fr_status fr_set_blocking(fr_mesh mesh, int32_t etype, int32_t op, int32_t cap, int32_t stage);

@@ -12,7 +12,8 @@
 //      fused gradient stage has left it in memory as D, five values per point
 //      instead of fifteen, and the sums start from it;
 //   2. the common normal flux Fn -> LDS, Rt = volume part + L Fn -> LDS;
-//   3. -Rt / J and the Runge-Kutta register update on 16-byte rows;
+//   3. -Rt / J and the Runge-Kutta register update on 16-byte rows (element
+//      by element where the learned closure adds its correction);
 //   4. inside a time step, U_f = M0 r of the state r just written (the next
 //      stage's input, still in LDS) -> memory, so the next stage needs no
 //      interpolation kernel.
@@ -23,7 +24,8 @@
 // What bounds it: memory.  At p = 4, FP32, Navier-Stokes inside a step, 196,608
 // tets take 264 us and 110,592 prisms 294 us, about 4 TB/s of the arrays named
 // above (the card copies at 4.9); the separate divergence and interpolation
-// products took 231 + 85 and 342 + 131 us and had Ft, three times D, to read.
+// products take 246 + 90 and 360 + 111 us and have Ft, three times D, to read.
+// What the volume part costs in the gradient stage is told there.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -18,11 +18,11 @@
 //      matrix cores -> memory: five values per point for the divergence
 //      stage to read instead of the fifteen of Ft.
 // Without the divergence stage on tiles (FR_SEPARATE_UPDATE, a forced
-// divergence product, the streaming form) Ft goes to memory in step 3 and the
-// kernel ends with step 4.  The operators are walked
-// in the K order of the product kernels (gathered layout, below), and the
-// point-wise arithmetic is the shared one, so every value has the bits of the
-// separate kernels.
+// divergence product, the streaming form, or the autotuner found the
+// divergence product faster) Ft goes to memory in step 3 and the kernel ends
+// with step 4.  The operators are walked in the K order of the product kernels
+// (gathered layout, below), and the point-wise arithmetic is the shared one,
+// so every value has the bits of the separate kernels.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -78,11 +78,14 @@ constexpr int tile_elems() { return (ET == 2 ? 16 : 32) * 4 / int(sizeof(T)); }
 // instead of Ft: Q stays in LDS until it is interpolated, then Ft takes its
 // place (phase 5) and is multiplied there (phase 6).
 // What bounds it (p = 4, FP32, 196,608 tets and 110,592 prisms: 571 and 492
-// us with the volume part, 571 + 264 and 492 + 294 us with the divergence
-// stage, against 467 + 231 + 85 and 518 + 342 + 131 us with Ft in memory and
-// separate divergence and interpolation products): the matrix cores, busy 44
-// per cent of the time for tets, and the waits between the phases; the interpolation's and phase 6's first operator steps
-// and row numbers are loaded one phase ahead (tets 595 -> 571 us).
+// us with the volume part): the matrix cores, busy 44 per cent of the time for
+// tets, and the waits between the phases; the interpolation's and phase 6's
+// first operator steps and row numbers are loaded one phase ahead (tets 595 ->
+// 571 us).  With the divergence stage, inside a step, 571 + 264 and 492 + 294
+// us; without the volume part and with the fastest divergence and
+// interpolation products 466 + 246 + 90 and 397 + 360 + 111 us: the dense
+// operators of tets make the volume part dear, so the autotuner takes the
+// products for them there, and tiles for prisms.
 template <typename T, int ET, int NE, int GH, int NBI, int NW, int MG, bool VD>
 __device__ __forceinline__ void gradflux(const GradFluxArgs<T> a, int64_t e0, unsigned char *lds_raw) {
     using v4 = typename Vec4<T>::type;
@@ -631,8 +634,7 @@ bool valid_args(const GradFluxArgs<T> &a) {
     return gathered(a.G, 3 * a.nu) && gathered(a.M, a.nf) && (!a.D || gathered(a.V, a.nu)) && a.ld % 64 == 0 &&
            a.nelem <= a.ld &&
            (reinterpret_cast<uintptr_t>(a.U) | reinterpret_cast<uintptr_t>(a.Cf) |
-            reinterpret_cast<uintptr_t>(a.geom)) % 16 == 0 &&
-           reinterpret_cast<uintptr_t>(a.xi) % 4 == 0;   // 16- and 4-byte direct loads into LDS
+            reinterpret_cast<uintptr_t>(a.geom)) % 16 == 0;   // 16-byte direct loads into LDS
 }
 
 template <typename T>

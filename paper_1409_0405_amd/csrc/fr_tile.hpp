@@ -1,6 +1,6 @@
 // Building blocks of the kernels that keep a tile of elements in LDS (the
 // fused gradient stage and the divergence stage): direct loads into LDS and
-// products of a step-list operator with a tile.
+// products of a gathered operator with a tile.
 // Internal header (not part of the C ABI).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -35,13 +35,10 @@ __device__ __forceinline__ void unrolled(F &&f) {
     }
 }
 
-// 16 (4) bytes from memory straight into LDS (global_load_lds): lane l of
-// the wavefront writes dst + 16 l (dst + 4 l), dst uniform in the wavefront.
+// 16 bytes from memory straight into LDS (global_load_lds): lane l of the
+// wavefront writes dst + 16 l, dst uniform in the wavefront.
 __device__ __forceinline__ void load_lds16(const void *src, void *dst) {
     __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
-}
-__device__ __forceinline__ void load_lds4(const void *src, void *dst) {
-    __builtin_amdgcn_global_load_lds(src, dst, 4, 0, 0);
 }
 
 // One lane's share of a step of a gathered operator (Op stage 7): its
