@@ -46,6 +46,8 @@ RIDGE = PEAK_FP32_MFMA / PEAK_HBM
 # traffic null.
 TRAFFIC_SOURCE = "profiles/rhs_ns_p4_tgv_mixed_hbm_counters.md"
 MEASURED_TRAFFIC = {
+    ('gradflux_tet', 0, 0): 1153.2e6,
+    ('gradflux_pri', 0, 0): 1257.6e6,
     ('gradflux_tet', 0, 1): 1018.2e6,
     ('gradflux_pri', 0, 1): 1049.1e6,
     ('div_tet', 0, 0): 976.4e6,
@@ -58,7 +60,7 @@ MEASURED_TRAFFIC = {
     ('interp_tet', 4, 0): 373.8e6,
     ('interp_tet', 2, 0): 373.7e6,
     ('div_tet', 1, 3): 995.2e6,
-    ('div_tet', 1, 1): 1037.2e6,
+    ('div_tet', 1, 1): 1172.8e6,
     ('div_pri', 1, 6): 1208.7e6,
     ('common_flux', 0, 0): 1966.5e6,
     ('common_solution', 0, 0): 795.9e6,
