@@ -335,8 +335,9 @@ fr_status fr_profile_read(fr_mesh mesh, double *total_ms, int64_t *count);
  * type's whole stage inside a step: separate kernels, the fused gradient stage
  * with the divergence product, both stages on tiles, and the streaming
  * gradient stage.  Small meshes, which run the tiles of all types in one
- * launch, are then compared as a whole.  A later call compares everything
- * again.  Results are bitwise unchanged (none changes any output's
+ * launch, are then compared as a whole, and product variants within a tenth of
+ * each other are decided by the time of the whole stage.  A later call compares
+ * everything again.  Results are bitwise unchanged (none changes any output's
  * accumulation order).  Synchronises
  * the stream; the choice is reported by fr_last_error(mesh) on success. */
 fr_status fr_autotune(fr_mesh mesh, void *stream);

@@ -31,6 +31,8 @@ struct State {
     std::map<const void *, std::string> names;           // host function -> kernel
     std::map<std::pair<int, const void *>, int> lds_limit;
     std::vector<std::pair<std::regex, double>> costs;    // of the names that match, microseconds
+    std::vector<std::pair<std::regex, double>> cold;     // and after another kernel (caches)
+    const void *last = nullptr;
     std::string log;                                     // "device grid name" per launch
     std::map<const void *, void *> symbols;
 };
@@ -45,8 +47,10 @@ extern "C" {
 // ---- control ----
 void stand_in_device(int d) { S().device = d; }
 void stand_in_cost(const char *name, double us) { S().costs.emplace_back(std::regex(name), us); }
+void stand_in_cold(const char *name, double us) { S().cold.emplace_back(std::regex(name), us); }
 void stand_in_clear() {
     S().costs.clear();
+    S().cold.clear();
     S().log.clear();
 }
 const char *stand_in_log() { return S().log.c_str(); }
@@ -85,6 +89,10 @@ int hipLaunchKernel(const void *f, Dim3 grid, Dim3, void **, size_t lds, void *)
     double us = 1;
     for (const auto &c : s.costs)
         if (std::regex_search(name, c.first)) us += c.second;
+    if (f != s.last)
+        for (const auto &c : s.cold)
+            if (std::regex_search(name, c.first)) us += c.second;
+    s.last = f;
     s.clock += us;
     return 0;
 }

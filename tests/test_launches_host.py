@@ -18,11 +18,11 @@ PRELUDE = textwrap.dedent(r"""
     import numpy as np
     S = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
     S.stand_in_log.restype = ctypes.c_char_p
-    S.stand_in_cost.argtypes = [ctypes.c_char_p, ctypes.c_double]
+    S.stand_in_cost.argtypes = S.stand_in_cold.argtypes = [ctypes.c_char_p, ctypes.c_double]
     from paper_1409_0405_amd import frlib, inputs
 
-    INTERP = r"opmul\w*kernelIf?Li[0-9]+ELi(0|4|8)E"    # products of tag 4 * type + operator
-    DIV = r"opmul\w*kernelIf?Li[0-9]+ELi(3|7|11)E"
+    INTERP = r"opmul\w*kernelIf?Li[0-9]+E(Lb[01]E)?Li(0|4|8)E"    # products of tag 4 * type + operator
+    DIV = r"opmul\w*kernelIf?Li[0-9]+E(Lb[01]E)?Li(3|7|11)E"
 
     def costs(us={}, **more):
         # one microsecond per launch and these on top, by a part of the name
@@ -232,3 +232,19 @@ def test_every_device_of_a_process_gets_the_lds_limit(stand_in, box, order, syst
                 rhs(m)
             m.close()
     """)
+
+
+def test_products_that_tie_alone_are_decided_by_the_stage(stand_in):
+    """A variant that is a little slower on its own, where its input is in the
+    caches, and faster behind the kernels of a stage."""
+    _run(stand_in, textwrap.dedent(TUNED) + textwrap.dedent("""
+        m = frlib.Mesh(mixed(), 4, system="ns", precision="split_bf16", mu=0.02)
+        costs({r"opmul_split_kernel": 0.05, r"opmul_split_lds_kernel": 0.0})
+        S.stand_in_cold(DIV.replace("w*", "w*lds_").encode(), 3.0)
+        report = m.autotune()
+        for kind in ("tet", "pri"):
+            assert re.search(kind + r" op3 cap \\d stage 0", report), report
+            assert re.search(kind + r" op1 cap \\d stage 1", report), report
+        ks = [k for k in step(m) if re.search(DIV, k)]
+        assert ks and not any("lds" in k for k in ks), ks
+    """))
