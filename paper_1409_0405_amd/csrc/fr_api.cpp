@@ -1466,14 +1466,22 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
         ~ProfilerOff() { on = was; }
     } profiler_off(m->prof.on);
     static const char *const sn[frh::NTYPE] = {"tet", "pri", "hex"};
+    // three runs of go, after one.  Event times are corrected from the GPU's
+    // clock to the host's now and then, and a pair taken around a correction
+    // can be too close or the wrong way round: such a time is taken again, and
+    // if it stays so nothing is made of it
     auto timed = [&](auto &&go, float &ms) -> fr_status {
         if (fr_status r = go()) return r;
-        FR_HIP(m, hipEventRecord(e0, s));
-        for (int r = 0; r < 3; ++r)
-            if (fr_status r2 = go()) return r2;
-        FR_HIP(m, hipEventRecord(e1, s));
-        FR_HIP(m, hipEventSynchronize(e1));
-        FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
+        ms = 0;
+        for (int attempt = 0; attempt < 3 && !(ms > 0); ++attempt) {
+            FR_HIP(m, hipEventRecord(e0, s));
+            for (int r = 0; r < 3; ++r)
+                if (fr_status r2 = go()) return r2;
+            FR_HIP(m, hipEventRecord(e1, s));
+            FR_HIP(m, hipEventSynchronize(e1));
+            FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
+        }
+        if (!(ms > 0)) ms = 1e30f;
         return FR_OK;
     };
     // a stage in the middle of a step, as the pipeline runs it with the forms
@@ -1620,26 +1628,24 @@ fr_status autotune_impl(fr_mesh m, hipStream_t s, std::string &report) {
                 na.fuse = true;
                 const frd::NegArgs<T> *ep =
                     c.op == frd::OP_DIV && !(m->flags & FR_SEPARATE_UPDATE) ? &na : nullptr;
-                auto run = [&]() -> hipError_t {
+                auto run = [&]() -> fr_status {
                     if constexpr (std::is_same<T, float>::value) {
-                        if (split)
-                            return frd::launch_opmul_split(4 * t + c.op, sop, c.B1, c.l1, c.K1, c.B2, c.l2,
-                                                           c.K2, c.C, c.lc, c.ncols, s, ep);
+                        if (split) {
+                            FR_HIP(m, frd::launch_opmul_split(4 * t + c.op, sop, c.B1, c.l1, c.K1, c.B2, c.l2,
+                                                              c.K2, c.C, c.lc, c.ncols, s, ep));
+                            return FR_OK;
+                        }
                     }
-                    return frd::launch_opmul<T>(4 * t + c.op, op, c.B1, c.l1, c.K1, c.B2, c.l2, c.K2,
-                                                c.C, c.lc, c.ncols, s, ep);
+                    FR_HIP(m, frd::launch_opmul<T>(4 * t + c.op, op, c.B1, c.l1, c.K1, c.B2, c.l2, c.K2,
+                                                   c.C, c.lc, c.ncols, s, ep));
+                    return FR_OK;
                 };
-                FR_HIP(m, run());
-                FR_HIP(m, hipEventRecord(e0, s));
-                for (int r = 0; r < 3; ++r) FR_HIP(m, run());
-                FR_HIP(m, hipEventRecord(e1, s));
-                FR_HIP(m, hipEventSynchronize(e1));
                 float ms = 0;
-                FR_HIP(m, hipEventElapsedTime(&ms, e0, e1));
+                if ((st = timed(run, ms))) return st;
                 tried.push_back({cap, stage, ms, op, sop, mine});
             }
             std::stable_sort(tried.begin(), tried.end(), [](const Variant &x, const Variant &y) { return x.ms < y.ms; });
-            while (tried.size() > 4 || tried.back().ms > 1.1f * tried[0].ms) {
+            while (tried.size() > 4 || (tried.size() > 1 && tried.back().ms > 1.1f * tried[0].ms)) {
                 for (void *p : tried.back().bufs) (void)hipFree(p);
                 tried.pop_back();
             }

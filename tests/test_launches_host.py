@@ -248,3 +248,18 @@ def test_products_that_tie_alone_are_decided_by_the_stage(stand_in):
         ks = [k for k in step(m) if re.search(DIV, k)]
         assert ks and not any("lds" in k for k in ks), ks
     """))
+
+
+@pytest.mark.parametrize("us", (-3.0, -1.0))
+def test_tuning_survives_times_that_are_not_positive(stand_in, us):
+    """Two event times of different clock corrections can lie a few
+    microseconds the wrong way round; so can every time of a variant."""
+    _run(stand_in, textwrap.dedent(TUNED) + textwrap.dedent(f"""
+        for prec in ("fp32", "fp64", "split_bf16"):
+            m = frlib.Mesh(mixed(), 2, system="euler", precision=prec)
+            costs({{"opmul": {us}}})
+            report = m.autotune()
+            assert re.search(r"pri op3 cap \\d stage \\d", report), report
+            rhs(m)
+            m.close()
+    """))
