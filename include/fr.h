@@ -381,10 +381,12 @@ fr_status fr_set_blocking(fr_mesh mesh, int32_t etype, int32_t op, int32_t cap, 
  * Per-problem states use the same layout as a single mesh of that problem:
  * [n_upts][5][ld] with ld from fr_batch_query.  fr_batch_set_dt sets one step
  * size per problem (host array of n doubles).  fr_batch_rk_step advances every
- * problem n_steps steps on `stream`; with graphs enabled (the default) an
- * RK45[2R+] step of all groups is captured once as a HIP graph, one branch
- * per group, and replayed (one graph launch per step).  Errors as for meshes; messages from
- * fr_batch_last_error. */
+ * problem n_steps steps on `stream`.  The merged groups share nothing: they
+ * run side by side on streams of the batch, forked from `stream` and joined to
+ * it, or with fr_batch_set_graph(batch, 0) one after the other on `stream`;
+ * the results are the same bits.  (The switch is named after the step graph
+ * that the batch once replayed; it captures none.)  Errors as for meshes;
+ * messages from fr_batch_last_error. */
 typedef struct fr_batch_s *fr_batch;
 fr_status fr_batch_create(int32_t n, const fr_mesh_desc *descs, void *stream, fr_batch *out);
 fr_status fr_batch_destroy(fr_batch batch);

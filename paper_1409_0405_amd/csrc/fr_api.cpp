@@ -1818,31 +1818,17 @@ struct fr_batch_s {
         int nu[frh::NTYPE] = {};
     };
     std::vector<Prob> prob;
-    hipStream_t stream = nullptr;             // stream the step graph replays on
-    hipEvent_t ev_in = nullptr, ev_out = nullptr;
-    // branches of the step graph: the groups' steps are independent (each
-    // group has its own buffers), and only capture uses these streams
+    // streams of the groups, forked from the caller's and joined to it
     hipStream_t branch[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t ev_fork = nullptr, ev_join[4] = {nullptr, nullptr, nullptr, nullptr};
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    // register pointers (group, type, register) the graph was captured with:
-    // an RK4 step swaps registers, after which the graph would advance a
-    // stale buffer, so a mismatch re-captures it
-    std::vector<const void *> graph_regs;
-    bool use_graph = true;
+    bool branches = true;                    // fr_batch_set_graph
     std::string err;
     ~fr_batch_s() {
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
-        if (ev_in) (void)hipEventDestroy(ev_in);
-        if (ev_out) (void)hipEventDestroy(ev_out);
         if (ev_fork) (void)hipEventDestroy(ev_fork);
         for (int g = 0; g < 4; ++g) {
             if (ev_join[g]) (void)hipEventDestroy(ev_join[g]);
             if (branch[g]) (void)hipStreamDestroy(branch[g]);
         }
-        if (stream) (void)hipStreamDestroy(stream);
     }
 };
 
@@ -2349,9 +2335,6 @@ fr_status fr_batch_create(int32_t n, const fr_mesh_desc *descs, void *stream, fr
         if (st) return bfail(nullptr, st, m->err);
         b->group[g] = std::move(m);
     }
-    FR_BHIP(nullptr, hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking));
-    FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming));
-    FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming));
     FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
     for (int g = 0; g < 4; ++g) {
         if (!b->group[g]) continue;
@@ -2366,7 +2349,8 @@ fr_status fr_batch_destroy(fr_batch b) {
     if (!b) return FR_OK;
     for (auto &g : b->group)
         if (g) (void)hipStreamSynchronize(g->create_stream);
-    if (b->stream) (void)hipStreamSynchronize(b->stream);
+    for (hipStream_t st : b->branch)
+        if (st) (void)hipStreamSynchronize(st);
     delete b;
     return FR_OK;
 }
@@ -2461,7 +2445,7 @@ fr_status fr_batch_set_dt(fr_batch b, const double *dt_host, void *stream) {
 
 fr_status fr_batch_set_graph(fr_batch b, int32_t enable) {
     if (!b) return FR_ERR_INVALID_ARG;
-    b->use_graph = enable != 0;
+    b->branches = enable != 0;
     return FR_OK;
 }
 
@@ -2478,67 +2462,33 @@ fr_status fr_batch_rk_step(fr_batch b, int32_t scheme, int32_t n_steps, void *st
                                               : rk_impl<double>(m, scheme, 1.0, steps, st, true, false);
         return r ? bfail(b, r, m->err) : FR_OK;
     };
-    auto step_all = [&](hipStream_t st, int steps) -> fr_status {
+    if (!b->branches) {
         for (int g = 0; g < 4; ++g)
-            if (fr_status r = step_group(g, st, steps)) return r;
+            if (fr_status r = step_group(g, s, n_steps)) return r;
         return FR_OK;
-    };
-    // In the graph the groups are parallel branches: one after the other, a
-    // sixth of a step was gaps between launches, and the ends of kernels no
-    // longer fill the chip (48 problems of 150 to 6,000 elements, orders 1 to
-    // 4, ten steps: 11.40 -> 8.54 ms).
-    auto capture_step = [&]() -> fr_status {
-        FR_BHIP(b, hipEventRecord(b->ev_fork, b->stream));
-        fr_status r = FR_OK;
-        for (int g = 0; g < 4; ++g) {
-            if (!b->group[g]) continue;
-            FR_BHIP(b, hipStreamWaitEvent(b->branch[g], b->ev_fork, 0));
+    }
+    // The groups share nothing and run side by side: one after the other, the
+    // ends of kernels do not fill the chip (48 problems of 150 to 6,000
+    // elements, orders 1 to 4, ten steps: 9.83 -> 8.20 ms).  They take turns
+    // step by step, so that no group waits for the launches of another's call.
+    // Not a captured graph, which is a little faster for several large groups
+    // (7.97 ms) and slower for few small ones (4 problems of at most 400
+    // elements, eight steps: 1.36 ms, and 1.16 ms so): a process that had made,
+    // stepped and destroyed several batches with one ended in a host
+    // segmentation fault, whose cause was not found.
+    FR_BHIP(b, hipEventRecord(b->ev_fork, s));
+    fr_status r = FR_OK;
+    for (int g = 0; g < 4; ++g)
+        if (b->group[g]) FR_BHIP(b, hipStreamWaitEvent(b->branch[g], b->ev_fork, 0));
+    for (int k = 0; k < n_steps; ++k)
+        for (int g = 0; g < 4; ++g)
             if (!r) r = step_group(g, b->branch[g], 1);
-            FR_BHIP(b, hipEventRecord(b->ev_join[g], b->branch[g]));
-            FR_BHIP(b, hipStreamWaitEvent(b->stream, b->ev_join[g], 0));
-        }
-        return r;
-    };
-    // RK4 swaps its registers every step and cannot be replayed as one graph
-    if (!b->use_graph || scheme != FR_RK45_2RP) return step_all(s, n_steps);
-    std::vector<const void *> regs;
     for (int g = 0; g < 4; ++g) {
-        fr_mesh m = b->group[g].get();
-        if (!m) continue;
-        for (int t = 0; t < frh::NTYPE; ++t)
-            for (int r = 0; r < 3; ++r)
-                regs.push_back(m->precision != FR_FP64 ? static_cast<const void *>(dev_of<float>(m).t[t].reg[r])
-                                                       : static_cast<const void *>(dev_of<double>(m).t[t].reg[r]));
+        if (!b->group[g]) continue;
+        FR_BHIP(b, hipEventRecord(b->ev_join[g], b->branch[g]));
+        FR_BHIP(b, hipStreamWaitEvent(s, b->ev_join[g], 0));
     }
-    if (b->exec && regs != b->graph_regs) {
-        // the captured launches still use the previous register order: wait
-        // for its replays on the batch stream, then capture again
-        FR_BHIP(b, hipStreamSynchronize(b->stream));
-        FR_BHIP(b, hipGraphExecDestroy(b->exec));
-        FR_BHIP(b, hipGraphDestroy(b->graph));
-        b->exec = nullptr;
-        b->graph = nullptr;
-    }
-    if (!b->exec) {
-        FR_BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-        fr_status r = capture_step();
-        hipGraph_t gph = nullptr;
-        hipError_t e = hipStreamEndCapture(b->stream, &gph);
-        if (r) {
-            if (gph) (void)hipGraphDestroy(gph);
-            return r;
-        }
-        if (e != hipSuccess) return bfail(b, FR_ERR_DEVICE, std::string("graph capture: ") + hipGetErrorString(e));
-        b->graph = gph;
-        FR_BHIP(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
-        b->graph_regs = regs;
-    }
-    FR_BHIP(b, hipEventRecord(b->ev_in, s));
-    FR_BHIP(b, hipStreamWaitEvent(b->stream, b->ev_in, 0));
-    for (int i = 0; i < n_steps; ++i) FR_BHIP(b, hipGraphLaunch(b->exec, b->stream));
-    FR_BHIP(b, hipEventRecord(b->ev_out, b->stream));
-    FR_BHIP(b, hipStreamWaitEvent(s, b->ev_out, 0));
-    return FR_OK;
+    return r;
 }
 
 const char *fr_batch_last_error(fr_batch b) { return b ? b->err.c_str() : g_create_error.c_str(); }

@@ -423,6 +423,8 @@ class Batch:
         self._check(lib().fr_batch_set_dt(self.h, _ptr(a, ctypes.c_double), ctypes.c_void_p(stream)))
 
     def set_graph(self, enable):
+        """Groups side by side on streams of their own (the default), or one
+        after the other on the caller's stream."""
         self._check(lib().fr_batch_set_graph(self.h, 1 if enable else 0))
 
     def rk_step(self, scheme, n_steps, stream=0):

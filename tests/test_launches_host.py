@@ -263,3 +263,25 @@ def test_tuning_survives_times_that_are_not_positive(stand_in, us):
             rhs(m)
             m.close()
     """))
+
+
+@pytest.mark.parametrize("scheme", ("FR_RK45_2RP", "FR_RK4", "FR_FWD_EULER"))
+def test_batches_launch_every_step(stand_in, scheme):
+    """No step is replayed from an earlier call, and the groups take turns
+    step by step; side by side or one after the other, a step is the same
+    launches."""
+    _run(stand_in, f"""
+        B = frlib.Batch([(mixed(), 2), (mixed(), 4), (mixed(2), 2)], system="euler", precision="fp32")
+        def step(n):
+            S.stand_in_clear()
+            B.rk_step(frlib.{scheme}, n)
+            return [k for _, _, k in log()]
+        costs()
+        want = step(1)
+        assert want and step(1) == want and step(3) == 3 * want
+        B.set_graph(False)
+        assert step(1) == want
+        B.set_graph(True)
+        assert step(2) == 2 * want
+        B.close()
+    """)
