@@ -382,7 +382,7 @@ fr_status fr_set_blocking(fr_mesh mesh, int32_t etype, int32_t op, int32_t cap, 
  * [n_upts][5][ld] with ld from fr_batch_query.  fr_batch_set_dt sets one step
  * size per problem (host array of n doubles).  fr_batch_rk_step advances every
  * problem n_steps steps on `stream`.  The merged groups share nothing: they
- * run side by side on streams of the batch, forked from `stream` and joined to
+ * run side by side on three streams of the batch, forked from `stream` and joined to
  * it, or with fr_batch_set_graph(batch, 0) one after the other on `stream`;
  * the results are the same bits.  (The switch is named after the step graph
  * that the batch once replayed; it captures none.)  Errors as for meshes;

@@ -1818,16 +1818,22 @@ struct fr_batch_s {
         int nu[frh::NTYPE] = {};
     };
     std::vector<Prob> prob;
-    // streams of the groups, forked from the caller's and joined to it
-    hipStream_t branch[4] = {nullptr, nullptr, nullptr, nullptr};
-    hipEvent_t ev_fork = nullptr, ev_join[4] = {nullptr, nullptr, nullptr, nullptr};
+    // Streams of the groups, forked from the caller's and joined to it: three,
+    // because a process has four hardware queues and the caller's stream one
+    // of them.  With a stream for each group two shared a queue, by chance the
+    // longest two (48 problems of 150 to 6,000 elements, orders 1 to 4, ten
+    // steps: 8.56 -> 7.24 ms; one order after the other 10.18 ms).
+    static constexpr int NBRANCH = 3;
+    hipStream_t branch[NBRANCH] = {nullptr, nullptr, nullptr};
+    hipEvent_t ev_fork = nullptr, ev_join[NBRANCH] = {nullptr, nullptr, nullptr};
+    int branch_of[4] = {0, 0, 0, 0};         // branch of a group
     bool branches = true;                    // fr_batch_set_graph
     std::string err;
     ~fr_batch_s() {
         if (ev_fork) (void)hipEventDestroy(ev_fork);
-        for (int g = 0; g < 4; ++g) {
-            if (ev_join[g]) (void)hipEventDestroy(ev_join[g]);
-            if (branch[g]) (void)hipStreamDestroy(branch[g]);
+        for (int i = 0; i < NBRANCH; ++i) {
+            if (ev_join[i]) (void)hipEventDestroy(ev_join[i]);
+            if (branch[i]) (void)hipStreamDestroy(branch[i]);
         }
     }
 };
@@ -2336,10 +2342,21 @@ fr_status fr_batch_create(int32_t n, const fr_mesh_desc *descs, void *stream, fr
         b->group[g] = std::move(m);
     }
     FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
-    for (int g = 0; g < 4; ++g) {
+    // the largest group first, each to the branch with the least work so far
+    int64_t work[4] = {0, 0, 0, 0}, load[fr_batch_s::NBRANCH] = {};
+    for (int g = 0; g < 4; ++g)
+        for (int t = 0; b->group[g] && t < frh::NTYPE; ++t)
+            if (const frh::TypeHost &H = b->group[g]->host.t[t]; H.ld) work[g] += H.ops.nu * H.ld;
+    int order[4] = {0, 1, 2, 3};
+    std::stable_sort(order, order + 4, [&](int x, int y) { return work[x] > work[y]; });
+    for (int g : order) {
         if (!b->group[g]) continue;
-        FR_BHIP(nullptr, hipStreamCreateWithFlags(&b->branch[g], hipStreamNonBlocking));
-        FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_join[g], hipEventDisableTiming));
+        const int i = int(std::min_element(load, load + fr_batch_s::NBRANCH) - load);
+        load[i] += work[g];
+        b->branch_of[g] = i;
+        if (b->branch[i]) continue;
+        FR_BHIP(nullptr, hipStreamCreateWithFlags(&b->branch[i], hipStreamNonBlocking));
+        FR_BHIP(nullptr, hipEventCreateWithFlags(&b->ev_join[i], hipEventDisableTiming));
     }
     *out = b.release();
     return FR_OK;
@@ -2469,24 +2486,23 @@ fr_status fr_batch_rk_step(fr_batch b, int32_t scheme, int32_t n_steps, void *st
     }
     // The groups share nothing and run side by side: one after the other, the
     // ends of kernels do not fill the chip (48 problems of 150 to 6,000
-    // elements, orders 1 to 4, ten steps: 9.83 -> 8.20 ms).  They take turns
+    // elements, orders 1 to 4, ten steps: 10.18 -> 7.24 ms).  They take turns
     // step by step, so that no group waits for the launches of another's call.
-    // Not a captured graph, which is a little faster for several large groups
-    // (7.97 ms) and slower for few small ones (4 problems of at most 400
-    // elements, eight steps: 1.36 ms, and 1.16 ms so): a process that had made,
-    // stepped and destroyed several batches with one ended in a host
-    // segmentation fault, whose cause was not found.
+    // Not a captured graph (7.85 ms; 4 problems of at most 400 elements, eight
+    // steps: 1.36 ms, and 1.18 so): a process that had made, stepped and
+    // destroyed several batches with one ended in a host segmentation fault,
+    // whose cause was not found.
     FR_BHIP(b, hipEventRecord(b->ev_fork, s));
     fr_status r = FR_OK;
-    for (int g = 0; g < 4; ++g)
-        if (b->group[g]) FR_BHIP(b, hipStreamWaitEvent(b->branch[g], b->ev_fork, 0));
+    for (hipStream_t st : b->branch)
+        if (st) FR_BHIP(b, hipStreamWaitEvent(st, b->ev_fork, 0));
     for (int k = 0; k < n_steps; ++k)
         for (int g = 0; g < 4; ++g)
-            if (!r) r = step_group(g, b->branch[g], 1);
-    for (int g = 0; g < 4; ++g) {
-        if (!b->group[g]) continue;
-        FR_BHIP(b, hipEventRecord(b->ev_join[g], b->branch[g]));
-        FR_BHIP(b, hipStreamWaitEvent(s, b->ev_join[g], 0));
+            if (!r) r = step_group(g, b->branch[b->branch_of[g]], 1);
+    for (int i = 0; i < fr_batch_s::NBRANCH; ++i) {
+        if (!b->branch[i]) continue;
+        FR_BHIP(b, hipEventRecord(b->ev_join[i], b->branch[i]));
+        FR_BHIP(b, hipStreamWaitEvent(s, b->ev_join[i], 0));
     }
     return r;
 }
