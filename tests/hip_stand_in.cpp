@@ -153,7 +153,7 @@ int hipGetSymbolAddress(void **p, const void *sym) {
     return 0;
 }
 
-// ---- events, streams, graphs ----
+// ---- events, streams ----
 int hipEventCreateWithFlags(void **e, unsigned) {
     *e = new double(0);
     return 0;
@@ -182,22 +182,4 @@ int hipStreamDestroy(void *s) {
 }
 int hipStreamSynchronize(void *) { return 0; }
 int hipStreamWaitEvent(void *, void *, unsigned) { return 0; }
-int hipStreamBeginCapture(void *, int) { return 0; }
-int hipStreamEndCapture(void *, void **g) {
-    *g = std::malloc(1);
-    return 0;
-}
-int hipGraphInstantiate(void **x, void *, void **, char *, size_t) {
-    *x = std::malloc(1);
-    return 0;
-}
-int hipGraphLaunch(void *, void *) { return 0; }
-int hipGraphDestroy(void *g) {
-    std::free(g);
-    return 0;
-}
-int hipGraphExecDestroy(void *x) {
-    std::free(x);
-    return 0;
-}
 }
